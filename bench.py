@@ -40,20 +40,36 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
 BYTES_PER_CELL = {"fp64": 432, "fp32": 216, "fp16": 108, "bf16": 108,  # 27 reads + 27 writes
                   "mom32": 72}  # moment representation: 9 FP32 numbers read + 9 written
+
+
+
+def bytes_per_cell(storage, steps):
+    """HBM bytes per cell and step of one call of `steps` steps on a large
+    lattice: FP64 and FP32 storage pass through the nine numbers (k_march)
+    between the first step, 27 in and 9 out, and the last, 9 in and 27 out."""
+    full = BYTES_PER_CELL[storage]
+    if storage not in ("fp64", "fp32") or steps < 2:
+        return full
+    size = full // 54
+    return size * (2 * 36 + 18 * (steps - 2)) / steps
+
+
 # template arguments: storage, cells per lane, solid mask, force field, non-temporal stores, collision model,
 # fused reductions, stochastic rounding
-STEP_KERNEL = {"fp32": "k_step<1, 1, false, false, true, 0, false, false>",
+# (FP64 / FP32: the inner steps of a call, k_march: type, tile rows, field, mask, populations out)
+STEP_KERNEL = {"fp32": "k_march<float, 12, false, false, false>",
                "fp16": "k_step<2, 2, false, false, true, 0, false, false>",
                "fp16sr": "k_step<2, 2, false, false, true, 0, false, true>",
                "bf16": "k_step<3, 2, false, false, true, 0, false, false>",
                "bf16sr": "k_step<3, 2, false, false, true, 0, false, true>",
-               "fp64": "k_step<0, 1, false, false, true, 0, false, false>"}
+               "fp64": "k_march<double, 8, false, false, false>"}
 # committed rocprofv3 counter summary (FETCH_SIZE, WRITE_SIZE) of every step configuration
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "k_step_counters.md")
 MOM_COUNTERS_FILE = os.path.join(ROOT, "profiles", "k_step_mom_tgv_counters.md")
 # non-packed FP32 VALU: 256 CUs x 4 SIMDs x 16 lanes per clock x 2.4 GHz
 VALU_PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_1905_10182_amd", "csrc", f) for f in ("cmlbm.hip", "d3q27.hpp")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_1905_10182_amd", "csrc", f) 
+                  for f in ("cmlbm.hip", "d3q27.hpp", "lockstep.hpp")]
 ALL_LEGS = ("fp32", "precision", "fp64", "mom", "d2q9", "mhd", "shanchen", "fused", "copy", "conv", "warmstart", "cpu")
 
 
@@ -111,7 +127,7 @@ def alu_roofline(n, glups):
     if v is None:
         return None
     a = v * glups * 1e9
-    return {"bound": "alu", "kernel": "k_step_mom", "achieved": round(a / 1e12, 2), "peak": round(VALU_PEAK_LANE_OPS / 1e12, 2),
+    return {"bound": "alu", "kernel": "k_march", "achieved": round(a / 1e12, 2), "peak": round(VALU_PEAK_LANE_OPS / 1e12, 2),
             "unit": "T lane-op/s", "frac": round(a / VALU_PEAK_LANE_OPS, 4), "valu_lane_ops_per_cell": v}
 
 
@@ -160,7 +176,7 @@ def run_gpu(n, storage, steps, warmup, repeats, stochastic=False, fields=None):
     r1 = lat.reduce()
     assert r1[0, 6] == 0, "non-finite state"
     lat.close()
-    out = rate(n ** 3, steps, windows, BYTES_PER_CELL[storage])
+    out = rate(n ** 3, steps, windows, bytes_per_cell(storage, steps))
     out["mass_drift"] = abs(r1[0, 0] / r0[0, 0] - 1)
     return out
 
@@ -212,7 +228,7 @@ def precision_legs(n, names, steps, warmup, repeats, error_steps, fields):
         log(f"  {name}: {err} ({t_err:.1f} s)")
         if name != "fp64":  # FP64 storage is timed at the headline size
             windows = time_steps(lat, steps, warmup, repeats)
-            row.update(rate(n ** 3, steps, windows, BYTES_PER_CELL[st]))
+            row.update(rate(n ** 3, steps, windows, bytes_per_cell(st, steps)))
             row["traffic"] = measured_traffic(name)
             log(f"  {name}: {row['glups']:.2f} GLUPS, {row['hbm_gbs']:.0f} GB/s")
         lat.close()
@@ -659,7 +675,7 @@ def main():
         log(f"TGV {n}^3 fp64 storage")
         r64 = run_gpu(n, "fp64", K, W, R, fields=fields)
         extra["fp64_storage"] = {"workload": f"taylor_green_{n}, fp64 populations and arithmetic",
-                                 "kernel": STEP_KERNEL["fp64"], "bytes_per_cell": BYTES_PER_CELL["fp64"],
+                                 "kernel": STEP_KERNEL["fp64"], "bytes_per_cell": round(bytes_per_cell("fp64", K), 2),
                                  "traffic": measured_traffic("fp64"), **r64}
         log(f"fp64 {r64['glups']:.2f} GLUPS")
     if "fused" in legs:
@@ -775,7 +791,7 @@ def main():
         "roofline": None if main_run is None else {
             "bound": "hbm", "kernel": STEP_KERNEL["fp32"], "achieved": main_run["hbm_gbs"], "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": main_run["hbm_frac"], "traffic": measured_traffic("fp32"),
-            "bytes_per_cell": BYTES_PER_CELL["fp32"], "window_ms_per_step": main_run["window_ms_per_step"],
+            "bytes_per_cell": round(bytes_per_cell("fp32", K), 2), "window_ms_per_step": main_run["window_ms_per_step"],
             "source_digest": source_digest(),
             # the same row-block access pattern with no arithmetic, timed in this run (copy leg)
             "pattern_copy_gbs": extra["pattern_copy"]["gbs"] if "pattern_copy" in extra else None},

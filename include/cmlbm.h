@@ -177,7 +177,11 @@ int cmlbm_init(cmlbm_lattice* lat, const void* dev_rho, const void* dev_u, int i
 /* Advance nsteps >= 0 time steps: each step is one fused launch doing the
  * pull-streaming gather (eq. "streaming"), collision in central-moment space
  * (eqs. "macroscopic", "pre_collision",
- * "post_collision_central_moments_forcing", "system") and the store. */
+ * "post_collision_central_moments_forcing", "system") and the store.  FP64 and
+ * FP32 storage may pass through the nine numbers that determine the
+ * post-collision populations between the first and the last step of a call
+ * (chosen by size); the populations after n steps are the same bits however n
+ * is split into calls.  The buffer that does not hold the state is scratch. */
 int cmlbm_step(cmlbm_lattice* lat, int32_t nsteps, void* hip_stream);
 
 /* rho(x, t) into dev_rho[N] and u(x, t) = (sum f c + F/2)/rho into dev_u[3][N]

@@ -5,6 +5,8 @@
 // Kernels
 //   k_step       fused pull-stream gather + collision + store (the hot path);
 //                with RED also the FP64 partial sums of the state it reads
+//   k_march      the step of the moment representation: moment storage, and
+//                FP64 / FP32 storage between the first and last step of a call
 //   k_red_waves  second level of those sums
 //   k_init       inverse of the gather: writes a given pre-collision state
 //   k_gather     rho/u or FP64 populations from the current state
@@ -20,6 +22,7 @@
 // apart beyond their rows).  Two such buffers alternate between steps.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -31,6 +34,7 @@
 
 #include "cmlbm.h"
 #include "d3q27.hpp"
+#include "lockstep.hpp"
 
 using namespace cmlbm;
 
@@ -44,7 +48,7 @@ constexpr int kModelEq2 = 2;  // second-order equilibrium
 constexpr int kModelBgk = 4;  // single relaxation time
 constexpr int kMaxRedBlocks = 2048;  // reduce workgroups per batch member (half that for FP64 storage)
 constexpr uint32_t kSolidBit = 1u << 27;
-constexpr size_t kPlanePad = 4096;  // bytes between consecutive population planes (a multiple of 256)
+constexpr size_t kPlanePad = 4096;  // bytes between consecutive planes of moment storage (a multiple of 256)
 
 // ---------------------------------------------------------------------------
 // storage types
@@ -260,7 +264,7 @@ __device__ __forceinline__ gchar* uniform_ptr(P* p)
     return (gchar*)(((uint64_t)hi << 32) | lo);
 }
 
-// Raw buffer access for 4-byte vectors: a descriptor in four scalar registers
+// Raw buffer access for 4- and 8-byte values: a descriptor in four scalar registers
 // (wave-uniform base, stride 0, size in bytes, the gfx9 raw-buffer format
 // word) and a 32-bit per-lane byte offset, added to the base by the memory
 // unit instead of by a 64-bit VALU add per access.  Offsets stay below the
@@ -273,16 +277,23 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(gchar* base, uint32_t
 template <typename X>
 __device__ __forceinline__ X ld_buf(gchar* base, uint32_t bytes, uint32_t byte_off)
 {
-    static_assert(sizeof(X) == 4, "4-byte buffer loads only");
-    return __builtin_bit_cast(X, __builtin_amdgcn_raw_buffer_load_b32(row_rsrc(base, bytes), byte_off, 0, 0));
+    static_assert(sizeof(X) == 4 || sizeof(X) == 8, "4- and 8-byte buffer loads only");
+    if constexpr (sizeof(X) == 4)
+        return __builtin_bit_cast(X, __builtin_amdgcn_raw_buffer_load_b32(row_rsrc(base, bytes), byte_off, 0, 0));
+    else
+        return __builtin_bit_cast(X, __builtin_amdgcn_raw_buffer_load_b64(row_rsrc(base, bytes), byte_off, 0, 0));
 }
 // aux bit 1: the non-temporal hint (nt) on gfx94x / gfx950
 template <bool NT, typename X>
 __device__ __forceinline__ void st_buf(gchar* base, uint32_t bytes, uint32_t byte_off, X v)
 {
-    static_assert(sizeof(X) == 4, "4-byte buffer stores only");
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), row_rsrc(base, bytes), byte_off, 0,
-                                          NT ? 2 : 0);
+    static_assert(sizeof(X) == 4 || sizeof(X) == 8, "4- and 8-byte buffer stores only");
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    if constexpr (sizeof(X) == 4)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), row_rsrc(base, bytes), byte_off, 0,
+                                              NT ? 2 : 0);
+    else
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), row_rsrc(base, bytes), byte_off, 0, NT ? 2 : 0);
 }
 
 // load of the X at byte_off from base
@@ -423,7 +434,9 @@ __device__ __forceinline__ double wave_max(double v)
 // cell only skip their contributions and stores.  (RED is a template flag of
 // the kernel itself: a shared device function changed the register
 // allocation of the RED = false kernels.)
-template <int ST, int V, bool MASK, bool FIELD, bool NT, int MODEL, bool RED, bool SR>
+// With MOUT the step stops before the reconstruction and stores the nine
+// numbers that determine the post-collision populations (k_march).
+template <int ST, int V, bool MASK, bool FIELD, bool NT, int MODEL, bool RED, bool SR, bool MOUT = false>
 __global__ __launch_bounds__(step_block(ST, MASK)) void k_step(const typename storage<ST>::S* __restrict__ src,
                                                   typename storage<ST>::S* __restrict__ dst, Geom g, int segs,
                                                   typename storage<ST>::T omega, typename storage<ST>::T rho0,
@@ -435,6 +448,7 @@ __global__ __launch_bounds__(step_block(ST, MASK)) void k_step(const typename st
     static_assert(V == 1 || !MASK, "bounce-back masks use one cell per lane");
     static_assert(MODEL == 0 || V == 1, "comparison models use one cell per lane");
     static_assert(!RED || MODEL == 0, "fused reductions are for the method's collision");
+    static_assert(!MOUT || (V == 1 && MODEL == 0 && !RED && ST <= CMLBM_FP32), "moment output: FP64 / FP32, the method's collision");
     using SS = storage<ST>;
     using S = typename SS::S;
     using T = typename SS::T;
@@ -575,16 +589,35 @@ __global__ __launch_bounds__(step_block(ST, MASK)) void k_step(const typename st
         if constexpr (RED) {
             // collide() with its density deviation kept for the mass sum
             T drho, k5[5], s5[5];
-            pre_collision(h[c], Fx[c], Fy[c], Fz[c], rho0s, drho, ux, uy, uz, k5);
+            const T om1 = T(1) - omega;
+            if constexpr (sizeof(S) == 2)
+                pre_collision(h[c], Fx[c], Fy[c], Fz[c], rho0s, drho, ux, uy, uz, k5);
+            else
+                lockstep::pre_collision(h[c], Fx[c], Fy[c], Fz[c], rho0s, drho, ux, uy, uz, k5);
 #pragma unroll
-            for (int j = 0; j < 5; ++j) s5[j] = (T(1) - omega) * k5[j];
-            reconstruct(drho, ux, uy, uz, Fx[c], Fy[c], Fz[c], s5, rho0s, h[c]);
+            for (int j = 0; j < 5; ++j) s5[j] = om1 * k5[j];
+            if constexpr (sizeof(S) == 2)
+                reconstruct(drho, ux, uy, uz, Fx[c], Fy[c], Fz[c], s5, rho0s, h[c]);
+            else
+                lockstep::reconstruct(drho, ux, uy, uz, Fx[c], Fy[c], Fz[c], s5, rho0s, h[c]);
             mq[c][0] = drho;
             mq[c][1] = ux;
             mq[c][2] = uy;
             mq[c][3] = uz;
-        } else if constexpr (MODEL == 0) {
+        } else if constexpr (MOUT) {
+            T drho, k5[5];
+            lockstep::pre_collision(h[c], Fx[c], Fy[c], Fz[c], rho0s, drho, ux, uy, uz, k5);
+            const T om1 = T(1) - omega;
+            const T v[9] = {drho, ux, uy, uz, om1 * k5[0], om1 * k5[1], om1 * k5[2], om1 * k5[3], om1 * k5[4]};
+#pragma unroll
+            for (int j = 0; j < 9; ++j)
+                st_off<NT>(uniform_ptr(dst + ((uint64_t)row * 9 + j) * g.nxp),
+                           (uint32_t)x0 * (uint32_t)sizeof(S), v[j]);
+            return;
+        } else if constexpr (MODEL == 0 && sizeof(S) == 2) {
             collide<T>(h[c], Fx[c], Fy[c], Fz[c], omega, rho0s, rho, ux, uy, uz);
+        } else if constexpr (MODEL == 0) {
+            lockstep::collide<T>(h[c], Fx[c], Fy[c], Fz[c], omega, rho0s);
         } else {
             collide_model<T, (MODEL & kModelEq2) != 0, (MODEL & kModelGuo) != 0, (MODEL & kModelBgk) != 0>(
                 h[c], Fx[c], Fy[c], Fz[c], omega, rho0s, rho, ux, uy, uz);
@@ -772,87 +805,88 @@ __global__ __launch_bounds__(kBlock) void k_init(typename storage<ST>::S* __rest
 }
 
 // ---------------------------------------------------------------------------
-// moment-representation storage (CMLBM_MOM32)
+// moment representation
 //
-// The state is the post-collision state of the current time t, kept as the
-// nine numbers it is made of: m = (rho - rho0, u, s4..s8 = (1 - omega) k4..k8),
-// FP32 planes [9][nb][nz][ny][nxp].  With the force density they determine the
-// post-collision populations (reconstruct()), so a step moves 9 values per
-// cell instead of 27 each way:
-//   reconstruct f*(t) for a tile and a one-cell halo in LDS, pull
-//   f(x, t + 1) = f*(x - c_i, t) from there, collide (pre_collision()) and
-//   store m of t + 1.
-// Workgroup: a 64 x 6 (x, y) tile marching up a chunk of kMomZC planes.  The
-// 66 x 8 halo tile of a plane is reconstructed by 9 waves (waves 0-7 rows
-// 0-7, columns 1-64; wave 8 the two edge columns of the 8 rows), one cell per
-// lane.  LDS keeps populations by their c_z class: c_z = +1 of the two
-// previous planes, c_z = 0 of the current plane, c_z = -1 of the next one, so
-// every plane of the chunk (and the two halo planes) is reconstructed once.
-// Waves 1-6 then collide the 64 x 6 interior cells of the current plane.
+// The post-collision populations of a cell depend on nine numbers,
+//   m = (rho - rho0, u, s4..s8 = (1 - omega) k4..k8),
+// and its force density (reconstruct()).  So a step can move nine values per
+// cell each way instead of twenty-seven:
+//   reconstruct f*(t) of a tile and a one-cell halo, exchange it through LDS,
+//   pull f(x, t + 1) = f*(x - c_i, t), collide (moments_of_sums()) and store m
+//   of t + 1.
+// CMLBM_MOM32 keeps its state this way.  FP64 and FP32 population storage
+// takes it between the first and the last step of a call (marches()): step 1
+// pulls populations and stores m (k_step with MOUT), the steps between go
+// from m to m, the last one from m to populations (POUT).  The nine numbers
+// are the values that k_step itself holds in registers when it reconstructs,
+// in the storage type, so the populations that come out are the same bits.
 
-constexpr int kMomTX = 64, kMomHX = kMomTX + 2;
-constexpr int kMomZC = 32;  // planes per workgroup
+constexpr int kMomTX = 64;
 
-template <int HY>
-__device__ __forceinline__ int mom_lds(int j, int hy, int hx) { return (j * HY + hy) * kMomHX + hx; }
-
-template <bool FIELD>
-__device__ __forceinline__ void mom_force(const Geom& g, uint64_t lin, int b, int y, const float* __restrict__ ftab,
-                                          const float* __restrict__ field, float F[3])
+// Position of population i among the 24 that the exchange carries (the three
+// with c_x = c_y = 0 stay with their lane).
+__device__ constexpr int xslot(int i)
 {
-    if (FIELD) {
-        F[0] = field[lin];
-        F[1] = field[g.ncell + lin];
-        F[2] = field[2 * g.ncell + lin];
-    } else {
-        const float* fr = ftab + 3 * (b * g.ny + y);
-        F[0] = fr[0];
-        F[1] = fr[1];
-        F[2] = fr[2];
-    }
+    int n = 0;
+    for (int j = 0; j < i; ++j) n += (vel_x(j) != 0 || vel_y(j) != 0);
+    return n;
 }
 
-__device__ __forceinline__ void mom_store(float* __restrict__ dst, uint64_t pstride, uint64_t off, float drho,
-                                          float ux, float uy, float uz, const float k[5], float om1)
+// LDS buffers of the exchange: two (one barrier per plane) where they fit the
+// 160 KB of a CU, else one (two barriers).
+template <typename T>
+constexpr int march_bufs(int TY)
 {
-    __builtin_nontemporal_store(drho, dst + off);
-    __builtin_nontemporal_store(ux, dst + pstride + off);
-    __builtin_nontemporal_store(uy, dst + 2 * pstride + off);
-    __builtin_nontemporal_store(uz, dst + 3 * pstride + off);
-#pragma unroll
-    for (int j = 0; j < 5; ++j) __builtin_nontemporal_store(om1 * k[j], dst + (4 + j) * pstride + off);
+    return 2 * 24 * TY * (kMomTX + 2) * sizeof(T) <= 160 * 1024 ? 2 : 1;
 }
 
-// The same nine stores into one z plane of each moment: plane_k = dst + k *
-// pstride (+ the plane's wave-uniform start), a 32-bit byte offset within it.
-__device__ __forceinline__ void mom_store_plane(float* __restrict__ plane0, uint64_t pstride, uint32_t bytes,
-                                                uint32_t byte_off, float drho, float ux, float uy, float uz,
-                                                const float k[5], float om1)
+// One step on a 64 x TY (x, y) tile, marching up zc planes.  TY + 2 waves
+// reconstruct the rows of the tile and its halo, one cell per lane, one more
+// the two edge columns (not needed where the tile is a whole periodic row).
+// Per source plane p:
+//   reconstruct p (27 values in registers) from the prefetched numbers and
+//   prefetch the numbers of p + 1;
+//   write 24 populations to LDS, each at the cell it streams to; barrier;
+//   the TY interior waves read what arrived at their cells, reduce each c_z
+//   class to its six in-plane sums, and finish plane p - 1.
+// What bounds it: FP32 the issue of vector instructions, about 440 per cell
+// (a reconstruction for each of the 15 waves of a 12-row tile, a collision for
+// 12); FP64 those and HBM.  Per step against k_step: FP32 256^3 649 -> 297 us
+// (56 G cells/s, 4.1 TB/s), 512^3 5250 -> 2240 us; FP64 256^3 1320 -> 510 us
+// (4.7 TB/s), 64 channels of 64 x 32 x 32 with walls 322 -> 140 us.  Moment
+// storage, whose earlier kernel kept the c_z classes in four LDS slots behind
+// two barriers and waited for its stores before each plane: 256^3 314 -> 304
+// us, 512^3 2380 -> 2200 us.
+// The z exchange stays in registers: of source plane p, class c_z = -1 goes
+// to target p - 1, 0 to p, +1 to p + 1, so a lane carries the sums of two
+// classes across iterations and every plane is reconstructed once per chunk
+// (plus two halo planes).  With two LDS buffers, written in turn, one barrier
+// per plane suffices; with one, a second barrier keeps the writes of a plane
+// behind the reads of the last.
+// Bounce-back (MASK): a population pulled from a wall or a solid cell is the
+// cell's own opposite one.  The own populations of a target plane z exist when
+// source plane z is reconstructed, so c_z = +1 is held as pulled until then
+// and the own c_z = +1 values wait one iteration for the c_z = -1 pull.
+template <typename T, int TY, bool FIELD, bool MASK, bool POUT>
+__global__ __launch_bounds__((TY + 3) * 64) void k_march(const T* __restrict__ src, T* __restrict__ dst, Geom g,
+                                                         uint64_t mstride, uint64_t mrow, int zc, T omega, T rho0, const T* __restrict__ ftab,
+                                                         const T* __restrict__ field, const uint32_t* __restrict__ mask,
+                                                         int gens, int cpx)
 {
-    const float v[9] = {drho, ux, uy, uz, om1 * k[0], om1 * k[1], om1 * k[2], om1 * k[3], om1 * k[4]};
-#pragma unroll
-    for (int j = 0; j < 9; ++j) st_buf<true>((gchar*)(plane0 + j * pstride), bytes, byte_off, v[j]);
-}
-
-// TY interior rows per tile: TY + 2 halo rows reconstructed by waves 0..TY+1,
-// the two edge columns of those rows by wave TY + 2.
-template <bool FIELD, int TY>
-__global__ __launch_bounds__((TY + 3) * 64) void k_step_mom(const float* __restrict__ src, float* __restrict__ dst,
-                                                            Geom g, float omega, float rho0,
-                                                            const float* __restrict__ ftab,
-                                                            const float* __restrict__ field, int gens, int cpx)
-{
-    constexpr int HY = TY + 2;
-    constexpr int SLOT = 9 * HY * kMomHX;  // floats: one c_z class of one halo plane
-    __shared__ float sp[2][SLOT];          // c_z = +1 populations, by plane parity
-    __shared__ float s0[SLOT];             // c_z = 0 populations of the current plane
-    __shared__ float sm[SLOT];             // c_z = -1 populations of the next plane
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int NBUF = march_bufs<T>(TY);
+    constexpr int ROW = kMomTX + 2;    // a column of slack on each side takes what leaves the tile along x
+    constexpr int SLOT = TY * ROW;
+    constexpr bool RAW = MASK || sizeof(T) == 4;
+    // FP64 has no registers left for the prefetch across the LDS writes
+    constexpr bool EARLY = sizeof(T) == 4;
+    __shared__ T buf[NBUF * 24 * SLOT];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     // Workgroups are dealt round-robin to the 8 XCDs; each XCD runs cpx of
     // them at a time (one per CU).
     const int ntx = (g.nx + kMomTX - 1) / kMomTX, nty = (g.ny + TY - 1) / TY;
-    const int nzc = (g.nz + kMomZC - 1) / kMomZC;
-    int tx, ty, b, zc;
+    const int nzc = (g.nz + zc - 1) / zc;
+    int tx, ty, b, zk;
     if (gens > 0) {
         // blocked schedule (cpx a multiple of ntx): a generation of an XCD is
         // cpx tiles covering the full x extent and cpx / ntx tile rows, all
@@ -865,7 +899,7 @@ __global__ __launch_bounds__((TY + 3) * 64) void k_step_mom(const float* __restr
         const int by = cpx / ntx, nyb = (nty + by - 1) / by;
         const int pair = xcd * gens + k / cpx, slot = k % cpx;
         if (pair >= g.nb * nyb * nzc) return;
-        zc = pair % nzc;
+        zk = pair % nzc;
         b = pair / (nzc * nyb);
         tx = slot % ntx;
         ty = ((pair / nzc) % nyb) * by + slot / ntx;
@@ -880,124 +914,222 @@ __global__ __launch_bounds__((TY + 3) * 64) void k_step_mom(const float* __restr
         ty = (int)((tile / ntx) % nty);
         const int bzc = (int)(tile / (ntx * nty));
         b = bzc / nzc;
-        zc = bzc % nzc;
+        zk = bzc % nzc;
     }
     const int x0 = tx * kMomTX;
     const int y0 = ty * TY;
-    const int zs = zc * kMomZC;
-    const int ze = zs + kMomZC < g.nz ? zs + kMomZC : g.nz;
+    const int zs = zk * zc;
+    const int ze = zs + zc < g.nz ? zs + zc : g.nz;
     const int nxi = g.nx - x0 < kMomTX ? g.nx - x0 : kMomTX;
     const int nyi = g.ny - y0 < TY ? g.ny - y0 : TY;
-    // reconstruction role: halo cell (hy, hx) of the 66 x HY tile; the right and
-    // bottom halo follow the last interior column / row of a partial tile
-    int hy, hx;
-    bool rec;
-    if (wave < HY) {
-        hy = wave;
-        hx = lane + 1;
-        rec = lane < nxi && hy <= nyi + 1;
-    } else {
-        hy = lane >> 1;
-        hx = (lane & 1) ? nxi + 1 : 0;
-        rec = lane < 2 * HY && hy <= nyi + 1;
+    const bool whole_row = ntx == 1;
+    // tile cell (hx, hy) of this lane, from -1 to nxi, nyi (the halo follows the
+    // last interior column / row of a partial tile): waves 0 and 1 the halo
+    // rows, wave 2 the edge columns of all rows, wave 3 + y interior row y
+    // (a CU's four SIMDs take waves in turn, so each gets about as many
+    // interior waves)
+    int hy = wave == 0 ? -1 : wave == 1 ? nyi : wave - 3, hx = lane;
+    bool rec = lane < nxi && hy < nyi + (wave == 1);
+    if (wave == 2) {
+        hy = (lane >> 1) - 1;
+        hx = (lane & 1) ? nxi : -1;
+        rec = !whole_row && hy <= nyi;
     }
-    const int gx = wrap(x0 + hx - 1, g.nx), gy = wrap(y0 + hy - 1, g.ny);
-    // collision role: interior cell (wave, lane + 1), waves 1..TY
-    const bool inter = wave >= 1 && wave <= nyi && lane < nxi;
-    const int iy = y0 + wave - 1, ix = x0 + lane;
-    const float om1 = 1.f - omega;
-    auto row_of = [&](int z, int y) -> uint64_t { return ((uint64_t)(b * g.nz + z) * g.ny + y) * g.nxp; };
-    auto lin_of = [&](int z, int y, int x) -> uint64_t { return ((uint64_t)(b * g.nz + z) * g.ny + y) * g.nx + x; };
-    // loads and stores address one z plane of a moment (wave-uniform start,
-    // ny * nxp floats) with a loop-invariant 32-bit lane offset
-    const uint32_t plane_bytes = (uint32_t)g.ny * (uint32_t)g.nxp * 4u;
-    const uint32_t rec_off = ((uint32_t)gy * (uint32_t)g.nxp + (uint32_t)gx) * 4u;
-    const uint32_t int_off = ((uint32_t)(inter ? iy : 0) * (uint32_t)g.nxp + (uint32_t)ix) * 4u;
-    // the force field the same way, in its unpadded [3][cells] layout
-    const uint32_t fplane_bytes = (uint32_t)g.ny * (uint32_t)g.nx * 4u;
-    const uint32_t rec_foff = ((uint32_t)gy * (uint32_t)g.nx + (uint32_t)gx) * 4u;
-    const uint32_t int_foff = ((uint32_t)(inter ? iy : 0) * (uint32_t)g.nx + (uint32_t)ix) * 4u;
-    auto field_at = [&](int z, uint32_t off, float F[3]) {
-        const float* p0 = field + lin_of(z, 0, 0);
+    const int gx = wrap(x0 + hx, g.nx), gy = rec ? wrap(y0 + hy, g.ny) : 0;
+    const T om1 = T(1) - omega;
+    auto row_of = [&](int z) -> uint64_t { return (uint64_t)(b * g.nz + z) * g.ny; };  // first row of a plane
+    // loads and stores address one z plane of a number or population
+    // (wave-uniform start) with a loop-invariant 32-bit lane offset.  Lanes
+    // without a cell take an offset past the buffer's range: their loads give
+    // 0 and their stores are dropped, so that no load or store of the loops is
+    // under a branch (with branches the compiler cannot count what is in
+    // flight and waits for everything, the stores included, before each plane)
+    constexpr uint32_t kNone = 0xffffff00u;
+    const uint32_t mbytes = (uint32_t)g.ny * (uint32_t)mrow * (uint32_t)sizeof(T);
+    const uint32_t moff = rec ? ((uint32_t)gy * (uint32_t)mrow + (uint32_t)gx) * (uint32_t)sizeof(T) : kNone;
+    const uint32_t pbytes = (uint32_t)g.ny * (uint32_t)g.rstride * (uint32_t)sizeof(T);
+    const uint32_t poff = rec ? ((uint32_t)gy * (uint32_t)g.rstride + (uint32_t)gx) * (uint32_t)sizeof(T) : kNone;
+    // the force field the same way, in its unpadded [3][cells] layout, and the link mask
+    const uint32_t fbytes = (uint32_t)g.ny * (uint32_t)g.nx * (uint32_t)sizeof(T);
+    const uint32_t foff = rec ? ((uint32_t)gy * (uint32_t)g.nx + (uint32_t)gx) * (uint32_t)sizeof(T) : kNone;
+    const uint32_t kbytes = (uint32_t)g.ny * (uint32_t)g.nxp * 4u;
+    const uint32_t koff = rec ? ((uint32_t)gy * (uint32_t)g.nxp + (uint32_t)gx) * 4u : kNone;
+    // LDS positions: of this lane's cell, and of the cells it streams to along
+    // x (per c_x; rows c_y away are a constant step)
+    int put[3];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) F[a] = ld_buf<float>((gchar*)(p0 + a * g.ncell), fplane_bytes, off);
-    };
+    for (int a = 0; a < 3; ++a) {
+        int col = hx + a - 1;
+        if (whole_row) col = wrap(col, nxi);
+        // what leaves the tile along x, and lanes without a cell: the columns of slack
+        col = !rec || col > kMomTX ? kMomTX : col < -1 ? -1 : col;
+        put[a] = hy * ROW + col + 1;
+    }
+    const int get = hy * ROW + lane + 1;
 
-    float mreg[9], freg[3] = {0.f, 0.f, 0.f};
-    auto load_m = [&](int zu) {
-        if (!rec) return;
+    // force of the loaded plane, of plane p and of the target plane p - 1: one
+    // set of registers where it does not vary along z
+    T Fn[3], Fbuf[2][3];
+    T(&F)[3] = FIELD ? Fbuf[0] : Fn;
+    T(&Fz)[3] = FIELD ? Fbuf[1] : Fn;
+    T mreg[9];
+    uint32_t mk = 0;  // link mask of the loaded plane
+    if (!FIELD) {
+        const T* fr = ftab + 3 * (b * g.ny + gy);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            Fn[a] = fr[a];
+            asm volatile("" : "+v"(Fn[a]));  // arrived before the loops: not counted in there
+        }
+    }
+    auto load_plane = [&](int zu) {
         const int z = wrap(zu, g.nz);
-        const float* plane0 = src + row_of(z, 0);
+        const T* p0 = src + row_of(z) * mrow;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) mreg[k] = ld_buf<float>((gchar*)(plane0 + k * g.pstride), plane_bytes, rec_off);
-        if (FIELD) field_at(z, rec_foff, freg);
-    };
-    float h[27];
-    auto recon = [&]() {
-        float F[3];
+        for (int k = 0; k < 9; ++k) mreg[k] = ld_buf<T>((gchar*)(p0 + k * mstride), mbytes, moff);
         if (FIELD) {
-            F[0] = freg[0];
-            F[1] = freg[1];
-            F[2] = freg[2];
-        } else {
-            mom_force<false>(g, 0, b, gy, ftab, field, F);
-        }
-        const float sh[5] = {mreg[4], mreg[5], mreg[6], mreg[7], mreg[8]};
-        reconstruct<float>(mreg[0], mreg[1], mreg[2], mreg[3], F[0], F[1], F[2], sh, rho0, h);
-    };
-    auto put = [&](float* slot, int cz) {
+            const T* f0 = field + row_of(z) * g.nx;
 #pragma unroll
-        for (int i = 0; i < 27; ++i)
-            if (vel_z(i) == cz) slot[mom_lds<HY>((vel_y(i) + 1) * 3 + vel_x(i) + 1, hy, hx)] = h[i];
+            for (int a = 0; a < 3; ++a) Fn[a] = ld_buf<T>((gchar*)(f0 + a * g.ncell), fbytes, foff);
+        }
+        if (MASK) mk = ld_buf<uint32_t>((gchar*)(mask + row_of(z) * g.nxp), kbytes, koff);
+    };
+    // the first plane, arrived before the loops: then the count of what is in
+    // flight at a loop's head is that of its own last iteration
+    auto first_plane = [&]() {
+        load_plane(zs - 1);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) asm volatile("" : "+v"(mreg[k]));
+        if (FIELD) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) asm volatile("" : "+v"(Fn[a]));
+        }
+        if (MASK) asm volatile("" : "+v"(mk));
+    };
+    // plane p: its numbers to populations, the prefetch of plane p + 1, and the exchange
+    T h[27];
+    T* slots = buf;
+    auto exchange = [&](int p) {
+        if (FIELD) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) F[a] = Fn[a];
+        }
+        const T sh[5] = {mreg[4], mreg[5], mreg[6], mreg[7], mreg[8]};
+        lockstep::reconstruct<T>(mreg[0], mreg[1], mreg[2], mreg[3], F[0], F[1], F[2], sh, rho0, h);
+        if (EARLY) load_plane(p < ze ? p + 1 : ze);
+        if (NBUF == 2)
+            slots = buf + (p & 1) * (24 * SLOT);
+        else
+            __syncthreads();
+#pragma unroll
+        for (int cy = -1; cy <= 1; ++cy) {
+            if (hy + cy < 0 || hy + cy >= nyi) continue;
+#pragma unroll
+            for (int i = 0; i < 27; ++i)
+                if (vel_y(i) == cy && (vel_x(i) != 0 || cy != 0))
+                    slots[xslot(i) * SLOT + cy * ROW + put[vel_x(i) + 1]] = h[i];
+        }
+        if (!EARLY) load_plane(p < ze ? p + 1 : ze);
+        __syncthreads();
     };
 
-    // prologue: c_z = +1 populations of plane zs - 1, c_z = +1 and 0 of plane zs
-    load_m(zs - 1);
-    if (rec) {
-        recon();
-        put(sp[(zs - 1) & 1], 1);
-    }
-    load_m(zs);
-    if (rec) {
-        recon();
-        put(sp[zs & 1], 1);
-        put(s0, 0);
-    }
-    load_m(zs + 1);
-    for (int z = zs; z < ze; ++z) {
-        // plane z + 1 from the prefetched numbers; then prefetch plane z + 2
-        if (rec) recon();
-        if (z + 2 <= ze) load_m(z + 2);
-        if (rec) put(sm, -1);
-        __syncthreads();
-        if (inter) {
-            float f[27];
-#pragma unroll
-            for (int i = 0; i < 27; ++i) {
-                const int cx = vel_x(i), cy = vel_y(i), cz = vel_z(i);
-                const float* slot = cz > 0 ? sp[(z - 1) & 1] : (cz == 0 ? s0 : sm);
-                f[i] = slot[mom_lds<HY>((cy + 1) * 3 + cx + 1, wave - cy, lane + 1 - cx)];
+    if (wave < 3 || wave - 3 >= nyi) {  // halo rows, edge columns, rows beyond a partial tile
+        const bool busy = wave < (whole_row ? 2 : 3);
+        if (busy) first_plane();
+        for (int p = zs - 1; p <= ze; ++p) {
+            if (busy) {
+                exchange(p);
+            } else {
+                if (NBUF == 1) __syncthreads();
+                __syncthreads();
             }
-            float F[3];
-            if (FIELD)
-                field_at(z, int_foff, F);
-            else
-                mom_force<false>(g, 0, b, iy, ftab, field, F);
-            float drho, ux, uy, uz, k[5];
-            pre_collision<float>(f, F[0], F[1], F[2], rho0, drho, ux, uy, uz, k);
-            mom_store_plane(dst + row_of(z, 0), g.pstride, plane_bytes, int_off, drho, ux, uy, uz, k, om1);
         }
-        __syncthreads();
-        if (rec) {
-            put(sp[(z + 1) & 1], 1);
-            put(s0, 0);
+        return;
+    }
+
+    // carried across planes (no register is copied from one plane to the next
+    // but the force and the mask: each is consumed before it is overwritten)
+    T Ps[6], Zs[6];      // sums of c_z = +1, 0 for the target plane p - 1
+    T Pr[RAW ? 9 : 6];   // c_z = +1 pulled from plane p - 1: values, or their sums
+    T own[MASK ? 9 : 1]; // MASK: own c_z = +1 values of plane p - 1
+    uint32_t mz = 0;     // MASK: link mask of plane p - 1
+#pragma unroll
+    for (int j = 0; j < 6; ++j) Ps[j] = Zs[j] = T(0);
+#pragma unroll
+    for (int j = 0; j < (RAW ? 9 : 6); ++j) Pr[j] = T(0);
+#pragma unroll
+    for (int j = 0; j < (MASK ? 9 : 1); ++j) own[j] = T(0);
+    if (FIELD) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) Fz[a] = T(0);
+    }
+
+    first_plane();
+    for (int p = zs - 1; p <= ze; ++p) {
+        const uint32_t mc = mk;
+        exchange(p);
+        // what streamed to this cell, by class (j = (c_y + 1) * 3 + c_x + 1)
+        auto pulled = [&](int cz, int j) -> T {
+            const int i = vel_index(j % 3 - 1, j / 3 - 1, cz);
+            return j == 4 ? h[i] : slots[xslot(i) * SLOT + get];
+        };
+        auto mine = [&](int cz, int j) -> T { return h[vel_index(j % 3 - 1, j / 3 - 1, cz)]; };
+        auto bounced = [&](uint32_t m, int cz, int j) -> bool { return (m >> vel_index(j % 3 - 1, j / 3 - 1, cz)) & 1u; };
+        T v[9], Ms[6], drho, ux, uy, uz, k[5];
+        // finish target p - 1 (nothing is stored while p <= zs)
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            v[j] = pulled(-1, j);
+            if (MASK) v[j] = bounced(mz, -1, j) ? own[8 - j] : v[j];
         }
+        lockstep::plane_sums<T>(v, Ms);
+        lockstep::moments_of_sums<T>(Ms, Zs, Ps, Fz[0], Fz[1], Fz[2], rho0, drho, ux, uy, uz, k);
+        const T s[9] = {drho, ux, uy, uz, om1 * k[0], om1 * k[1], om1 * k[2], om1 * k[3], om1 * k[4]};
+        const bool store = p > zs && !(MASK && (mz & kSolidBit));
+        const int zt = p > zs ? p - 1 : zs;
+        if constexpr (!POUT) {
+            T* d0 = dst + row_of(zt) * mrow;
+            const uint32_t off = store ? moff : kNone;
+#pragma unroll
+            for (int j = 0; j < 9; ++j) st_buf<true>((gchar*)(d0 + j * mstride), mbytes, off, s[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            v[j] = pulled(0, j);
+            if (MASK) v[j] = bounced(mc, 0, j) ? mine(0, 8 - j) : v[j];
+        }
+        lockstep::plane_sums<T>(v, Zs);
+        if constexpr (RAW) {
+            // target p: pulled from plane p - 1 in the last iteration, bounced from own plane p
+#pragma unroll
+            for (int j = 0; j < 9; ++j) v[j] = MASK && bounced(mc, 1, j) ? mine(-1, 8 - j) : Pr[j];
+            lockstep::plane_sums<T>(v, Ps);
+#pragma unroll
+            for (int j = 0; j < 9; ++j) {
+                Pr[j] = pulled(1, j);
+                if (MASK) own[j] = mine(1, j);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 6; ++j) Ps[j] = Pr[j];
+#pragma unroll
+            for (int j = 0; j < 9; ++j) v[j] = pulled(1, j);
+            lockstep::plane_sums<T>(v, Pr);
+        }
+        if constexpr (POUT) {  // after the last use of plane p's own populations, whose registers it takes
+            lockstep::reconstruct<T>(drho, ux, uy, uz, Fz[0], Fz[1], Fz[2], s + 4, rho0, h);
+            T* d0 = dst + row_of(zt) * g.rstride;
+            const uint32_t off = store ? poff : kNone;
+#pragma unroll
+            for (int i = 0; i < 27; ++i) st_buf<true>((gchar*)(d0 + i * g.pstride), pbytes, off, h[i]);
+        }
+        if (FIELD) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) Fz[a] = F[a];
+        }
+        mz = mc;
     }
 }
-
-// interior tile rows of the moment kernel: 12 when the lattice is tall enough
-// (halo overhead 14/12 in y, one workgroup of 15 waves per CU), else 6
-int mom_rows(const Geom& g) { return g.ny >= 24 ? 12 : 6; }
 
 // First collision of a moment-representation state: f(x, 0) = f^eq(rho, u)
 // at every cell, collided in place (cell-local), the nine numbers stored.
@@ -1023,13 +1155,13 @@ __global__ __launch_bounds__(kBlock) void k_init_mom(float* __restrict__ dst, Ge
     float e[27];
     feq_dev<float>(drho0, u, rho0, e);
     float F[3];
-    if (field)
-        mom_force<true>(g, c.lin, c.b, c.y, ftab, field, F);
-    else
-        mom_force<false>(g, c.lin, c.b, c.y, ftab, field, F);
+    for (int a = 0; a < 3; ++a) F[a] = field ? field[a * g.ncell + c.lin] : ftab[3 * (c.b * g.ny + c.y) + a];
     float drho, ux, uy, uz, k[5];
-    pre_collision<float>(e, F[0], F[1], F[2], rho0, drho, ux, uy, uz, k);
-    mom_store(dst, g.pstride, c.pown, drho, ux, uy, uz, k, 1.f - omega);
+    lockstep::pre_collision<float>(e, F[0], F[1], F[2], rho0, drho, ux, uy, uz, k);
+    const float om1 = 1.f - omega;
+    const float v[9] = {drho, ux, uy, uz, om1 * k[0], om1 * k[1], om1 * k[2], om1 * k[3], om1 * k[4]};
+#pragma unroll
+    for (int j = 0; j < 9; ++j) __builtin_nontemporal_store(v[j], dst + j * g.pstride + c.pown);
 }
 
 // ---------------------------------------------------------------------------
@@ -1860,11 +1992,43 @@ int launch_step_red(cmlbm_lattice* lat, hipStream_t s)
     }
 }
 
-template <int TY>
-void launch_step_mom_t(cmlbm_lattice* lat, hipStream_t s)
+// Interior rows of k_march's tiles: FP32 12 (15 waves), or 6 on lattices of
+// fewer than 24 rows; FP64 8, the most whose 11 waves (three on a SIMD) leave
+// a lane the 168 registers it takes.
+int march_rows(bool f64, int ny) { return f64 ? 8 : ny >= 24 ? 12 : 6; }
+
+// Planes per workgroup of k_march: the fewest rounds of workgroups over the
+// CUs, each costing its planes, two halo planes and a start.
+uint64_t march_cols(const Geom& g, int TY)
+{
+    return (uint64_t)((g.nx + kMomTX - 1) / kMomTX) * (uint64_t)((g.ny + TY - 1) / TY) * g.nb;
+}
+
+int march_chunk(const Geom& g, int TY, int cus)
+{
+    const uint64_t cols = march_cols(g, TY);
+    const uint64_t cap = cus > 0 ? (uint64_t)cus : 256;
+    int best = g.nz;
+    uint64_t best_cost = ~0ULL;
+    for (int n = 1; n <= g.nz; ++n) {
+        const int zc = (g.nz + n - 1) / n;
+        if ((g.nz + zc - 1) / zc != n) continue;
+        if (cols * n * (uint64_t)(TY + 3) * 64 > 0xffffffffULL) break;  // work-items of a launch
+        const uint64_t cost = ((cols * n + cap - 1) / cap) * (uint64_t)(zc + 3);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = zc;
+        }
+    }
+    return best;
+}
+
+template <typename T, int TY, bool FIELD, bool MASK>
+void launch_march_t(cmlbm_lattice* lat, hipStream_t s, bool pout)
 {
     const Geom& g = lat->g;
-    const int nzc = (g.nz + kMomZC - 1) / kMomZC;
+    const int zc = march_chunk(g, TY, lat->cus);
+    const int nzc = (g.nz + zc - 1) / zc;
     const int ntx = (g.nx + kMomTX - 1) / kMomTX, nty = (g.ny + TY - 1) / TY;
     dim3 grid((unsigned)(ntx * nty * g.nb * nzc));
     // the blocked schedule when an XCD's generation covers whole tile rows,
@@ -1884,30 +2048,126 @@ void launch_step_mom_t(cmlbm_lattice* lat, hipStream_t s)
             grid = dim3((unsigned)(round * gens));
         }
     }
-    const float* ftab = (const float*)(lat->scratch + lat->off_ftab32);
-    const float* src = (const float*)lat->pop[lat->cur];
-    float* dst = (float*)lat->pop[1 - lat->cur];
-    const float om = (float)(1.0 / lat->p.tau), r0 = (float)lat->p.rho0;
+    const T* ftab = (const T*)(lat->scratch + (sizeof(T) == 8 ? lat->off_ftab64 : lat->off_ftab32));
+    const T* src = (const T*)lat->pop[lat->cur];
+    T* dst = (T*)lat->pop[1 - lat->cur];
+    const T om = (T)(1.0 / lat->p.tau), r0 = (T)lat->p.rho0;
     const dim3 block((TY + 3) * 64);
-    if (lat->force_mode == CMLBM_FORCE_FIELD)
-        k_step_mom<true, TY><<<grid, block, 0, s>>>(src, dst, g, om, r0, ftab, (const float*)lat->field, gens, cpx);
+    const T* field = FIELD ? (const T*)lat->field : nullptr;
+    // elements from one of the nine numbers to the next of one row, and from one row to the
+    // next: the state itself in moment storage, else row blocks in the population buffers
+    const bool state = lat->p.storage == CMLBM_MOM32;
+    const uint64_t mstride = state ? g.pstride : (uint64_t)g.nxp, mrow = state ? g.rstride : 9ull * g.nxp;
+    if (pout)
+        k_march<T, TY, FIELD, MASK, true><<<grid, block, 0, s>>>(src, dst, g, mstride, mrow, zc, om, r0, ftab, field,
+                                                                     mask_ptr(lat), gens, cpx);
     else
-        k_step_mom<false, TY><<<grid, block, 0, s>>>(src, dst, g, om, r0, ftab, nullptr, gens, cpx);
+        k_march<T, TY, FIELD, MASK, false><<<grid, block, 0, s>>>(src, dst, g, mstride, mrow, zc, om, r0, ftab, field,
+                                                                     mask_ptr(lat), gens, cpx);
 }
 
-int launch_step_mom(cmlbm_lattice* lat, hipStream_t s)
+template <typename T, int TY>
+void launch_march_ty(cmlbm_lattice* lat, hipStream_t s, bool pout)
 {
-    if (mom_rows(lat->g) == 12)
-        launch_step_mom_t<12>(lat, s);
+    const bool F = lat->force_mode == CMLBM_FORCE_FIELD;
+    if (lat->needs_mask) {
+        if (F)
+            launch_march_t<T, TY, true, true>(lat, s, pout);
+        else
+            launch_march_t<T, TY, false, true>(lat, s, pout);
+    } else {
+        if (F)
+            launch_march_t<T, TY, true, false>(lat, s, pout);
+        else
+            launch_march_t<T, TY, false, false>(lat, s, pout);
+    }
+}
+
+// pout: populations come out (the last step of a call on population storage)
+template <typename T>
+int launch_march(cmlbm_lattice* lat, hipStream_t s, bool pout)
+{
+    if constexpr (sizeof(T) == 8)
+        launch_march_ty<T, 8>(lat, s, pout);
+    else if (march_rows(false, lat->g.ny) == 12)
+        launch_march_ty<T, 12>(lat, s, pout);
     else
-        launch_step_mom_t<6>(lat, s);
+        launch_march_ty<T, 6>(lat, s, pout);
     return launch_check(lat, "step");
+}
+
+// The first step of a call that marches: populations in, the nine numbers out.
+template <int ST, bool MASK, bool FIELD>
+void launch_to_moments_t(cmlbm_lattice* lat, hipStream_t s)
+{
+    using T = typename storage<ST>::T;
+    const Geom& g = lat->g;
+    const int segs = (g.nx + 63) / 64;
+    const uint64_t waves = (uint64_t)g.rows * (uint64_t)segs;
+    constexpr int wpb = step_block(ST, MASK) / 64;
+    const dim3 grid((unsigned)((waves + wpb - 1) / wpb));
+    const T* ftab = (const T*)(lat->scratch + (ST == CMLBM_FP64 ? lat->off_ftab64 : lat->off_ftab32));
+    k_step<ST, 1, MASK, FIELD, true, 0, false, false, true><<<grid, dim3(step_block(ST, MASK)), 0, s>>>(
+        (const T*)lat->pop[lat->cur], (T*)lat->pop[1 - lat->cur], g, segs, (T)(1.0 / lat->p.tau), (T)lat->p.rho0, ftab,
+        (const T*)lat->field, mask_ptr(lat), (uint32_t)lat->t, nullptr);
+}
+
+template <int ST>
+int launch_to_moments_st(cmlbm_lattice* lat, hipStream_t s)
+{
+    const bool F = lat->force_mode == CMLBM_FORCE_FIELD;
+    if (lat->needs_mask) {
+        if (F)
+            launch_to_moments_t<ST, true, true>(lat, s);
+        else
+            launch_to_moments_t<ST, true, false>(lat, s);
+    } else {
+        if (F)
+            launch_to_moments_t<ST, false, true>(lat, s);
+        else
+            launch_to_moments_t<ST, false, false>(lat, s);
+    }
+    return launch_check(lat, "step");
+}
+
+int launch_to_moments(cmlbm_lattice* lat, hipStream_t s)
+{
+    return lat->p.storage == CMLBM_FP64 ? launch_to_moments_st<CMLBM_FP64>(lat, s)
+                                        : launch_to_moments_st<CMLBM_FP32>(lat, s);
+}
+
+// Whether a call of n steps goes through the nine numbers: where its first,
+// inner and last steps are estimated to take less than n steps of k_step.
+// k_step moves 54 numbers per cell at about 5.4 TB/s, a lane without a cell
+// costs it as much as one with FP32 numbers, and it takes 6.5 us at the least;
+// an inner step takes the rounds of its workgroups, each zc + 3 planes
+// of 2.6 us (FP32), 3.3 us (FP64) or 3.6 us (FP64 with a link mask); the first
+// and the last step move 36 numbers.  Measured, k_step against an inner step:
+// FP32 32^3 7.4 / 9.7 us, 64^3 13.2 / 11.9, 96^3 37.3 / 23.0, 128^3 81.6 /
+// 46.4, 256^3 649 / 297, 512^3 5250 / 2240; FP64 32^3 7.2 / 11.8, 64^3 22.6 /
+// 15.6, 128^3 162 / 75, 256^3 1320 / 510; FP64 with walls 32 x 16 x 16 5.7 /
+// 12.7, 64^3 21.7 / 17.6, 64 members of 64 x 32 x 32 322 / 140.
+bool marches(const cmlbm_lattice* lat, int n)
+{
+    const Geom& g = lat->g;
+    const bool f64 = lat->p.storage == CMLBM_FP64;
+    if (n < 2 || (!f64 && lat->p.storage != CMLBM_FP32) || lat_model(lat)) return false;
+    const uint64_t elem = f64 ? 8 : 4;
+    // k_march's offsets within a plane are 32-bit, below its offset of no cell
+    if ((uint64_t)g.ny * g.rstride * elem >= 0xffffff00ULL) return false;
+    const int TY = march_rows(f64, g.ny), zc = march_chunk(g, TY, lat->cus);
+    const uint64_t wgs = march_cols(g, TY) * (uint64_t)((g.nz + zc - 1) / zc), cap = lat->cus > 0 ? lat->cus : 256;
+    if (wgs * (uint64_t)(TY + 3) * 64 > 0xffffffffULL) return false;  // work-items of a launch
+    const double lanes = (double)g.rows * ((g.nx + 63) / 64 * 64);
+    const double step = std::max({6.5, 54.0 * elem * (double)g.ncell / 5.4e6, 54.0 * 4 * lanes / 5.4e6});
+    const double inner = (double)((wgs + cap - 1) / cap) * (zc + 3) * (!f64 ? 2.6 : lat->needs_mask ? 3.6 : 3.3);
+    return n * step > 0.75 * step + (n - 2) * inner + std::max(1.25 * inner, 0.75 * step);
 }
 
 int launch_step(cmlbm_lattice* lat, hipStream_t s)
 {
     switch (lat->p.storage) {
-        case CMLBM_MOM32: return launch_step_mom(lat, s);
+        case CMLBM_MOM32: return launch_march<float>(lat, s, false);
         case CMLBM_FP64: return launch_step_st<CMLBM_FP64>(lat, s);
         case CMLBM_FP32: return launch_step_st<CMLBM_FP32>(lat, s);
         case CMLBM_FP16: return launch_step_st<CMLBM_FP16>(lat, s);
@@ -2235,8 +2495,12 @@ int cmlbm_step(cmlbm_lattice* lat, int32_t nsteps, void* hip_stream)
     if (!lat || nsteps < 0) return CMLBM_EINVAL;
     if (!lat->initialized) return fail(lat, CMLBM_ESTATE, "step before init");
     hipStream_t s = (hipStream_t)hip_stream;
+    const bool march = marches(lat, nsteps);
     for (int32_t k = 0; k < nsteps; ++k) {
-        int rc = launch_step(lat, s);
+        int rc = !march             ? launch_step(lat, s)
+                 : k == 0           ? launch_to_moments(lat, s)
+                 : lat->p.storage == CMLBM_FP64 ? launch_march<double>(lat, s, k == nsteps - 1)
+                                                : launch_march<float>(lat, s, k == nsteps - 1);
         if (rc) return rc;
         lat->cur = 1 - lat->cur;
         lat->t += 1;
