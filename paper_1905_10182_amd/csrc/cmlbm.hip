@@ -401,9 +401,9 @@ __device__ __forceinline__ void st_off(gchar* base, uint32_t byte_off, X v)
     }
 }
 
-// Threads per k_step workgroup: 1024 for FP32 storage, 512 for FP64 without a
-// bounce-back mask, 256 otherwise (measured best for each; the grid is rows x
-// segments of waves either way).
+// Most threads of a k_step workgroup: 1024 for FP32 storage, 512 for FP64
+// without a bounce-back mask, 256 otherwise (measured best for each on large
+// lattices; step_waves gives small ones 256).
 constexpr int step_block(int st, bool mask)
 {
     return st == CMLBM_FP32 ? 1024 : (st == CMLBM_FP64 && !mask) ? 512 : 256;
@@ -438,7 +438,7 @@ __device__ __forceinline__ double wave_max(double v)
 // numbers that determine the post-collision populations (k_march).
 template <int ST, int V, bool MASK, bool FIELD, bool NT, int MODEL, bool RED, bool SR, bool MOUT = false>
 __global__ __launch_bounds__(step_block(ST, MASK)) void k_step(const typename storage<ST>::S* __restrict__ src,
-                                                  typename storage<ST>::S* __restrict__ dst, Geom g, int segs,
+                                                  typename storage<ST>::S* __restrict__ dst, Geom g, int segs, int wpb,
                                                   typename storage<ST>::T omega, typename storage<ST>::T rho0,
                                                   const typename storage<ST>::T* __restrict__ ftab,
                                                   const typename storage<ST>::T* __restrict__ field,
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(step_block(ST, MASK)) void k_step(const typename st
     const T rho0s = rho0 * kS;
     typedef S vt __attribute__((ext_vector_type(V == 1 ? 2 : V)));
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (step_block(ST, MASK) / 64) + (threadIdx.x >> 6)));
+    const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * wpb + (threadIdx.x >> 6)));
     const int row = wave / segs;
     if (row >= g.rows) return;  // whole wave
     const int seg = wave - row * segs;
@@ -1823,6 +1823,18 @@ int lat_model(const cmlbm_lattice* lat)
            ((lat->p.flags & CMLBM_FLAG_BGK) ? kModelBgk : 0);
 }
 
+// Waves per k_step workgroup: step_block's, or four where the lattice would
+// give those fewer than two per CU: a large workgroup starts and ends as
+// one, and most CUs have none.  us a step, before and after: FP32 32 x 16 x 16
+// 8.0 / 5.4, 32^3 7.4 / 4.8, 48^3 9.5 / 8.6, 64^3 13.2 / 12.3; FP64 48^3 15.1 /
+// 12.9, 64^3 22.5 / 22.5.
+template <int ST, bool MASK>
+int step_waves(uint64_t waves)
+{
+    constexpr int most = step_block(ST, MASK) / 64;
+    return waves < 512ull * most ? 4 : most;
+}
+
 template <int ST, int V, bool MASK, bool FIELD, int MODEL = 0>
 void launch_step_v(cmlbm_lattice* lat, hipStream_t s)
 {
@@ -1831,12 +1843,12 @@ void launch_step_v(cmlbm_lattice* lat, hipStream_t s)
     const Geom& g = lat->g;
     const int segs = (g.nx + 64 * V - 1) / (64 * V);
     const uint64_t waves = (uint64_t)g.rows * (uint64_t)segs;
-    constexpr int wpb = step_block(ST, MASK) / 64;
+    const int wpb = step_waves<ST, MASK>(waves);
     const dim3 grid((unsigned)((waves + wpb - 1) / wpb));
     const T* ftab = (const T*)(lat->scratch + (ST == CMLBM_FP64 ? lat->off_ftab64 : lat->off_ftab32));
     auto go = [&](auto sr) {
-        k_step<ST, V, MASK, FIELD, true, MODEL, false, decltype(sr)::value><<<grid, dim3(step_block(ST, MASK)), 0, s>>>(
-            (const typename SS::S*)lat->pop[lat->cur], (typename SS::S*)lat->pop[1 - lat->cur], g, segs,
+        k_step<ST, V, MASK, FIELD, true, MODEL, false, decltype(sr)::value><<<grid, dim3(64 * wpb), 0, s>>>(
+            (const typename SS::S*)lat->pop[lat->cur], (typename SS::S*)lat->pop[1 - lat->cur], g, segs, wpb,
             (T)(1.0 / lat->p.tau), (T)lat->p.rho0, ftab, (const T*)lat->field, mask_ptr(lat), (uint32_t)lat->t,
             nullptr);
     };
@@ -1924,12 +1936,12 @@ void launch_step_red_v(cmlbm_lattice* lat, hipStream_t s)
     const Geom& g = lat->g;
     const int segs = (g.nx + 64 * V - 1) / (64 * V);
     const uint64_t waves = (uint64_t)g.rows * (uint64_t)segs;
-    constexpr int wpb = step_block(ST, MASK) / 64;
+    const int wpb = step_waves<ST, MASK>(waves);
     const dim3 grid((unsigned)((waves + wpb - 1) / wpb));
     const T* ftab = (const T*)(lat->scratch + (ST == CMLBM_FP64 ? lat->off_ftab64 : lat->off_ftab32));
     auto go = [&](auto sr) {
-        k_step<ST, V, MASK, FIELD, true, 0, true, decltype(sr)::value><<<grid, dim3(step_block(ST, MASK)), 0, s>>>(
-            (const typename SS::S*)lat->pop[lat->cur], (typename SS::S*)lat->pop[1 - lat->cur], g, segs,
+        k_step<ST, V, MASK, FIELD, true, 0, true, decltype(sr)::value><<<grid, dim3(64 * wpb), 0, s>>>(
+            (const typename SS::S*)lat->pop[lat->cur], (typename SS::S*)lat->pop[1 - lat->cur], g, segs, wpb,
             (T)(1.0 / lat->p.tau), (T)lat->p.rho0, ftab, (const T*)lat->field, mask_ptr(lat), (uint32_t)lat->t,
             (double*)(lat->scratch + lat->off_wpart));
     };
@@ -2104,11 +2116,11 @@ void launch_to_moments_t(cmlbm_lattice* lat, hipStream_t s)
     const Geom& g = lat->g;
     const int segs = (g.nx + 63) / 64;
     const uint64_t waves = (uint64_t)g.rows * (uint64_t)segs;
-    constexpr int wpb = step_block(ST, MASK) / 64;
+    const int wpb = step_waves<ST, MASK>(waves);
     const dim3 grid((unsigned)((waves + wpb - 1) / wpb));
     const T* ftab = (const T*)(lat->scratch + (ST == CMLBM_FP64 ? lat->off_ftab64 : lat->off_ftab32));
-    k_step<ST, 1, MASK, FIELD, true, 0, false, false, true><<<grid, dim3(step_block(ST, MASK)), 0, s>>>(
-        (const T*)lat->pop[lat->cur], (T*)lat->pop[1 - lat->cur], g, segs, (T)(1.0 / lat->p.tau), (T)lat->p.rho0, ftab,
+    k_step<ST, 1, MASK, FIELD, true, 0, false, false, true><<<grid, dim3(64 * wpb), 0, s>>>(
+        (const T*)lat->pop[lat->cur], (T*)lat->pop[1 - lat->cur], g, segs, wpb, (T)(1.0 / lat->p.tau), (T)lat->p.rho0, ftab,
         (const T*)lat->field, mask_ptr(lat), (uint32_t)lat->t, nullptr);
 }
 
