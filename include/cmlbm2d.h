@@ -102,8 +102,11 @@ int cmlbm2d_set_force(cmlbm2d_lattice* lat, int mode, const double* host_values,
  * io_dtype CMLBM2D_FP64 or CMLBM2D_FP32.  Resets the step counter to 0. */
 int cmlbm2d_init(cmlbm2d_lattice* lat, const void* dev_rho, const void* dev_u, int io_dtype, void* hip_stream);
 
-/* Advance nsteps >= 0 time steps, one fused launch each: pull streaming,
- * central-moment collision with forcing, store. */
+/* Advance nsteps >= 0 time steps: pull streaming, central-moment collision
+ * with forcing, store.  FP64 and FP32 storage may take several steps in one
+ * launch (chosen by size); the populations after n steps are the same bits
+ * however n is split into calls.  The buffer that does not hold the state is
+ * scratch. */
 int cmlbm2d_step(cmlbm2d_lattice* lat, int32_t nsteps, void* hip_stream);
 
 /* rho(x, t) into dev_rho[N] and u = (sum f c + F/2)/rho into dev_u[2][N]

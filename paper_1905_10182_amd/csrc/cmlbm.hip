@@ -1647,6 +1647,7 @@ struct cmlbm_lattice {
     int cu_per_xcd;  // compute units per XCD of the lattice's device (the moment kernel's generation size)
     int cus;         // compute units of the lattice's device (0 if unknown)
     int psi_zc;      // z chunk of the pseudo-potential tiles (0 until the first launch)
+    int march_zc;    // z chunk of k_march (0 until the first call that could use it)
     std::string err;
 };
 
@@ -2035,11 +2036,17 @@ int march_chunk(const Geom& g, int TY, int cus)
     return best;
 }
 
+int march_zc(cmlbm_lattice* lat, int TY)
+{
+    if (!lat->march_zc) lat->march_zc = march_chunk(lat->g, TY, lat->cus);
+    return lat->march_zc;
+}
+
 template <typename T, int TY, bool FIELD, bool MASK>
 void launch_march_t(cmlbm_lattice* lat, hipStream_t s, bool pout)
 {
     const Geom& g = lat->g;
-    const int zc = march_chunk(g, TY, lat->cus);
+    const int zc = march_zc(lat, TY);
     const int nzc = (g.nz + zc - 1) / zc;
     const int ntx = (g.nx + kMomTX - 1) / kMomTX, nty = (g.ny + TY - 1) / TY;
     dim3 grid((unsigned)(ntx * nty * g.nb * nzc));
@@ -2159,7 +2166,7 @@ int launch_to_moments(cmlbm_lattice* lat, hipStream_t s)
 // 46.4, 256^3 649 / 297, 512^3 5250 / 2240; FP64 32^3 7.2 / 11.8, 64^3 22.6 /
 // 15.6, 128^3 162 / 75, 256^3 1320 / 510; FP64 with walls 32 x 16 x 16 5.7 /
 // 12.7, 64^3 21.7 / 17.6, 64 members of 64 x 32 x 32 322 / 140.
-bool marches(const cmlbm_lattice* lat, int n)
+bool marches(cmlbm_lattice* lat, int n)
 {
     const Geom& g = lat->g;
     const bool f64 = lat->p.storage == CMLBM_FP64;
@@ -2167,7 +2174,7 @@ bool marches(const cmlbm_lattice* lat, int n)
     const uint64_t elem = f64 ? 8 : 4;
     // k_march's offsets within a plane are 32-bit, below its offset of no cell
     if ((uint64_t)g.ny * g.rstride * elem >= 0xffffff00ULL) return false;
-    const int TY = march_rows(f64, g.ny), zc = march_chunk(g, TY, lat->cus);
+    const int TY = march_rows(f64, g.ny), zc = march_zc(lat, TY);
     const uint64_t wgs = march_cols(g, TY) * (uint64_t)((g.nz + zc - 1) / zc), cap = lat->cus > 0 ? lat->cus : 256;
     if (wgs * (uint64_t)(TY + 3) * 64 > 0xffffffffULL) return false;  // work-items of a launch
     const double lanes = (double)g.rows * ((g.nx + 63) / 64 * 64);
@@ -2386,6 +2393,7 @@ int cmlbm_create(const cmlbm_params* params, void* pop_a, size_t pop_a_bytes, vo
         lat->cus = cus;
     }
     lat->psi_zc = 0;  // chosen at the first pseudo-potential launch
+    lat->march_zc = 0;
     lat->field = nullptr;
     lat->field_dtype = CMLBM_FP64;
     lat->t = 0;

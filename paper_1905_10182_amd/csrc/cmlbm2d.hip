@@ -11,11 +11,17 @@
 // holds the population that the next pull gather moves to y + c_i, so
 // f_i(x, t) = A_i(x - c_i): a step is gather (streaming), collision and a
 // store at the cell's own index.
+//
+// Kernels: k2_step one step; k2_march and k2_tile several steps of FP64 and
+// FP32 storage in one launch (large and small planes); k2_init, k2_gather the
+// state's import and export.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <new>
 #include <string>
+#include <type_traits>
 
 #include "cmlbm2d.h"
 #include "d2q9.hpp"
@@ -227,7 +233,10 @@ __global__ __launch_bounds__(kBlock) void k2_step(const typename storage2<ST>::S
 #pragma unroll
     for (int c = 0; c < V; ++c) {
         T drho, ux, uy;
-        collide<T>(h[c], Fx[c], Fy[c], omega, rho0, drho, ux, uy);
+        if constexpr (sizeof(S) == 2)
+            joined::collide<T>(h[c], Fx[c], Fy[c], omega, rho0, drho, ux, uy);
+        else
+            lockstep::collide<T>(h[c], Fx[c], Fy[c], omega, rho0, drho, ux, uy);
     }
     const uint32_t own = (uint32_t)x0 * (uint32_t)sizeof(S);
     const uint64_t orow = (uint64_t)row * g.rstride;
@@ -243,6 +252,248 @@ __global__ __launch_bounds__(kBlock) void k2_step(const typename storage2<ST>::S
             store_nt<vt>(plane_row, own, o);
         }
     }
+}
+
+// ---------------------------------------------------------------------------
+// several steps in one pass
+//
+// K steps of a strip of 64 V cells, one wave, marching up y.  At source row r
+// of the state, stage 1 pulls from the stored populations and finishes row
+// r - 1 of the next time; stage k takes the numbers that stage k - 1 finished
+// (rho - rho0, u, s4, s5: with the force they determine the post-collision
+// populations), reconstructs that row and finishes row r - k, k steps on; the
+// last stage's row is reconstructed and stored.  The x shift is a DPP rotation
+// of the wave; the y shift stays in a lane's registers: of a row, class
+// c_y = -1 goes to the row below, 0 to the row itself, +1 to the row above, as
+// three row sums each.  No LDS and no barrier: waves are independent.
+// (Per step at 8192^2 with a force field: FP32 890 -> 327 us, 205 G cells/s;
+// FP64 1873 -> 609 us, 110 G cells/s.)
+// A strip loses one cell at each end per stage, so strips overlap by 2 K cells
+// (none where a strip is exactly a periodic row), and a chunk of rows starts
+// and ends K rows outside.  What bounds it is the issue of vector
+// instructions: 72 bytes per cell (FP32) for K steps instead of for each.
+template <typename X>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const X* base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)bytes, 0x00020000);
+}
+
+template <int ST, int V, int K, bool FIELD>
+__global__ __launch_bounds__(kBlock) void k2_march(const typename storage2<ST>::S* __restrict__ src,
+                                                   typename storage2<ST>::S* __restrict__ dst, Geom2 g, int strips,
+                                                   int rows, typename storage2<ST>::T omega,
+                                                   typename storage2<ST>::T rho0, typename storage2<ST>::T fx,
+                                                   typename storage2<ST>::T fy,
+                                                   const typename storage2<ST>::T* __restrict__ field)
+{
+    using T = typename storage2<ST>::T;
+    static_assert(std::is_same<T, typename storage2<ST>::S>::value, "FP64 and FP32 storage");
+    static_assert(K % V == 0 && V * sizeof(T) <= 8, "a lane's cells are one vector of 4 or 8 bytes");
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)));
+    const int chunk = wave / strips, strip = wave - chunk * strips;
+    const int ys = chunk * rows, ye = ys + rows < g.ny ? ys + rows : g.ny;
+    if (ys >= g.ny) return;  // whole wave
+    // cells of this lane: position i0 in the strip, x (periodic); stored are the
+    // positions [K, 64 V - K) of an overlapping strip that lie in the row
+    const bool ring = g.nx == 64 * V;
+    const int stride = ring ? 64 * V : 64 * V - 2 * K, i0 = lane * V;
+    const int xr = strip * stride + i0 - (ring ? 0 : K);
+    const int x = ((xr % g.nx) + g.nx) % g.nx;
+    const bool stored = ring || (i0 >= K && i0 < 64 * V - K && xr < g.nx);
+    constexpr uint32_t kNone = 0xffffff00u;  // past every range: the store is dropped
+    const uint32_t rowb = (uint32_t)g.nxp * (uint32_t)sizeof(T), off = (uint32_t)x * (uint32_t)sizeof(T);
+    const uint32_t fieldb = (uint32_t)g.nx * (uint32_t)sizeof(T);
+    auto ld = [&](const T* row, uint32_t bytes, T v[V]) {
+        if constexpr (V * sizeof(T) == 4) {
+            v[0] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(rsrc_of(row, bytes), off, 0, 0));
+            return;
+        }
+        const u2 w = __builtin_amdgcn_raw_buffer_load_b64(rsrc_of(row, bytes), off, 0, 0);
+        if constexpr (sizeof(T) == 8) {
+            v[0] = __builtin_bit_cast(T, w);
+        } else {
+            const uint32_t w0 = w.x, w1 = w.y;
+            v[0] = __builtin_bit_cast(T, w0);
+            v[V - 1] = __builtin_bit_cast(T, w1);
+        }
+    };
+
+    T nh[9][V];  // populations of the next source row
+    auto load_row = [&](int r) {
+        const T* p = src + (uint64_t)r * g.rstride;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) ld(p + (uint64_t)i * g.pstride, rowb, nh[i]);
+    };
+    T Z[K][V][3], P[K][2][V][3];  // row sums of c_y = 0 (last row) and +1 (last two rows) of each stage
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int c = 0; c < V; ++c)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) Z[k][c][j] = P[k][0][c][j] = P[k][1][c][j] = T(0);
+    const T om1 = T(1) - omega;
+
+    int y[K + 1];  // row of stage k's target, periodic (y[0]: the source row)
+    y[0] = (((ys - K) % g.ny) + g.ny) % g.ny;
+#pragma unroll
+    for (int k = 1; k <= K; ++k) y[k] = y[k - 1] == 0 ? g.ny - 1 : y[k - 1] - 1;
+    load_row(y[0]);
+#pragma unroll
+    for (int i = 0; i < 9; ++i)
+#pragma unroll
+        for (int c = 0; c < V; ++c) asm volatile("" : "+v"(nh[i][c]));  // arrived: not counted in the loop
+    auto advance = [&](int r, auto parity) {
+        constexpr int q = decltype(parity)::value;
+        T h[V][9], Fx[V], Fy[V], F[K][2][V];
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+#pragma unroll
+            for (int c = 0; c < V; ++c) h[c][i] = nh[i][c];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (FIELD) {
+                ld(field + (uint64_t)y[k + 1] * g.nx, fieldb, F[k][0]);
+                ld(field + g.ncell + (uint64_t)y[k + 1] * g.nx, fieldb, F[k][1]);
+            } else {
+#pragma unroll
+                for (int c = 0; c < V; ++c) {
+                    F[k][0][c] = fx;
+                    F[k][1][c] = fy;
+                }
+            }
+        }
+        load_row(y[0] + 1 == g.ny ? 0 : y[0] + 1);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            T X[V][3][3];  // row sums of this row, by c_y class
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const int ip = vel_index(1, b - 1), i0 = vel_index(0, b - 1), im = vel_index(-1, b - 1);
+                const T from_prev = shift_lane<T>(h[V - 1][ip], true), from_next = shift_lane<T>(h[0][im], false);
+#pragma unroll
+                for (int c = 0; c < V; ++c)
+                    lockstep::row_sums<T>(c < V - 1 ? h[c + 1][im] : from_next, h[c][i0],
+                                          c > 0 ? h[c - 1][ip] : from_prev, X[c][b]);
+            }
+#pragma unroll
+            for (int c = 0; c < V; ++c) {
+                Fx[c] = F[k][0][c];
+                Fy[c] = F[k][1][c];
+                T drho, ux, uy, k4, k5;
+                lockstep::moments_of_sums<T>(X[c][0], Z[k][c], P[k][q][c], Fx[c], Fy[c], rho0, drho, ux, uy, k4, k5);
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {
+                    Z[k][c][j] = X[c][1][j];
+                    P[k][q][c][j] = X[c][2][j];
+                }
+                const T s4 = om1 * k4, s5 = om1 * k5;
+                lockstep::reconstruct<T>(drho, ux, uy, Fx[c], Fy[c], s4, s5, rho0, h[c]);
+            }
+        }
+        const int yt = r - K;  // the row just finished, K steps on
+        T* out = dst + (uint64_t)y[K] * g.rstride;
+        const uint32_t so = stored && yt >= ys ? off : kNone;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            if constexpr (V * sizeof(T) == 4) {
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, h[0][i]),
+                                                      rsrc_of(out + (uint64_t)i * g.pstride, rowb), so, 0, 2);
+                continue;
+            }
+            u2 w;
+            if constexpr (sizeof(T) == 8) {
+                w = __builtin_bit_cast(u2, h[0][i]);
+            } else {
+                w.x = __builtin_bit_cast(uint32_t, h[0][i]);
+                w.y = __builtin_bit_cast(uint32_t, h[V - 1][i]);
+            }
+            __builtin_amdgcn_raw_buffer_store_b64(w, rsrc_of(out + (uint64_t)i * g.pstride, rowb), so, 0, 2);
+        }
+#pragma unroll
+        for (int k = 0; k <= K; ++k) y[k] = y[k] + 1 == g.ny ? 0 : y[k] + 1;
+    };
+    int r = ys - K;
+    const int end = ye + K;  // one past the last source row
+    for (; r + 1 < end; r += 2) {
+        advance(r, std::integral_constant<int, 0>{});
+        advance(r + 1, std::integral_constant<int, 1>{});
+    }
+    if (r < end) advance(r, std::integral_constant<int, 0>{});
+}
+
+// K steps of a small lattice: a workgroup of kTileRows waves, one row of 64
+// cells each, advances its rows K steps in registers.  Per step a wave forms
+// the row sums of its populations, hands those of c_y = +1 and -1 to the rows
+// above and below through LDS (two buffers in turn, one barrier), and finishes
+// its own row.  A row at each end and a cell at each side are lost per step, so
+// kTileRows - 2 K rows by 64 - 2 K cells (64 where that is the periodic row)
+// are stored.  A launch and the loads cost as much as several of these steps,
+// which is what a step of k2_step pays on such a lattice.
+constexpr int kTileRows = 16;
+
+template <int ST, bool FIELD>
+__global__ __launch_bounds__(kTileRows * 64) void k2_tile(const typename storage2<ST>::S* __restrict__ src,
+                                                          typename storage2<ST>::S* __restrict__ dst, Geom2 g, int K,
+                                                          int strips, typename storage2<ST>::T omega,
+                                                          typename storage2<ST>::T rho0,
+                                                          typename storage2<ST>::T fx, typename storage2<ST>::T fy,
+                                                          const typename storage2<ST>::T* __restrict__ field)
+{
+    using T = typename storage2<ST>::T;
+    static_assert(std::is_same<T, typename storage2<ST>::S>::value, "FP64 and FP32 storage");
+    __shared__ T up[2][kTileRows][3][64], down[2][kTileRows][3][64];
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int tile = (int)blockIdx.x / strips, strip = (int)blockIdx.x - tile * strips;
+    const bool ring = g.nx == 64;
+    const int xr = strip * (ring ? 64 : 64 - 2 * K) + lane - (ring ? 0 : K);
+    const int x = ((xr % g.nx) + g.nx) % g.nx;
+    const int yr = tile * (kTileRows - 2 * K) + w - K;
+    const int y = ((yr % g.ny) + g.ny) % g.ny;
+    T h[9], Fx = fx, Fy = fy;
+    const T* row = src + (uint64_t)y * g.rstride + x;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) h[i] = row[(uint64_t)i * g.pstride];
+    if (FIELD) {
+        const uint64_t lin = (uint64_t)y * (uint64_t)g.nx + (uint64_t)x;
+        Fx = field[lin];
+        Fy = field[g.ncell + lin];
+    }
+    const T om1 = T(1) - omega;
+    for (int t = 0; t < K; ++t) {
+        const int q = t & 1;
+        T X[3][3];  // row sums by c_y class
+        if (w >= t && w < kTileRows - t) {
+#pragma unroll
+            for (int b = 0; b < 3; ++b)
+                lockstep::row_sums<T>(shift_lane<T>(h[vel_index(-1, b - 1)], false), h[vel_index(0, b - 1)],
+                                      shift_lane<T>(h[vel_index(1, b - 1)], true), X[b]);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                down[q][w][j][lane] = X[0][j];
+                up[q][w][j][lane] = X[2][j];
+            }
+        }
+        __syncthreads();
+        if (w > t && w < kTileRows - 1 - t) {
+            T Xm[3], Xp[3], drho, ux, uy, k4, k5;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                Xm[j] = down[q][w + 1][j][lane];
+                Xp[j] = up[q][w - 1][j][lane];
+            }
+            lockstep::moments_of_sums<T>(Xm, X[1], Xp, Fx, Fy, rho0, drho, ux, uy, k4, k5);
+            const T s4 = om1 * k4, s5 = om1 * k5;
+            lockstep::reconstruct<T>(drho, ux, uy, Fx, Fy, s4, s5, rho0, h);
+        }
+    }
+    if (w < K || w >= kTileRows - K || yr >= g.ny) return;
+    if (!ring && (lane < K || lane >= 64 - K || xr >= g.nx)) return;
+    T* out = dst + (uint64_t)y * g.rstride + x;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) out[(uint64_t)i * g.pstride] = h[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -287,7 +538,7 @@ __global__ __launch_bounds__(kBlock) void k2_init(typename storage2<ST>::S* __re
                 uy = (T)U[g.ncell + n];
             }
         }
-        reconstruct<T>(drho, ux, uy, T(0), T(0), T(0), T(0), (T)rho0, e);
+        joined::reconstruct<T>(drho, ux, uy, T(0), T(0), T(0), T(0), (T)rho0, e);
     }
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
@@ -442,6 +693,33 @@ int launch_check(cmlbm2d_lattice* lat, const char* what)
 
 dim3 cell_grid(const Geom2& g) { return dim3((unsigned)((g.ncell + kBlock - 1) / kBlock)); }
 
+int march_strips(const Geom2& g, int V, int K)
+{
+    return g.nx == 64 * V ? 1 : (g.nx + 64 * V - 2 * K - 1) / (64 * V - 2 * K);
+}
+
+// Rows per wave of k2_march, and the waves that a SIMD then runs: the least of
+// that number (a SIMD is bound by their instructions) times the rows of each
+// and the 2 K it starts and ends with.
+int march_rows2(const Geom2& g, int strips, int K, int* waves_per_simd)
+{
+    int best = g.ny, best_w = (strips + 1023) / 1024;
+    uint64_t best_cost = (uint64_t)best_w * (uint64_t)(g.ny + 2 * K);
+    for (int w = 1; w <= 4; ++w) {
+        const int n = std::min(g.ny, 1024 * w / strips);
+        if (n < 1) continue;
+        const int rows = (g.ny + n - 1) / n;
+        const uint64_t cost = (uint64_t)w * (uint64_t)(rows + 2 * K);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = rows;
+            best_w = w;
+        }
+    }
+    if (waves_per_simd) *waves_per_simd = best_w;
+    return best;
+}
+
 template <int ST, int V>
 void launch_step_v(cmlbm2d_lattice* lat, hipStream_t s)
 {
@@ -478,6 +756,111 @@ void launch_step(cmlbm2d_lattice* lat, hipStream_t s)
         case CMLBM2D_FP16: launch_step_st<CMLBM2D_FP16>(lat, s); break;
         default: launch_step_st<CMLBM2D_BF16>(lat, s); break;
     }
+}
+
+// K steps in one pass of k2_march.
+template <int ST, int V, int K>
+void launch_march_k(cmlbm2d_lattice* lat, hipStream_t s)
+{
+    using T = typename storage2<ST>::T;
+    const Geom2& g = lat->g;
+    const int strips = march_strips(g, V, K), rows = march_rows2(g, strips, K, nullptr);
+    const uint64_t waves = (uint64_t)strips * (uint64_t)((g.ny + rows - 1) / rows);
+    const dim3 grid((unsigned)((waves + kBlock / 64 - 1) / (kBlock / 64)));
+    const T* src = (const T*)lat->pop[lat->cur];
+    T* dst = (T*)lat->pop[1 - lat->cur];
+    const T om = (T)(1.0 / lat->p.tau), r0 = (T)lat->p.rho0;
+    if (lat->force_mode == CMLBM2D_FORCE_FIELD)
+        k2_march<ST, V, K, true><<<grid, dim3(kBlock), 0, s>>>(src, dst, g, strips, rows, om, r0, T(0), T(0),
+                                                               (const T*)lat->field);
+    else
+        k2_march<ST, V, K, false><<<grid, dim3(kBlock), 0, s>>>(src, dst, g, strips, rows, om, r0, (T)lat->fu[0],
+                                                                (T)lat->fu[1], nullptr);
+}
+
+template <int ST>
+void launch_tile(cmlbm2d_lattice* lat, int K, hipStream_t s)
+{
+    using T = typename storage2<ST>::T;
+    const Geom2& g = lat->g;
+    const int strips = march_strips(g, 1, K), R = kTileRows - 2 * K;
+    const dim3 grid((unsigned)(strips * ((g.ny + R - 1) / R)));
+    const T* src = (const T*)lat->pop[lat->cur];
+    T* dst = (T*)lat->pop[1 - lat->cur];
+    const T om = (T)(1.0 / lat->p.tau), r0 = (T)lat->p.rho0;
+    if (lat->force_mode == CMLBM2D_FORCE_FIELD)
+        k2_tile<ST, true><<<grid, dim3(kTileRows * 64), 0, s>>>(src, dst, g, K, strips, om, r0, T(0), T(0),
+                                                                (const T*)lat->field);
+    else
+        k2_tile<ST, false><<<grid, dim3(kTileRows * 64), 0, s>>>(src, dst, g, K, strips, om, r0, (T)lat->fu[0],
+                                                                 (T)lat->fu[1], nullptr);
+}
+
+// The next launch of a call with n steps left: how many steps, in which kernel.
+struct Pass {
+    enum Kind { STEP, MARCH, TILE } kind;
+    int steps, V;
+};
+
+// The pass with the least time per step, by estimates of each kernel's launch
+// in us (measured, FP64 / FP32; the four-rolls mill on n x n cells):
+//   k2_step   3.0 + 160 (80) bytes per cell at 5.6 TB/s;
+//   k2_march  2.5 + waves per SIMD x (rows + 2 K) x 1.9 / 2.35 (FP32 one cell a lane 1.5);
+//             K = 2: x 2.3 / 2.4 (HBM-bound);
+//   k2_tile   with x = workgroups / 256: up to 1, 4.6 + 0.59 K + 3.7 x / 3.6 +
+//             0.53 K + 3.7 x; beyond, 3.5 + 7.5 x / 3.5 + 3.9 x.
+// us per step, k2_step / chosen: FP64 16^2 3.06 / 1.23 (tile), 64^2 3.18 / 1.25
+// (tile), 256^2 4.9 / 2.3 (tile), 500^2 9.3 / 5.8, 1024^2 30.9 / 13.8 (march),
+// 8192^2 1873 / 609 (march); FP32 64^2 3.4 / 1.04, 300^2 4.2 / 1.9, 1024^2 16.8 /
+// 10.1, 4096^2 223 / 94 (march), 8192^2 890 / 327 (march).
+Pass next_pass(const cmlbm2d_lattice* lat, int n)
+{
+    const Geom2& g = lat->g;
+    Pass best{Pass::STEP, 1, g.V};
+    if ((lat->p.storage != CMLBM2D_FP64 && lat->p.storage != CMLBM2D_FP32) || n < 2) return best;
+    const bool f64 = lat->p.storage == CMLBM2D_FP64;
+    double best_t = 3.0 + (double)g.ncell * (f64 ? 160.0 : 80.0) / 5.6e6;
+    auto consider = [&](Pass::Kind kind, int steps, int V, double t) {
+        if (t < best_t * steps) {
+            best_t = t / steps;
+            best = Pass{kind, steps, V};
+        }
+    };
+    const int V = f64 || g.nx % 2 ? 1 : 2;
+    for (int K = 2; K <= 4 && K <= n; K += 2) {
+        int w = 1;
+        const int rows = march_rows2(g, march_strips(g, V, K), K, &w);
+        const double per_row = K == 2 ? (f64 ? 2.3 : 2.4) : f64 ? 1.9 : V == 2 ? 2.35 : 1.5;
+        consider(Pass::MARCH, K, V, 2.5 + w * (double)(rows + 2 * K) * per_row);
+    }
+    for (int K = 2; K <= 7 && K <= n; ++K) {
+        const int R = kTileRows - 2 * K;
+        const double x = (double)march_strips(g, 1, K) * ((g.ny + R - 1) / R) / 256.0;
+        if (x > 8192) break;  // far beyond its range, and near a launch's work-items
+        const double t = x > 1.0 ? 3.5 + (f64 ? 7.5 : 3.9) * x : (f64 ? 4.6 + 0.59 * K : 3.6 + 0.53 * K) + 3.7 * x;
+        consider(Pass::TILE, K, 1, t);
+    }
+    return best;
+}
+
+template <int ST>
+void launch_pass_st(cmlbm2d_lattice* lat, const Pass& p, hipStream_t s)
+{
+    if (p.kind == Pass::TILE) return launch_tile<ST>(lat, p.steps, s);
+    if constexpr (ST == CMLBM2D_FP32) {
+        if (p.V == 2) return p.steps == 4 ? launch_march_k<ST, 2, 4>(lat, s) : launch_march_k<ST, 2, 2>(lat, s);
+    }
+    p.steps == 4 ? launch_march_k<ST, 1, 4>(lat, s) : launch_march_k<ST, 1, 2>(lat, s);
+}
+
+void launch_pass(cmlbm2d_lattice* lat, const Pass& p, hipStream_t s)
+{
+    if (p.kind == Pass::STEP)
+        launch_step(lat, s);
+    else if (lat->p.storage == CMLBM2D_FP64)
+        launch_pass_st<CMLBM2D_FP64>(lat, p, s);
+    else
+        launch_pass_st<CMLBM2D_FP32>(lat, p, s);
 }
 
 template <int ST>
@@ -625,12 +1008,14 @@ int cmlbm2d_step(cmlbm2d_lattice* lat, int32_t nsteps, void* hip_stream)
     if (nsteps < 0) return fail(lat, CMLBM2D_EINVAL, "nsteps must be >= 0");
     if (!lat->initialized) return fail(lat, CMLBM2D_ESTATE, "step before init");
     hipStream_t s = (hipStream_t)hip_stream;
-    for (int32_t k = 0; k < nsteps; ++k) {
-        launch_step(lat, s);
+    for (int32_t k = 0; k < nsteps;) {
+        const Pass p = next_pass(lat, nsteps - k);
+        launch_pass(lat, p, s);
         const int rc = launch_check(lat, "step");
         if (rc) return rc;
         lat->cur = 1 - lat->cur;
-        ++lat->t;
+        lat->t += p.steps;
+        k += p.steps;
     }
     return CMLBM2D_OK;
 }
