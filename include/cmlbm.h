@@ -184,6 +184,13 @@ int cmlbm_init(cmlbm_lattice* lat, const void* dev_rho, const void* dev_u, int i
  * is split into calls.  The buffer that does not hold the state is scratch. */
 int cmlbm_step(cmlbm_lattice* lat, int32_t nsteps, void* hip_stream);
 
+/* One time step (cmlbm_step with nsteps = 1) that also writes the velocity of
+ * the state it starts from, u(x, t) as cmlbm_moments gives it, into dev_u[3][N]
+ * of io_dtype.  With a force field, the method's own collision and io_dtype
+ * equal to the storage (FP64 or FP32) the step's kernel writes it and the
+ * populations are read once; otherwise it is the export, then the step. */
+int cmlbm_step_velocity(cmlbm_lattice* lat, void* dev_u, int io_dtype, void* hip_stream);
+
 /* rho(x, t) into dev_rho[N] and u(x, t) = (sum f c + F/2)/rho into dev_u[3][N]
  * (either may be NULL), io_dtype CMLBM_FP64 or CMLBM_FP32.  With dev_u NULL
  * only the populations are read (the force enters the velocity alone); the

@@ -33,7 +33,7 @@ NRED = 11
 
 # Every entry point declared in include/cmlbm.h.
 EXPORTS = ["cmlbm_required_bytes", "cmlbm_create", "cmlbm_set_solid", "cmlbm_set_force", "cmlbm_init",
-           "cmlbm_step", "cmlbm_moments", "cmlbm_reduce", "cmlbm_step_reduce", "cmlbm_populations",
+           "cmlbm_step", "cmlbm_step_velocity", "cmlbm_moments", "cmlbm_reduce", "cmlbm_step_reduce", "cmlbm_populations",
            "cmlbm_load_populations",
            "cmlbm_save_state", "cmlbm_restore_state", "cmlbm_get_time", "cmlbm_set_time", "cmlbm_destroy",
            "cmlbm_last_error", "cmlbm_status_string", "cmlbm_pseudopotential_force", "cmlbm_device_copy", "cmlbm_plane_copy",
@@ -71,6 +71,7 @@ def load_library():
     lib.cmlbm_set_force.argtypes = [vp, ctypes.c_int, ctypes.POINTER(ctypes.c_double), vp, ctypes.c_int, vp]
     lib.cmlbm_init.argtypes = [vp, vp, vp, ctypes.c_int, vp]
     lib.cmlbm_step.argtypes = [vp, i32, vp]
+    lib.cmlbm_step_velocity.argtypes = [vp, vp, ctypes.c_int, vp]
     lib.cmlbm_moments.argtypes = [vp, vp, vp, ctypes.c_int, vp]
     lib.cmlbm_reduce.argtypes = [vp, u32, ctypes.POINTER(ctypes.c_double), vp]
     lib.cmlbm_step_reduce.argtypes = [vp, ctypes.POINTER(ctypes.c_double), vp]
@@ -286,6 +287,15 @@ class Lattice:
 
     def step(self, n=1):
         self._check(self.lib.cmlbm_step(self.handle, int(n), self._stream()), "step")
+
+    def step_velocity(self, out):
+        """One step; the velocity of the state it starts from goes to out, a
+        contiguous (3, nbatch, nz, ny, nx) FP64 or FP32 tensor (returned)."""
+        assert out.is_contiguous() and tuple(out.shape) == (3,) + self.shape
+        assert out.dtype in (self.torch.float64, self.torch.float32)
+        io = FP64 if out.dtype == self.torch.float64 else FP32
+        self._check(self.lib.cmlbm_step_velocity(self.handle, _ptr(out), io, self._stream()), "step_velocity")
+        return out
 
     def moments(self, dtype=None):
         dtype = dtype or self.torch.float64

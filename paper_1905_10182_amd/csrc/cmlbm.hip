@@ -401,6 +401,28 @@ __device__ __forceinline__ void st_off(gchar* base, uint32_t byte_off, X v)
     }
 }
 
+// Density and half-force-corrected velocity of one cell in FP64.
+__device__ __forceinline__ void macro64(const double h[27], double rho0, const double F[3], double& rho, double u[3],
+                                        double j[3], double& drho)
+{
+    double s = 0, jx = 0, jy = 0, jz = 0;
+#pragma unroll
+    for (int i = 0; i < 27; ++i) {
+        s += h[i];
+        jx += vel_x(i) * h[i];
+        jy += vel_y(i) * h[i];
+        jz += vel_z(i) * h[i];
+    }
+    drho = s;
+    rho = rho0 + s;
+    j[0] = jx;
+    j[1] = jy;
+    j[2] = jz;
+    u[0] = (jx + 0.5 * F[0]) / rho;
+    u[1] = (jy + 0.5 * F[1]) / rho;
+    u[2] = (jz + 0.5 * F[2]) / rho;
+}
+
 // Most threads of a k_step workgroup: 1024 for FP32 storage, 512 for FP64
 // without a bounce-back mask, 256 otherwise (measured best for each on large
 // lattices; step_waves gives small ones 256).
@@ -434,9 +456,12 @@ __device__ __forceinline__ double wave_max(double v)
 // cell only skip their contributions and stores.  (RED is a template flag of
 // the kernel itself: a shared device function changed the register
 // allocation of the RED = false kernels.)
-// With MOUT the step stops before the reconstruction and stores the nine
-// numbers that determine the post-collision populations (k_march).
-template <int ST, int V, bool MASK, bool FIELD, bool NT, int MODEL, bool RED, bool SR, bool MOUT = false>
+// OUT = kOutMoments: the step stops before the reconstruction and stores the
+// nine numbers that determine the post-collision populations (k_march).
+// OUT = kOutVelocity: it also writes the velocity of the state it reads to
+// wpart as [3][cells] in the arithmetic type, with the sums of k_gather.
+constexpr int kOutPops = 0, kOutMoments = 1, kOutVelocity = 2;
+template <int ST, int V, bool MASK, bool FIELD, bool NT, int MODEL, bool RED, bool SR, int OUT = kOutPops>
 __global__ __launch_bounds__(step_block(ST, MASK)) void k_step(const typename storage<ST>::S* __restrict__ src,
                                                   typename storage<ST>::S* __restrict__ dst, Geom g, int segs, int wpb,
                                                   typename storage<ST>::T omega, typename storage<ST>::T rho0,
@@ -448,7 +473,9 @@ __global__ __launch_bounds__(step_block(ST, MASK)) void k_step(const typename st
     static_assert(V == 1 || !MASK, "bounce-back masks use one cell per lane");
     static_assert(MODEL == 0 || V == 1, "comparison models use one cell per lane");
     static_assert(!RED || MODEL == 0, "fused reductions are for the method's collision");
-    static_assert(!MOUT || (V == 1 && MODEL == 0 && !RED && ST <= CMLBM_FP32), "moment output: FP64 / FP32, the method's collision");
+    static_assert(OUT == kOutPops || (V == 1 && MODEL == 0 && !RED && ST <= CMLBM_FP32),
+                  "moment and velocity output: FP64 / FP32, the method's collision");
+    static_assert(OUT != kOutVelocity || FIELD, "velocity output: a force field");
     using SS = storage<ST>;
     using S = typename SS::S;
     using T = typename SS::T;
@@ -493,10 +520,15 @@ __global__ __launch_bounds__(step_block(ST, MASK)) void k_step(const typename st
                                 (uint32_t)wrap(xa - 1, g.nx) * (uint32_t)sizeof(S)};
         uint32_t m = 0;
         if (MASK) m = active ? mask[own_row + x0] : kSolidBit;
-        if constexpr (RED)
+        if constexpr (RED) {
             live = active && !(m & kSolidBit);
-        else if (!active || (m & kSolidBit))
+        } else if (!active || (m & kSolidBit)) {
+            if constexpr (OUT == kOutVelocity) {
+                if (active)
+                    for (int a = 0; a < 3; ++a) ((T*)wpart)[a * g.ncell + (uint64_t)row * (uint64_t)g.nx + x0] = T(0);
+            }
             return;
+        }
 #pragma unroll
         for (int i = 0; i < 27; ++i) {
             const S* plane_row = srow[vel_y(i) + 1][vel_z(i) + 1] + (uint64_t)i * g.pstride;
@@ -582,6 +614,15 @@ __global__ __launch_bounds__(step_block(ST, MASK)) void k_step(const typename st
             Fy[c] *= kS;
             Fz[c] *= kS;
         }
+    if constexpr (OUT == kOutVelocity) {
+        double hd[27], u[3], j[3], rho, drho;
+        const double F[3] = {(double)Fx[0], (double)Fy[0], (double)Fz[0]};
+#pragma unroll
+        for (int i = 0; i < 27; ++i) hd[i] = (double)h[0][i];
+        macro64(hd, (double)rho0, F, rho, u, j, drho);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) ((T*)wpart)[a * g.ncell + (uint64_t)row * (uint64_t)g.nx + x0] = (T)u[a];
+    }
     T mq[RED ? V : 1][4];  // RED: each cell's drho, ux, uy, uz
 #pragma unroll
     for (int c = 0; c < V; ++c) {
@@ -604,7 +645,7 @@ __global__ __launch_bounds__(step_block(ST, MASK)) void k_step(const typename st
             mq[c][1] = ux;
             mq[c][2] = uy;
             mq[c][3] = uz;
-        } else if constexpr (MOUT) {
+        } else if constexpr (OUT == kOutMoments) {
             T drho, k5[5];
             lockstep::pre_collision(h[c], Fx[c], Fy[c], Fz[c], rho0s, drho, ux, uy, uz, k5);
             const T om1 = T(1) - omega;
@@ -1313,27 +1354,6 @@ __device__ __forceinline__ void cell_force64(const Geom& g, const Cell& c, const
         F[1] = fr[1];
         F[2] = fr[2];
     }
-}
-
-__device__ __forceinline__ void macro64(const double h[27], double rho0, const double F[3], double& rho, double u[3],
-                                        double j[3], double& drho)
-{
-    double s = 0, jx = 0, jy = 0, jz = 0;
-#pragma unroll
-    for (int i = 0; i < 27; ++i) {
-        s += h[i];
-        jx += vel_x(i) * h[i];
-        jy += vel_y(i) * h[i];
-        jz += vel_z(i) * h[i];
-    }
-    drho = s;
-    rho = rho0 + s;
-    j[0] = jx;
-    j[1] = jy;
-    j[2] = jz;
-    u[0] = (jx + 0.5 * F[0]) / rho;
-    u[1] = (jy + 0.5 * F[1]) / rho;
-    u[2] = (jz + 0.5 * F[2]) / rho;
 }
 
 // rho/u (io FP64 or FP32) or FP64 populations of the current state
@@ -2126,7 +2146,7 @@ void launch_to_moments_t(cmlbm_lattice* lat, hipStream_t s)
     const int wpb = step_waves<ST, MASK>(waves);
     const dim3 grid((unsigned)((waves + wpb - 1) / wpb));
     const T* ftab = (const T*)(lat->scratch + (ST == CMLBM_FP64 ? lat->off_ftab64 : lat->off_ftab32));
-    k_step<ST, 1, MASK, FIELD, true, 0, false, false, true><<<grid, dim3(64 * wpb), 0, s>>>(
+    k_step<ST, 1, MASK, FIELD, true, 0, false, false, kOutMoments><<<grid, dim3(64 * wpb), 0, s>>>(
         (const T*)lat->pop[lat->cur], (T*)lat->pop[1 - lat->cur], g, segs, wpb, (T)(1.0 / lat->p.tau), (T)lat->p.rho0, ftab,
         (const T*)lat->field, mask_ptr(lat), (uint32_t)lat->t, nullptr);
 }
@@ -2192,6 +2212,39 @@ int launch_step(cmlbm_lattice* lat, hipStream_t s)
         case CMLBM_FP16: return launch_step_st<CMLBM_FP16>(lat, s);
         default: return launch_step_st<CMLBM_BF16>(lat, s);
     }
+}
+
+// One step that also writes the velocity of the state it reads to u (the
+// storage's arithmetic type); only where velocity_fused() allows.
+bool velocity_fused(const cmlbm_lattice* lat, int io_dtype)
+{
+    return lat->force_mode == CMLBM_FORCE_FIELD && !lat_model(lat) && lat->p.storage <= CMLBM_FP32 &&
+           io_dtype == lat->p.storage && (io_dtype == CMLBM_FP64 || lat->p.rho0 == (double)(float)lat->p.rho0);
+}
+
+template <int ST, bool MASK>
+void launch_step_velocity_t(cmlbm_lattice* lat, void* u, hipStream_t s)
+{
+    using T = typename storage<ST>::T;
+    const Geom& g = lat->g;
+    const int segs = (g.nx + 63) / 64;
+    const uint64_t waves = (uint64_t)g.rows * (uint64_t)segs;
+    const int wpb = step_waves<ST, MASK>(waves);
+    const dim3 grid((unsigned)((waves + wpb - 1) / wpb));
+    k_step<ST, 1, MASK, true, true, 0, false, false, kOutVelocity><<<grid, dim3(64 * wpb), 0, s>>>(
+        (const T*)lat->pop[lat->cur], (T*)lat->pop[1 - lat->cur], g, segs, wpb, (T)(1.0 / lat->p.tau), (T)lat->p.rho0,
+        nullptr, (const T*)lat->field, mask_ptr(lat), (uint32_t)lat->t, (double*)u);
+}
+
+int launch_step_velocity(cmlbm_lattice* lat, void* u, hipStream_t s)
+{
+    if (lat->p.storage == CMLBM_FP64)
+        lat->needs_mask ? launch_step_velocity_t<CMLBM_FP64, true>(lat, u, s)
+                        : launch_step_velocity_t<CMLBM_FP64, false>(lat, u, s);
+    else
+        lat->needs_mask ? launch_step_velocity_t<CMLBM_FP32, true>(lat, u, s)
+                        : launch_step_velocity_t<CMLBM_FP32, false>(lat, u, s);
+    return launch_check(lat, "step (velocity)");
 }
 
 template <int ST, bool MASK>
@@ -2525,6 +2578,27 @@ int cmlbm_step(cmlbm_lattice* lat, int32_t nsteps, void* hip_stream)
         lat->cur = 1 - lat->cur;
         lat->t += 1;
     }
+    return CMLBM_OK;
+}
+
+int cmlbm_step_velocity(cmlbm_lattice* lat, void* dev_u, int io_dtype, void* hip_stream)
+{
+    if (!lat) return CMLBM_EINVAL;
+    if (io_dtype != CMLBM_FP64 && io_dtype != CMLBM_FP32) return fail(lat, CMLBM_EINVAL, "io_dtype must be FP64/FP32");
+    if (!lat->initialized) return fail(lat, CMLBM_ESTATE, "step before init");
+    if (!dev_u) return fail(lat, CMLBM_EINVAL, "step_velocity needs dev_u[3][N]");
+    hipStream_t s = (hipStream_t)hip_stream;
+    int rc;
+    if (velocity_fused(lat, io_dtype)) {
+        rc = launch_step_velocity(lat, dev_u, s);
+    } else {
+        rc = launch_gather(lat, nullptr, dev_u, io_dtype == CMLBM_FP64, nullptr, s);
+        if (rc) return rc;
+        rc = launch_step(lat, s);
+    }
+    if (rc) return rc;
+    lat->cur = 1 - lat->cur;
+    lat->t += 1;
     return CMLBM_OK;
 }
 

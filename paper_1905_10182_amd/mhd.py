@@ -196,6 +196,15 @@ class MagneticLattice:
                                               _ptr(F_out), self._stream()), "fields")
         return b, j
 
+    def lorentz_force(self, F_out, u=None, current="populations", b=None):
+        """The Lorentz force F = j x b (plus the body force) alone, into F_out (a
+        contiguous device tensor of 3N values).  The stencil current works on b
+        ((3, nz, ny, nx), overwritten) and does not read u; the population
+        current needs u and no b."""
+        assert F_out.is_contiguous() and F_out.dtype == self.dtype and F_out.numel() == 3 * int(np.prod(self.shape))
+        self._check(self.lib.cmlbm_mhd_fields(self.handle, _ptr(self._vec(u)), CURRENT[current], _ptr(b), None,
+                                              _ptr(F_out), self._stream()), "fields")
+
     def populations(self):
         out = self.torch.empty((7, 3) + self.shape, dtype=self.torch.float64, device=self.device)
         self._check(self.lib.cmlbm_mhd_populations(self.handle, _ptr(out), self._stream()), "populations")
@@ -217,6 +226,9 @@ class CoupledMHD:
       (c) u = fluid velocity with F;
       (d) magnetic collision towards h^eq(b, u) and streaming;
       (e) fluid step with F.
+    The stencil current does not depend on u_lag, so (a) runs for the population
+    current only; (c) and (e) read the same populations with the same force and
+    are one launch (cmlbm_step_velocity).
     `model` is a fluid collision model of cmlbm.MODELS (m1, m4, m5, ...).
     `wall` flags axes with walls for both lattices (fluid: halfway
     bounce-back; field: b = b_wall there); `body_force` is a uniform force
@@ -235,6 +247,7 @@ class CoupledMHD:
         self.shape = (int(nz), int(ny), int(nx))
         self.dtype = self.mag.dtype
         self.F = self.torch.zeros((3, 1) + self.shape, dtype=self.dtype, device=self.mag.device)
+        self._u = self._b = None  # step()'s work arrays, from its first call on
 
     def init(self, rho, u, b):
         u = np.asarray(u, np.float64).reshape((3,) + self.shape)
@@ -249,12 +262,15 @@ class CoupledMHD:
         return self.fluid.moments(dtype=dt)
 
     def step(self, n=1):
+        if self._u is None:
+            self._u = self.torch.empty((3, 1) + self.shape, dtype=self.dtype, device=self.mag.device)
+            if self.current == "stencil":
+                self._b = self.torch.empty((3,) + self.shape, dtype=self.dtype, device=self.mag.device)
         for _ in range(int(n)):
-            _, u_lag = self.velocity()
-            self.mag.fields(u_lag, self.current, F_out=self.F)
-            _, u = self.velocity()
-            self.mag.step(u)
-            self.fluid.step(1)
+            u_lag = None if self.current == "stencil" else self.velocity()[1]
+            self.mag.lorentz_force(self.F, u_lag, self.current, self._b)
+            self.fluid.step_velocity(self._u)
+            self.mag.step(self._u)
 
     @property
     def time(self):
