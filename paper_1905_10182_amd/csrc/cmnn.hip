@@ -379,6 +379,196 @@ __global__ __launch_bounds__(256) void k_conv_tile(G g, const bf16* __restrict__
 }
 
 // ---------------------------------------------------------------------------
+// row-tiled forward convolution (and data gradient), for extents that are
+// multiples of 4 x 8 x 16 (d, h, w)
+//
+// Workgroup = a brick of 512 output voxels x 32 output channels; wave w owns
+// depth slice w, eight rows of 16 x-consecutive voxels.  Per 32-channel input
+// chunk the 6 x 10 x 18 halo is staged in LDS, 64 bytes per voxel with the
+// 16-byte channel groups XOR-swizzled by (x / 2) mod 4 (eight consecutive
+// voxels of a fragment read then cover all banks without padding, and two
+// workgroups fit a CU).  For each of the three depth taps a wave holds the nine
+// (dy, dx) weight fragments in registers and walks down the ten halo rows once:
+// a row is read once per x tap and feeds up to 18 MFMAs, those of the three
+// output rows it is a neighbour of.
+// Against the 4 x 4 x 16 brick kernel, which is bound by its weight reads from
+// L1 and by the vector instructions between MFMAs, this reads the weights half
+// as often per voxel and the halo 0.83 times, finds the halo rows' sources once
+// per workgroup instead of once per thread and part, and writes four
+// consecutive channels of a voxel per lane (8-byte stores: the weights are the
+// first MFMA operand).  The x - 1 and x + 1 fragments are LDS reads of their
+// own: built from the centre one by lane shifts they cost as much issue time as
+// the MFMAs (75 us instead of 66).  Each output adds its products in the order
+// of the brick kernel: same bits.
+// 16 x 32 x 32 x 64, 32 -> 32: 91 -> 66 us forward, 81 -> 59 us data gradient
+// (983 TFLOP/s); 96 -> 32: 220 -> 170 and (32 -> 96) 182 -> 155; 160 -> 64 at
+// half extents: 92 -> 77 and 134 -> 85.
+constexpr int kRH = 8, kRHH = kRH + 2, kRRows = kHD * kRHH;  // 60 halo rows of 18 voxels
+constexpr uint32_t kRRow = kHW * 64;                          // bytes of a halo row
+constexpr int kRParts = kHW * 4;                              // 16-byte parts of a halo row: 72
+constexpr int kRIters = kRRows / 3;                           // three rows are staged at a time, by 216 threads
+constexpr uint32_t kNone = 0xffffff00u;                       // past every buffer range: loads give 0
+
+template <int SIGN, int ACT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_conv_rows(
+    G g, const bf16* __restrict__ x, int cin, const bf16* __restrict__ wt, const float* __restrict__ bias, int cout,
+    bf16* __restrict__ y, unsigned xcd_span, const bf16* __restrict__ gate)
+{
+    typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    __shared__ __attribute__((aligned(128))) char sx[kRRows * kRRow];
+    __shared__ uint32_t row_off[kRRows];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // blocks are dealt round-robin to the 8 XCDs: each XCD gets a contiguous
+    // run of (brick, output block) pairs, the blocks of a brick together
+    unsigned bid = blockIdx.x;
+    if (xcd_span) bid = (bid & 7u) * xcd_span + (bid >> 3);
+    const int ncb = cout / 32;
+    const int co0 = (int)(bid % ncb) * 32;
+    int r0 = (int)(bid / ncb);
+    const int nbw = g.w / kTW, nbh = g.h / kRH, nbd = g.d / kTD;
+    const int x0 = (r0 % nbw) * kTW;
+    r0 /= nbw;
+    const int h0 = (r0 % nbh) * kRH;
+    r0 /= nbh;
+    const int d0 = (r0 % nbd) * kTD;
+    const long long n = r0 / nbd;
+    // halo staging: the source offset of each row within the sample (kNone
+    // where it is padding) once per workgroup; a thread keeps one voxel column
+    // and channel part
+    auto source = [](int v, int q, int ext, int periodic, bool& out) -> int {
+        const int t = v + q - 1, w = t < 0 ? t + ext : t >= ext ? t - ext : t;
+        out |= t != w && !periodic;
+        return w;
+    };
+    if (tid < kRRows) {
+        bool out = false;
+        const int sd = source(d0, tid / kRHH, g.d, g.per[0], out), sh = source(h0, tid % kRHH, g.h, g.per[1], out);
+        row_off[tid] = out ? kNone : (uint32_t)(sd * g.h + sh) * (uint32_t)g.w * (uint32_t)cin * 2u;
+    }
+    const int trow = tid / kRParts, hx = (tid - trow * kRParts) >> 2, part = tid & 3;
+    uint32_t col_off;
+    {
+        bool out = trow >= 3;
+        const int sw = source(x0, hx, g.w, g.per[2], out);
+        col_off = out ? kNone : ((uint32_t)sw * (uint32_t)cin + (uint32_t)part * 8u) * 2u;
+    }
+    char* const put = sx + trow * kRRow + hx * 64 + ((part ^ ((hx >> 1) & 3)) << 4);
+    const uint32_t sample = (uint32_t)g.d * (uint32_t)g.h * (uint32_t)g.w * (uint32_t)cin * 2u;
+    const __amdgpu_buffer_rsrc_t xr = buf_rsrc(x + n * (long long)(sample / 2u), sample);
+    const __amdgpu_buffer_rsrc_t wr = buf_rsrc(wt, 27u * (uint32_t)cout * (uint32_t)cin * 2u);
+    const uint32_t wlane = ((uint32_t)(co0 + (lane & 15)) * (uint32_t)cin + (uint32_t)(lane >> 4) * 8u) * 2u;
+    // this lane's output channels co + 16 b + i
+    const int co = co0 + (lane >> 4) * 4;
+    f4 bb[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
+    if (SIGN > 0 && bias) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) bb[b][i] = bias[co + 16 * b + i];
+    }
+    f4 acc[kRH][2];
+#pragma unroll
+    for (int m = 0; m < kRH; ++m) acc[m][0] = acc[m][1] = f4{0.f, 0.f, 0.f, 0.f};
+    // LDS fragment reads: voxel x = lane % 16 + dx of a halo row, dx = 0, 1, 2
+    uint32_t lane_a[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const uint32_t vx = (uint32_t)(lane & 15) + (uint32_t)k, grp = (uint32_t)(lane >> 4);
+        lane_a[k] = vx * 64u + ((grp ^ ((vx >> 1) & 3u)) << 4);
+    }
+    __syncthreads();
+    for (int c0 = 0; c0 < cin; c0 += 32) {
+        u4 stage[kRIters];
+#pragma unroll
+        for (int it = 0; it < kRIters; ++it) {
+            const uint32_t row = row_off[(it * 3 + trow) % kRRows];
+            stage[it] = __builtin_bit_cast(u4, ldb8(xr, __builtin_elementwise_add_sat(row, col_off), (uint32_t)c0 * 2u));
+        }
+        __syncthreads();
+        if (trow < 3) {
+#pragma unroll
+            for (int it = 0; it < kRIters; ++it) *(u4*)(put + it * 3 * kRRow) = stage[it];
+        }
+        __syncthreads();
+        // weight fragments of (depth tap tz, row tap ty): reloaded in place for
+        // tz + 1 as soon as the last row that needs them is done, so that a
+        // row or two of MFMAs covers the load.  The order is pinned per row:
+        // left to itself the compiler sinks each load to its first use.
+        bf16x8 bw[9][2];
+        auto wload = [&](int tz, int ty) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+                    bw[ty * 3 + j][b] = ldb8(wr, wlane, (((uint32_t)(tz * 9 + ty * 3 + j) * (uint32_t)cout + 16u * b) * (uint32_t)cin + (uint32_t)c0) * 2u);
+        };
+#pragma unroll
+        for (int ty = 0; ty < 3; ++ty) wload(0, ty);
+        bf16x8 af[2][3];
+        auto row_load = [&](int s30) {  // row s30 % 10 of depth tap s30 / 10
+            const int dz = SIGN * (s30 / kRHH - 1), r = SIGN > 0 ? s30 % kRHH : kRHH - 1 - s30 % kRHH;
+            const char* row = sx + (uint32_t)((wv + 1 + dz) * kRHH + r) * kRRow;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) af[s30 & 1][k] = *(const bf16x8*)(row + lane_a[k]);
+        };
+        row_load(0);
+#pragma unroll
+        for (int s30 = 0; s30 < 3 * kRHH; ++s30) {
+            const int tz = s30 / kRHH, rr = s30 % kRHH, r = SIGN > 0 ? rr : kRHH - 1 - rr;
+            if (s30 + 1 < 3 * kRHH) row_load(s30 + 1);
+            if (tz < 2 && rr >= kRH) wload(tz + 1, rr - kRH);  // ty = 0 after its last row, 1 after its last
+            if (tz > 0 && rr == 0) wload(tz, 2);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+#pragma unroll
+                for (int ty = 0; ty < 3; ++ty) {
+                    const int m = r - 1 - SIGN * (ty - 1);
+                    if (m < 0 || m >= kRH) continue;
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+                        acc[m][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            bw[ty * 3 + j][b], af[s30 & 1][SIGN > 0 ? j : 2 - j], acc[m][b], 0, 0, 0);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // D[row][col]: row = output channel (lane / 16) * 4 + i, col = voxel lane % 16;
+    // a lane offset and a wave-uniform offset within the sample
+    const uint32_t sample_y = (uint32_t)g.d * (uint32_t)g.h * (uint32_t)g.w * (uint32_t)cout * 2u;
+    const __amdgpu_buffer_rsrc_t yr = buf_rsrc(y + n * (long long)(sample_y / 2u), sample_y);
+    const __amdgpu_buffer_rsrc_t gr = buf_rsrc(gate + n * (long long)(sample_y / 2u), sample_y);
+    const uint32_t ylane = ((uint32_t)(lane & 15) * (uint32_t)cout + (uint32_t)co) * 2u;
+#pragma unroll
+    for (int m = 0; m < kRH; ++m) {
+        const uint32_t yrow = (uint32_t)(((d0 + wv) * g.h + h0 + m) * g.w + x0) * (uint32_t)cout * 2u;
+        u2 gt[2];
+        if (SIGN < 0 && ACT == CMNN_ACT_LEAKY) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b) gt[b] = __builtin_amdgcn_raw_buffer_load_b64(gr, ylane, yrow + 32u * b, 0);
+        }
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            bf16x4 o;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float f = acc[m][b][i];
+                if (SIGN > 0) {
+                    f += bb[b][i];
+                    if (ACT == CMNN_ACT_LEAKY) f = f > 0.f ? f : kLeak * f;
+                } else if (ACT == CMNN_ACT_LEAKY) {
+                    if ((float)__builtin_bit_cast(bf16x4, gt[b])[i] <= 0.f) f *= kLeak;
+                }
+                o[i] = (bf16)f;
+            }
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, o), yr, ylane, yrow + 32u * b, 0);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // weight gradient
 //
 // Workgroup (chunk, tap, co tile of 32, ci tile of 32) accumulates over the
@@ -1578,6 +1768,15 @@ int conv_tile_launch(const G& g, const bf16* x, int cin, const bf16* w, const fl
 }
 
 template <int SIGN, int ACT>
+int conv_rows_launch(const G& g, const bf16* x, int cin, const bf16* w, const float* bias, int cout, bf16* y,
+                     const bf16* gate, hipStream_t s)
+{
+    const unsigned blocks = (unsigned)(g.nvox / (kTD * kRH * kTW)) * (unsigned)(cout / 32);
+    k_conv_rows<SIGN, ACT><<<dim3(blocks), 256, 0, s>>>(g, x, cin, w, bias, cout, y, blocks % 8 == 0 ? blocks / 8 : 0, gate);
+    return launched();
+}
+
+template <int SIGN, int ACT>
 int conv_dispatch(const G& g, const bf16* x, int cin, const bf16* w, const float* bias, int cout, bf16* y,
                   const bf16* gate, hipStream_t s)
 {
@@ -1586,6 +1785,15 @@ int conv_dispatch(const G& g, const bf16* x, int cin, const bf16* w, const float
         // widest output tile that still leaves >= 512 workgroups (two per CU)
         const long long bricks = g.nvox / (kTD * kTH * kTW);
         const int c16 = cout / 16;
+        // The row kernel's workgroup does the work of four 16-channel bricks in
+        // one pass, so it needs workgroups for three quarters of the CUs to win:
+        // 192 -> 25 us against 29 (bricks), 256 -> 24 / 33, 512 -> 20 / 26; at 128
+        // it is 11.6 / 10.6 and at 96 22 / 20.  It has 32-bit offsets within a
+        // sample and stores 8 bytes at a time.
+        const long long row_blocks = bricks / 2 * (c16 / 2);
+        const bool rows32 = g.nvox / g.n * 2 * (cin > cout ? cin : cout) < (long long)kNone;
+        if (g.h % kRH == 0 && row_blocks >= 192 && row_blocks < (1LL << 31) && rows32 && ((uintptr_t)y & 7u) == 0)
+            return conv_rows_launch<SIGN, ACT>(g, x, cin, w, bias, cout, y, gate, s);
         if (c16 % 6 == 0 && bricks * (c16 / 6) >= 512) return conv_tile_launch<6, SIGN, ACT>(g, x, cin, w, bias, cout, y, gate, s);
         if (c16 % 4 == 0 && bricks * (c16 / 4) >= 512) return conv_tile_launch<4, SIGN, ACT>(g, x, cin, w, bias, cout, y, gate, s);
         // a grid of fewer workgroups than CUs takes 16-channel tiles (twice the workgroups)
