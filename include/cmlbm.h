@@ -174,13 +174,14 @@ int cmlbm_set_force(cmlbm_lattice* lat, int mode, const double* host_values, con
  * Resets the step counter to 0. */
 int cmlbm_init(cmlbm_lattice* lat, const void* dev_rho, const void* dev_u, int io_dtype, void* hip_stream);
 
-/* Advance nsteps >= 0 time steps: each step is one fused launch doing the
+/* Advance nsteps >= 0 time steps: each step is one fused pass doing the
  * pull-streaming gather (eq. "streaming"), collision in central-moment space
  * (eqs. "macroscopic", "pre_collision",
  * "post_collision_central_moments_forcing", "system") and the store.  FP64 and
  * FP32 storage may pass through the nine numbers that determine the
- * post-collision populations between the first and the last step of a call
- * (chosen by size); the populations after n steps are the same bits however n
+ * post-collision populations between the first and the last step of a call,
+ * or take two or three steps of a small lattice in one launch (chosen by
+ * size); the populations after n steps are the same bits however n
  * is split into calls.  The buffer that does not hold the state is scratch. */
 int cmlbm_step(cmlbm_lattice* lat, int32_t nsteps, void* hip_stream);
 

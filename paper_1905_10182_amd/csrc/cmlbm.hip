@@ -7,6 +7,7 @@
 //                with RED also the FP64 partial sums of the state it reads
 //   k_march      the step of the moment representation: moment storage, and
 //                FP64 / FP32 storage between the first and last step of a call
+//   k_tile       two or three steps of a small FP64 / FP32 lattice in one launch
 //   k_red_waves  second level of those sums
 //   k_init       inverse of the gather: writes a given pre-collision state
 //   k_gather     rho/u or FP64 populations from the current state
@@ -769,6 +770,104 @@ __global__ __launch_bounds__(step_block(ST, MASK)) void k_step(const typename st
                 st_buf<NT>(plane_row, (uint32_t)g.nxp * (uint32_t)sizeof(S), bst, o);
             else
                 st_off<NT>(plane_row, bst, o);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// K steps of a small lattice in one launch
+//
+// A step of a few hundred waves is a chain of latencies: about 2 us from one
+// launch to the next, one trip to memory, and the collision of a single wave
+// (dependent vector instructions, nothing else to issue).  k_tile does K steps
+// for one launch and one trip.  A workgroup owns a CX x CY x CZ tile.  Stage 0
+// pulls from memory and collides the tile and a halo of K - 1 cells and keeps
+// the post-collision populations in LDS; each later stage pulls from there on a
+// region one cell smaller on every side; the last one stores the tile.  Every
+// cell update is k_step's, so K steps give the bits of K launches of k_step.
+// Stages are unrolled: with one looped stage and a fixed cell per thread the
+// later stages run half-empty waves and a step takes 3 to 15% longer.
+// us a step, k_step / 3 steps on 4 x 4 x 4 tiles / 2 on 8 x 4 x 2: FP64 with
+// walls 32 x 16 x 16 5.8 / 3.8 / 4.0, FP64 32 x 16 x 16 6.5 / 3.4 / 3.5, 32 x 32 x
+// 16 6.9 / 4.1 / 4.4, 32^3 7.2 / 7.2 / 5.3, 48 x 40 x 40 10.2 / 16 / 11.2; FP32
+// 32 x 16 x 16 5.4 / 2.8 / 3.2, 32^3 4.8 / 4.5 / 4.7, 48 x 40 x 40 6.6 / 10.1 / 9.0.
+template <int K, int CX, int CY, int CZ>
+struct TileBox {
+    static constexpr int x = CX + 2 * (K - 1), y = CY + 2 * (K - 1), z = CZ + 2 * (K - 1), cells = x * y * z;
+    static constexpr int threads = (cells + 63) / 64 * 64;
+};
+
+template <typename T, int K, int CX, int CY, int CZ, bool MASK, bool FIELD>
+__global__ __launch_bounds__((TileBox<K, CX, CY, CZ>::threads)) void k_tile(
+    const T* __restrict__ src, T* __restrict__ dst, Geom g, T omega, T rho0, const T* __restrict__ ftab,
+    const T* __restrict__ field, const uint32_t* __restrict__ mask)
+{
+    using B = TileBox<K, CX, CY, CZ>;
+    __shared__ T f[27 * B::cells];
+    const int ntx = (g.nx + CX - 1) / CX, nty = (g.ny + CY - 1) / CY, ntz = (g.nz + CZ - 1) / CZ;
+    int blk = blockIdx.x;
+    const int x0 = blk % ntx * CX - (K - 1);
+    blk /= ntx;
+    const int y0 = blk % nty * CY - (K - 1);
+    blk /= nty;
+    const int z0 = blk % ntz * CZ - (K - 1), b = blk / ntz;
+#pragma unroll
+    for (int s = 0; s < K; ++s) {
+        const int R = K - 1 - s, sx = CX + 2 * R, sy = CY + 2 * R, sz = CZ + 2 * R;
+        const int t = (int)threadIdx.x;
+        bool on = t < sx * sy * sz;
+        const int bx = t % sx + s, by = t / sx % sy + s, bz = t / (sx * sy) + s;  // in the box
+        const int at = bx + B::x * (by + B::y * bz);
+        if (s == K - 1) on = on && x0 + bx < g.nx && y0 + by < g.ny && z0 + bz < g.nz;
+        const int x = wrap(x0 + bx, g.nx), y = wrap(y0 + by, g.ny), z = wrap(z0 + bz, g.nz);
+        const uint32_t row = (uint32_t)((b * g.nz + z) * g.ny + y);
+        uint32_t m = 0;
+        if (MASK && on) {
+            m = mask[row * (uint32_t)g.nxp + (uint32_t)x];
+            on = !(m & kSolidBit);
+        }
+        T h[27];
+        if (on) {
+            if (s == 0) {
+                const uint32_t rs = (uint32_t)g.rstride * (uint32_t)sizeof(T);
+                uint32_t ro[3][3], xo[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) xo[a] = (uint32_t)wrap(x - (a - 1), g.nx) * (uint32_t)sizeof(T);
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+#pragma unroll
+                    for (int d = 0; d < 3; ++d)
+                        ro[c][d] = (uint32_t)((b * g.nz + wrap(z - (d - 1), g.nz)) * g.ny + wrap(y - (c - 1), g.ny)) * rs;
+                const uint32_t ps = (uint32_t)g.pstride * (uint32_t)sizeof(T);
+#pragma unroll
+                for (int i = 0; i < 27; ++i) {
+                    const bool bounce = MASK && ((m >> i) & 1u);
+                    const uint32_t pull = (uint32_t)i * ps + ro[vel_y(i) + 1][vel_z(i) + 1] + xo[vel_x(i) + 1];
+                    h[i] = ld_off<T>(src, bounce ? (uint32_t)opposite(i) * ps + ro[1][1] + xo[1] : pull);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 27; ++i) {
+                    const bool bounce = MASK && ((m >> i) & 1u);
+                    const int pull = i * B::cells - (vel_x(i) + B::x * (vel_y(i) + B::y * vel_z(i)));
+                    h[i] = f[at + (bounce ? opposite(i) * B::cells : pull)];
+                }
+            }
+            const T* fr = FIELD ? field + (uint64_t)row * g.nx + x : ftab + 3 * (b * g.ny + y);
+            const uint64_t fs = FIELD ? g.ncell : 1;
+            lockstep::collide<T>(h, fr[0], fr[fs], fr[2 * fs], omega, rho0);
+        }
+        if (s > 0 && s < K - 1) __syncthreads();  // the reads of this stage before its writes
+        if (s < K - 1) {
+            if (on) {
+#pragma unroll
+                for (int i = 0; i < 27; ++i) f[i * B::cells + at] = h[i];
+            }
+            __syncthreads();
+        } else if (on) {
+            T* o = dst + row * g.rstride + (uint64_t)x;
+#pragma unroll
+            for (int i = 0; i < 27; ++i) o[i * g.pstride] = h[i];
         }
     }
 }
@@ -2175,6 +2274,58 @@ int launch_to_moments(cmlbm_lattice* lat, hipStream_t s)
                                         : launch_to_moments_st<CMLBM_FP32>(lat, s);
 }
 
+template <int K, int CX, int CY, int CZ>
+uint64_t tile_count(const Geom& g)
+{
+    return (uint64_t)((g.nx + CX - 1) / CX) * ((g.ny + CY - 1) / CY) * ((g.nz + CZ - 1) / CZ) * g.nb;
+}
+
+template <typename T, int K, int CX, int CY, int CZ>
+void launch_tile_t(cmlbm_lattice* lat, hipStream_t s)
+{
+    const Geom& g = lat->g;
+    const dim3 grid((unsigned)tile_count<K, CX, CY, CZ>(g)), block(TileBox<K, CX, CY, CZ>::threads);
+    const T* ftab = (const T*)(lat->scratch + (sizeof(T) == 8 ? lat->off_ftab64 : lat->off_ftab32));
+    auto go = [&](auto mask, auto field) {
+        constexpr bool MASK = decltype(mask)::value, FIELD = decltype(field)::value;
+        k_tile<T, K, CX, CY, CZ, MASK, FIELD><<<grid, block, 0, s>>>(
+            (const T*)lat->pop[lat->cur], (T*)lat->pop[1 - lat->cur], g, (T)(1.0 / lat->p.tau), (T)lat->p.rho0, ftab,
+            FIELD ? (const T*)lat->field : nullptr, mask_ptr(lat));
+    };
+    const bool F = lat->force_mode == CMLBM_FORCE_FIELD;
+    if (lat->needs_mask)
+        F ? go(std::true_type{}, std::true_type{}) : go(std::true_type{}, std::false_type{});
+    else
+        F ? go(std::false_type{}, std::true_type{}) : go(std::false_type{}, std::false_type{});
+}
+
+// How many of n steps one launch of k_tile takes (0: none).  The tile's halo
+// makes it do 4.1 (three steps) or 2.4 (two) collisions per cell and step, so
+// it pays only while the workgroups fit the chip at once: one per CU for three
+// FP64 steps (110 KB of LDS each), else two (k_tile's figures: FP64 32^3, 512
+// workgroups, 7.2 us a step by threes, 5.3 by twos, 7.2 by k_step).  A halo
+// cell wraps around an axis once: no axis shorter than a tile and its halo.
+int tile_steps(const cmlbm_lattice* lat, int n)
+{
+    const Geom& g = lat->g;
+    const bool f64 = lat->p.storage == CMLBM_FP64;
+    if (n < 2 || (!f64 && lat->p.storage != CMLBM_FP32) || lat_model(lat)) return 0;
+    if (g.nx < 8 || g.ny < 8 || g.nz < 8) return 0;
+    const uint64_t cus = lat->cus > 0 ? lat->cus : 256;
+    const uint64_t t3 = tile_count<3, 4, 4, 4>(g), t2 = tile_count<2, 8, 4, 2>(g);
+    if (n >= 3 && t3 <= (f64 ? cus : 2 * cus)) return 3;
+    return t2 <= 2 * cus ? 2 : 0;
+}
+
+int launch_tile(cmlbm_lattice* lat, int k, hipStream_t s)
+{
+    if (lat->p.storage == CMLBM_FP64)
+        k == 3 ? launch_tile_t<double, 3, 4, 4, 4>(lat, s) : launch_tile_t<double, 2, 8, 4, 2>(lat, s);
+    else
+        k == 3 ? launch_tile_t<float, 3, 4, 4, 4>(lat, s) : launch_tile_t<float, 2, 8, 4, 2>(lat, s);
+    return launch_check(lat, "step");
+}
+
 // Whether a call of n steps goes through the nine numbers: where its first,
 // inner and last steps are estimated to take less than n steps of k_step.
 // k_step moves 54 numbers per cell at about 5.4 TB/s, a lane without a cell
@@ -2569,14 +2720,17 @@ int cmlbm_step(cmlbm_lattice* lat, int32_t nsteps, void* hip_stream)
     if (!lat->initialized) return fail(lat, CMLBM_ESTATE, "step before init");
     hipStream_t s = (hipStream_t)hip_stream;
     const bool march = marches(lat, nsteps);
-    for (int32_t k = 0; k < nsteps; ++k) {
-        int rc = !march             ? launch_step(lat, s)
+    for (int32_t k = 0; k < nsteps;) {
+        const int many = march ? 0 : tile_steps(lat, nsteps - k);
+        int rc = many               ? launch_tile(lat, many, s)
+                 : !march           ? launch_step(lat, s)
                  : k == 0           ? launch_to_moments(lat, s)
                  : lat->p.storage == CMLBM_FP64 ? launch_march<double>(lat, s, k == nsteps - 1)
                                                 : launch_march<float>(lat, s, k == nsteps - 1);
         if (rc) return rc;
         lat->cur = 1 - lat->cur;
-        lat->t += 1;
+        lat->t += many ? many : 1;
+        k += many ? many : 1;
     }
     return CMLBM_OK;
 }
