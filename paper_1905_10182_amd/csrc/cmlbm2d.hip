@@ -265,13 +265,23 @@ __global__ __launch_bounds__(kBlock) void k2_step(const typename storage2<ST>::S
 // last stage's row is reconstructed and stored.  The x shift is a DPP rotation
 // of the wave; the y shift stays in a lane's registers: of a row, class
 // c_y = -1 goes to the row below, 0 to the row itself, +1 to the row above, as
-// three row sums each.  No LDS and no barrier: waves are independent.
-// (Per step at 8192^2 with a force field: FP32 890 -> 327 us, 205 G cells/s;
-// FP64 1873 -> 609 us, 110 G cells/s.)
-// A strip loses one cell at each end per stage, so strips overlap by 2 K cells
-// (none where a strip is exactly a periodic row), and a chunk of rows starts
-// and ends K rows outside.  What bounds it is the issue of vector
-// instructions: 72 bytes per cell (FP32) for K steps instead of for each.
+// three row sums each.  No barrier: waves are independent.
+// The stages are kept apart in the schedule: left to itself the compiler moves
+// parts of later stages up until the registers are full (K = 6 with a field:
+// 256 and spills instead of 195; K = 4 on 3001 x 3000 358 -> 283 us).
+// A strip loses one cell at each end per stage, so strips overlap by 2 H >= 2 K
+// cells (none where a strip is exactly a periodic row), and a chunk of rows
+// starts and ends K rows outside.
+// What bounds it: K = 2 HBM, 72 bytes per cell (FP32) and 8 with a field, at 5.1
+// TB/s; K = 8 the issue of vector instructions, about 133 per cell and step, 95%
+// of the time.  Per step at 8192^2 with a force field: FP32 k2_step 890, K = 2 524,
+// 4 320, 6 299, 8 270 us; FP64 1870, 1100, 592, 518, 489.
+// H: for K = 2, 8 cells make strips of whole 64-byte pieces, where 2 leave each
+// end in pieces that two waves write (FP32 8192^2 1260 -> 1050 us a pass);
+// longer passes lose more to the overlap than that gains (K = 4 on 2048^2 97 /
+// 101 us, FP64 on 4096^2 592 / 650).
+constexpr int march_halo(int K) { return K == 2 ? 8 : K; }
+
 template <typename X>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const X* base, uint32_t bytes)
 {
@@ -279,7 +289,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const X* base, uint32_
 }
 
 template <int ST, int V, int K, bool FIELD>
-__global__ __launch_bounds__(kBlock) void k2_march(const typename storage2<ST>::S* __restrict__ src,
+__global__ __launch_bounds__(kBlock, K >= 6 ? 2 : 1) void k2_march(const typename storage2<ST>::S* __restrict__ src,
                                                    typename storage2<ST>::S* __restrict__ dst, Geom2 g, int strips,
                                                    int rows, typename storage2<ST>::T omega,
                                                    typename storage2<ST>::T rho0, typename storage2<ST>::T fx,
@@ -288,7 +298,8 @@ __global__ __launch_bounds__(kBlock) void k2_march(const typename storage2<ST>::
 {
     using T = typename storage2<ST>::T;
     static_assert(std::is_same<T, typename storage2<ST>::S>::value, "FP64 and FP32 storage");
-    static_assert(K % V == 0 && V * sizeof(T) <= 8, "a lane's cells are one vector of 4 or 8 bytes");
+    constexpr int H = march_halo(K);
+    static_assert(H >= K && H % V == 0 && V * sizeof(T) <= 8, "a lane's cells are one vector of 4 or 8 bytes");
     typedef uint32_t u2 __attribute__((ext_vector_type(2)));
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)));
@@ -298,10 +309,10 @@ __global__ __launch_bounds__(kBlock) void k2_march(const typename storage2<ST>::
     // cells of this lane: position i0 in the strip, x (periodic); stored are the
     // positions [K, 64 V - K) of an overlapping strip that lie in the row
     const bool ring = g.nx == 64 * V;
-    const int stride = ring ? 64 * V : 64 * V - 2 * K, i0 = lane * V;
-    const int xr = strip * stride + i0 - (ring ? 0 : K);
+    const int stride = ring ? 64 * V : 64 * V - 2 * H, i0 = lane * V;
+    const int xr = strip * stride + i0 - (ring ? 0 : H);
     const int x = ((xr % g.nx) + g.nx) % g.nx;
-    const bool stored = ring || (i0 >= K && i0 < 64 * V - K && xr < g.nx);
+    const bool stored = ring || (i0 >= H && i0 < 64 * V - H && xr < g.nx);
     constexpr uint32_t kNone = 0xffffff00u;  // past every range: the store is dropped
     const uint32_t rowb = (uint32_t)g.nxp * (uint32_t)sizeof(T), off = (uint32_t)x * (uint32_t)sizeof(T);
     const uint32_t fieldb = (uint32_t)g.nx * (uint32_t)sizeof(T);
@@ -320,11 +331,23 @@ __global__ __launch_bounds__(kBlock) void k2_march(const typename storage2<ST>::
         }
     };
 
-    T nh[9][V];  // populations of the next source row
-    auto load_row = [&](int r) {
+    // Forces of the K rows that the stages work on: each is loaded once and kept
+    // in the wave's own ring of LDS rows until the last stage has used it.
+    typedef T tv __attribute__((ext_vector_type(V == 1 ? 2 : V)));
+    using FV = std::conditional_t<V == 1, T, tv>;
+    __shared__ FV ring_f[FIELD ? kBlock / 64 : 1][FIELD ? K : 1][2][64];
+    FV(*const my_f)[2][64] = ring_f[FIELD ? threadIdx.x >> 6 : 0];
+    int slot = 0;  // of the row that stage 1 works on
+
+    T nh[9][V], nf[2][V];  // populations of the next source row, force of the current one
+    auto load_row = [&](int r, int fr) {
         const T* p = src + (uint64_t)r * g.rstride;
 #pragma unroll
         for (int i = 0; i < 9; ++i) ld(p + (uint64_t)i * g.pstride, rowb, nh[i]);
+        if (FIELD) {
+            ld(field + (uint64_t)fr * g.nx, fieldb, nf[0]);
+            ld(field + g.ncell + (uint64_t)fr * g.nx, fieldb, nf[1]);
+        }
     };
     T Z[K][V][3], P[K][2][V][3];  // row sums of c_y = 0 (last row) and +1 (last two rows) of each stage
 #pragma unroll
@@ -339,32 +362,32 @@ __global__ __launch_bounds__(kBlock) void k2_march(const typename storage2<ST>::
     y[0] = (((ys - K) % g.ny) + g.ny) % g.ny;
 #pragma unroll
     for (int k = 1; k <= K; ++k) y[k] = y[k - 1] == 0 ? g.ny - 1 : y[k - 1] - 1;
-    load_row(y[0]);
+    load_row(y[0], y[1]);
 #pragma unroll
-    for (int i = 0; i < 9; ++i)
+    for (int c = 0; c < V; ++c) {  // arrived: not counted in the loop
 #pragma unroll
-        for (int c = 0; c < V; ++c) asm volatile("" : "+v"(nh[i][c]));  // arrived: not counted in the loop
+        for (int i = 0; i < 9; ++i) asm volatile("" : "+v"(nh[i][c]));
+        if (FIELD) asm volatile("" : "+v"(nf[0][c]), "+v"(nf[1][c]));
+    }
     auto advance = [&](int r, auto parity) {
         constexpr int q = decltype(parity)::value;
-        T h[V][9], Fx[V], Fy[V], F[K][2][V];
+        T h[V][9], Fx[V], Fy[V];
 #pragma unroll
         for (int i = 0; i < 9; ++i)
 #pragma unroll
             for (int c = 0; c < V; ++c) h[c][i] = nh[i][c];
+        if constexpr (FIELD) {
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            if (FIELD) {
-                ld(field + (uint64_t)y[k + 1] * g.nx, fieldb, F[k][0]);
-                ld(field + g.ncell + (uint64_t)y[k + 1] * g.nx, fieldb, F[k][1]);
-            } else {
-#pragma unroll
-                for (int c = 0; c < V; ++c) {
-                    F[k][0][c] = fx;
-                    F[k][1][c] = fy;
-                }
+            for (int a = 0; a < 2; ++a) {
+                FV w;
+                if constexpr (V == 1)
+                    w = nf[a][0];
+                else
+                    for (int c = 0; c < V; ++c) w[c] = nf[a][c];
+                my_f[slot][a][lane] = w;
             }
         }
-        load_row(y[0] + 1 == g.ny ? 0 : y[0] + 1);
+        load_row(y[0] + 1 == g.ny ? 0 : y[0] + 1, y[0]);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             T X[V][3][3];  // row sums of this row, by c_y class
@@ -379,8 +402,19 @@ __global__ __launch_bounds__(kBlock) void k2_march(const typename storage2<ST>::
             }
 #pragma unroll
             for (int c = 0; c < V; ++c) {
-                Fx[c] = F[k][0][c];
-                Fy[c] = F[k][1][c];
+                Fx[c] = fx;
+                Fy[c] = fy;
+                if constexpr (FIELD) {
+                    const FV w0 = my_f[slot >= k ? slot - k : slot - k + K][0][lane];
+                    const FV w1 = my_f[slot >= k ? slot - k : slot - k + K][1][lane];
+                    if constexpr (V == 1) {
+                        Fx[c] = w0;
+                        Fy[c] = w1;
+                    } else {
+                        Fx[c] = w0[c];
+                        Fy[c] = w1[c];
+                    }
+                }
                 T drho, ux, uy, k4, k5;
                 lockstep::moments_of_sums<T>(X[c][0], Z[k][c], P[k][q][c], Fx[c], Fy[c], rho0, drho, ux, uy, k4, k5);
 #pragma unroll
@@ -391,6 +425,7 @@ __global__ __launch_bounds__(kBlock) void k2_march(const typename storage2<ST>::
                 const T s4 = om1 * k4, s5 = om1 * k5;
                 lockstep::reconstruct<T>(drho, ux, uy, Fx[c], Fy[c], s4, s5, rho0, h[c]);
             }
+            __builtin_amdgcn_sched_barrier(0);
         }
         const int yt = r - K;  // the row just finished, K steps on
         T* out = dst + (uint64_t)y[K] * g.rstride;
@@ -413,6 +448,7 @@ __global__ __launch_bounds__(kBlock) void k2_march(const typename storage2<ST>::
         }
 #pragma unroll
         for (int k = 0; k <= K; ++k) y[k] = y[k] + 1 == g.ny ? 0 : y[k] + 1;
+        slot = slot + 1 == K ? 0 : slot + 1;
     };
     int r = ys - K;
     const int end = ye + K;  // one past the last source row
@@ -693,10 +729,14 @@ int launch_check(cmlbm2d_lattice* lat, const char* what)
 
 dim3 cell_grid(const Geom2& g) { return dim3((unsigned)((g.ncell + kBlock - 1) / kBlock)); }
 
-int march_strips(const Geom2& g, int V, int K)
+// Strips of k2_march (and k2_tile: V = 1) across a row, with H cells of halo at each end.
+int march_strips(const Geom2& g, int V, int H)
 {
-    return g.nx == 64 * V ? 1 : (g.nx + 64 * V - 2 * K - 1) / (64 * V - 2 * K);
+    return g.nx == 64 * V ? 1 : (g.nx + 64 * V - 2 * H - 1) / (64 * V - 2 * H);
 }
+
+// Waves that a SIMD holds of k2_march, by its registers (K = 4 about 150, 6 and 8 about 200 to 250).
+constexpr int march_waves(int K) { return K >= 6 ? 2 : K == 4 ? 3 : 4; }
 
 // Rows per wave of k2_march, and the waves that a SIMD then runs: the least of
 // that number (a SIMD is bound by their instructions) times the rows of each
@@ -705,7 +745,7 @@ int march_rows2(const Geom2& g, int strips, int K, int* waves_per_simd)
 {
     int best = g.ny, best_w = (strips + 1023) / 1024;
     uint64_t best_cost = (uint64_t)best_w * (uint64_t)(g.ny + 2 * K);
-    for (int w = 1; w <= 4; ++w) {
+    for (int w = 1; w <= march_waves(K); ++w) {
         const int n = std::min(g.ny, 1024 * w / strips);
         if (n < 1) continue;
         const int rows = (g.ny + n - 1) / n;
@@ -764,7 +804,7 @@ void launch_march_k(cmlbm2d_lattice* lat, hipStream_t s)
 {
     using T = typename storage2<ST>::T;
     const Geom2& g = lat->g;
-    const int strips = march_strips(g, V, K), rows = march_rows2(g, strips, K, nullptr);
+    const int strips = march_strips(g, V, march_halo(K)), rows = march_rows2(g, strips, K, nullptr);
     const uint64_t waves = (uint64_t)strips * (uint64_t)((g.ny + rows - 1) / rows);
     const dim3 grid((unsigned)((waves + kBlock / 64 - 1) / (kBlock / 64)));
     const T* src = (const T*)lat->pop[lat->cur];
@@ -776,6 +816,16 @@ void launch_march_k(cmlbm2d_lattice* lat, hipStream_t s)
     else
         k2_march<ST, V, K, false><<<grid, dim3(kBlock), 0, s>>>(src, dst, g, strips, rows, om, r0, (T)lat->fu[0],
                                                                 (T)lat->fu[1], nullptr);
+}
+
+template <int ST, int V>
+void launch_march_v(cmlbm2d_lattice* lat, int K, hipStream_t s)
+{
+    if constexpr (ST == CMLBM2D_FP64 || V == 2) {
+        if (K == 8) return launch_march_k<ST, V, 8>(lat, s);
+    }
+    if (K == 6) return launch_march_k<ST, V, 6>(lat, s);
+    K == 4 ? launch_march_k<ST, V, 4>(lat, s) : launch_march_k<ST, V, 2>(lat, s);
 }
 
 template <int ST>
@@ -800,47 +850,69 @@ void launch_tile(cmlbm2d_lattice* lat, int K, hipStream_t s)
 struct Pass {
     enum Kind { STEP, MARCH, TILE } kind;
     int steps, V;
+    double t;  // estimated us
 };
 
-// The pass with the least time per step, by estimates of each kernel's launch
-// in us (measured, FP64 / FP32; the four-rolls mill on n x n cells):
+// The first of the launches that take n steps in the least time, by estimates
+// of each kernel's launch in us (measured, FP64 / FP32; the four-rolls mill on
+// n x n cells):
 //   k2_step   3.0 + 160 (80) bytes per cell at 5.6 TB/s;
-//   k2_march  2.5 + waves per SIMD x (rows + 2 K) x 1.9 / 2.35 (FP32 one cell a lane 1.5);
-//             K = 2: x 2.3 / 2.4 (HBM-bound);
+//   k2_march  2.5 + waves per SIMD x (rows + 2 K) x the time of a row: K = 2
+//             1.45 / 1.65 (HBM-bound), 4 1.75 / 2.15, 6 2.15 / 2.95, 8 2.6 / 3.8
+//             (3.4 with two waves); FP32 with one cell a lane 0.97, 1.26, 1.69
+//             and, no better than 6, 2.19;
 //   k2_tile   with x = workgroups / 256: up to 1, 4.6 + 0.59 K + 3.7 x / 3.6 +
 //             0.53 K + 3.7 x; beyond, 3.5 + 7.5 x / 3.5 + 3.9 x.
+// The best rate decides while many steps are left, the best way to end exactly
+// (6 + 4 for ten steps where 8 + 2 has the better start) over the last sixteen.
 // us per step, k2_step / chosen: FP64 16^2 3.06 / 1.23 (tile), 64^2 3.18 / 1.25
-// (tile), 256^2 4.9 / 2.3 (tile), 500^2 9.3 / 5.8, 1024^2 30.9 / 13.8 (march),
-// 8192^2 1873 / 609 (march); FP32 64^2 3.4 / 1.04, 300^2 4.2 / 1.9, 1024^2 16.8 /
-// 10.1, 4096^2 223 / 94 (march), 8192^2 890 / 327 (march).
+// (tile), 256^2 4.9 / 2.3 (tile), 500^2 9.3 / 5.8, 1024^2 30.9 / 11.8 (march),
+// 4096^2 495 / 127, 8192^2 1873 / 489; FP32 64^2 3.4 / 1.04, 300^2 4.2 / 1.9, 1024^2
+// 16.8 / 10.1, 4096^2 223 / 78 (march), 8192^2 890 / 270.
 Pass next_pass(const cmlbm2d_lattice* lat, int n)
 {
+    constexpr int kMost = 8, kLast = 16;
     const Geom2& g = lat->g;
-    Pass best{Pass::STEP, 1, g.V};
-    if ((lat->p.storage != CMLBM2D_FP64 && lat->p.storage != CMLBM2D_FP32) || n < 2) return best;
     const bool f64 = lat->p.storage == CMLBM2D_FP64;
-    double best_t = 3.0 + (double)g.ncell * (f64 ? 160.0 : 80.0) / 5.6e6;
-    auto consider = [&](Pass::Kind kind, int steps, int V, double t) {
-        if (t < best_t * steps) {
-            best_t = t / steps;
-            best = Pass{kind, steps, V};
-        }
+    Pass of[kMost + 1];  // the fastest launch of k steps
+    of[1] = Pass{Pass::STEP, 1, g.V, 3.0 + (double)g.ncell * (f64 ? 160.0 : 80.0) / 5.6e6};
+    if ((!f64 && lat->p.storage != CMLBM2D_FP32) || n < 2) return of[1];
+    for (int K = 2; K <= kMost; ++K) of[K] = Pass{Pass::STEP, 0, 1, 1e300};
+    auto consider = [&](Pass::Kind kind, int K, int V, double t) {
+        if (t < of[K].t) of[K] = Pass{kind, K, V, t};
     };
     const int V = f64 || g.nx % 2 ? 1 : 2;
-    for (int K = 2; K <= 4 && K <= n; K += 2) {
+    for (int K = 2; K <= (f64 || V == 2 ? 8 : 6); K += 2) {
         int w = 1;
-        const int rows = march_rows2(g, march_strips(g, V, K), K, &w);
-        const double per_row = K == 2 ? (f64 ? 2.3 : 2.4) : f64 ? 1.9 : V == 2 ? 2.35 : 1.5;
+        const int rows = march_rows2(g, march_strips(g, V, march_halo(K)), K, &w);
+        const double per_row = f64      ? (K == 2 ? 1.45 : K == 4 ? 1.75 : K == 6 ? 2.15 : 2.6)
+                               : V == 1 ? (K == 2 ? 0.97 : K == 4 ? 1.26 : 1.69)
+                                        : (K == 2 ? 1.65 : K == 4 ? 2.15 : K == 6 ? 2.95 : w > 1 ? 3.4 : 3.8);
         consider(Pass::MARCH, K, V, 2.5 + w * (double)(rows + 2 * K) * per_row);
     }
-    for (int K = 2; K <= 7 && K <= n; ++K) {
+    for (int K = 2; K <= 7; ++K) {
         const int R = kTileRows - 2 * K;
         const double x = (double)march_strips(g, 1, K) * ((g.ny + R - 1) / R) / 256.0;
         if (x > 8192) break;  // far beyond its range, and near a launch's work-items
         const double t = x > 1.0 ? 3.5 + (f64 ? 7.5 : 3.9) * x : (f64 ? 4.6 + 0.59 * K : 3.6 + 0.53 * K) + 3.7 * x;
         consider(Pass::TILE, K, 1, t);
     }
-    return best;
+    int first = 1;
+    if (n > kLast) {
+        for (int K = 2; K <= kMost; ++K)
+            if (of[K].t * first < of[first].t * K) first = K;
+        return of[first];
+    }
+    double least[kLast + 1] = {0.0};
+    for (int m = 1; m <= n; ++m) {
+        least[m] = 1e300;
+        for (int K = 1; K <= kMost && K <= m; ++K)
+            if (of[K].t + least[m - K] < least[m]) {
+                least[m] = of[K].t + least[m - K];
+                first = K;
+            }
+    }
+    return of[first];
 }
 
 template <int ST>
@@ -848,9 +920,9 @@ void launch_pass_st(cmlbm2d_lattice* lat, const Pass& p, hipStream_t s)
 {
     if (p.kind == Pass::TILE) return launch_tile<ST>(lat, p.steps, s);
     if constexpr (ST == CMLBM2D_FP32) {
-        if (p.V == 2) return p.steps == 4 ? launch_march_k<ST, 2, 4>(lat, s) : launch_march_k<ST, 2, 2>(lat, s);
+        if (p.V == 2) return launch_march_v<ST, 2>(lat, p.steps, s);
     }
-    p.steps == 4 ? launch_march_k<ST, 1, 4>(lat, s) : launch_march_k<ST, 1, 2>(lat, s);
+    launch_march_v<ST, 1>(lat, p.steps, s);
 }
 
 void launch_pass(cmlbm2d_lattice* lat, const Pass& p, hipStream_t s)
