@@ -400,14 +400,25 @@ __global__ __launch_bounds__(256) void k_conv_tile(G g, const bf16* __restrict__
 // own: built from the centre one by lane shifts they cost as much issue time as
 // the MFMAs (75 us instead of 66).  Each output adds its products in the order
 // of the brick kernel: same bits.
-// 16 x 32 x 32 x 64, 32 -> 32: 91 -> 66 us forward, 81 -> 59 us data gradient
-// (983 TFLOP/s); 96 -> 32: 220 -> 170 and (32 -> 96) 182 -> 155; 160 -> 64 at
-// half extents: 92 -> 77 and 134 -> 85.
+// What waits on memory at the start of a workgroup is issued together: the gates
+// and the first row's weights with the halo (forward 65 -> 60 us; all nine
+// weights early, or the gates kept with them, run out of registers: 87 us).
+// 16 x 32 x 32 x 64, 32 -> 32: 91 -> 60 us forward, 81 -> 56 us data gradient
+// (1037 TFLOP/s); 96 -> 32: 220 -> 168 and (32 -> 96) 182 -> 153; 160 -> 64 at
+// half extents: 92 -> 75 and 134 -> 84.
 constexpr int kRH = 8, kRHH = kRH + 2, kRRows = kHD * kRHH;  // 60 halo rows of 18 voxels
 constexpr uint32_t kRRow = kHW * 64;                          // bytes of a halo row
 constexpr int kRParts = kHW * 4;                              // 16-byte parts of a halo row: 72
 constexpr int kRIters = kRRows / 3;                           // three rows are staged at a time, by 216 threads
 constexpr uint32_t kNone = 0xffffff00u;                       // past every buffer range: loads give 0
+
+// f > 0 ? f : kLeak f, as the larger of the two (0 < kLeak < 1)
+__device__ __forceinline__ float leaky(float f)
+{
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(f), "v"(kLeak * f));
+    return r;
+}
 
 template <int SIGN, int ACT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_conv_rows(
@@ -468,6 +479,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int i = 0; i < 4; ++i) bb[b][i] = bias[co + 16 * b + i];
     }
+    // D[row][col]: row = output channel (lane / 16) * 4 + i, col = voxel lane % 16;
+    // a lane offset and a wave-uniform offset within the sample.  The gates are
+    // read ahead of the products.
+    const uint32_t sample_y = (uint32_t)g.d * (uint32_t)g.h * (uint32_t)g.w * (uint32_t)cout * 2u;
+    const __amdgpu_buffer_rsrc_t yr = buf_rsrc(y + n * (long long)(sample_y / 2u), sample_y);
+    const __amdgpu_buffer_rsrc_t gr = buf_rsrc(gate + n * (long long)(sample_y / 2u), sample_y);
+    const uint32_t ylane = ((uint32_t)(lane & 15) * (uint32_t)cout + (uint32_t)co) * 2u;
+    auto yrow = [&](int m) { return (uint32_t)(((d0 + wv) * g.h + h0 + m) * g.w + x0) * (uint32_t)cout * 2u; };
+    u2 gt[kRH][2];
+    if (SIGN < 0 && ACT == CMNN_ACT_LEAKY) {
+#pragma unroll
+        for (int m = 0; m < kRH; ++m)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) gt[m][b] = __builtin_amdgcn_raw_buffer_load_b64(gr, ylane, yrow(m) + 32u * b, 0);
+    }
     f4 acc[kRH][2];
 #pragma unroll
     for (int m = 0; m < kRH; ++m) acc[m][0] = acc[m][1] = f4{0.f, 0.f, 0.f, 0.f};
@@ -486,12 +512,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const uint32_t row = row_off[(it * 3 + trow) % kRRows];
             stage[it] = __builtin_bit_cast(u4, ldb8(xr, __builtin_elementwise_add_sat(row, col_off), (uint32_t)c0 * 2u));
         }
-        __syncthreads();
-        if (trow < 3) {
-#pragma unroll
-            for (int it = 0; it < kRIters; ++it) *(u4*)(put + it * 3 * kRRow) = stage[it];
-        }
-        __syncthreads();
         // weight fragments of (depth tap tz, row tap ty): reloaded in place for
         // tz + 1 as soon as the last row that needs them is done, so that a
         // row or two of MFMAs covers the load.  The order is pinned per row:
@@ -504,8 +524,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 for (int b = 0; b < 2; ++b)
                     bw[ty * 3 + j][b] = ldb8(wr, wlane, (((uint32_t)(tz * 9 + ty * 3 + j) * (uint32_t)cout + 16u * b) * (uint32_t)cin + (uint32_t)c0) * 2u);
         };
+        wload(0, 0);  // the first row's, behind the halo's loads
+        __syncthreads();
+        if (trow < 3) {
 #pragma unroll
-        for (int ty = 0; ty < 3; ++ty) wload(0, ty);
+            for (int it = 0; it < kRIters; ++it) *(u4*)(put + it * 3 * kRRow) = stage[it];
+        }
+        __syncthreads();
+        wload(0, 1);
+        wload(0, 2);
         bf16x8 af[2][3];
         auto row_load = [&](int s30) {  // row s30 % 10 of depth tap s30 / 10
             const int dz = SIGN * (s30 / kRHH - 1), r = SIGN > 0 ? s30 % kRHH : kRHH - 1 - s30 % kRHH;
@@ -535,20 +562,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    // D[row][col]: row = output channel (lane / 16) * 4 + i, col = voxel lane % 16;
-    // a lane offset and a wave-uniform offset within the sample
-    const uint32_t sample_y = (uint32_t)g.d * (uint32_t)g.h * (uint32_t)g.w * (uint32_t)cout * 2u;
-    const __amdgpu_buffer_rsrc_t yr = buf_rsrc(y + n * (long long)(sample_y / 2u), sample_y);
-    const __amdgpu_buffer_rsrc_t gr = buf_rsrc(gate + n * (long long)(sample_y / 2u), sample_y);
-    const uint32_t ylane = ((uint32_t)(lane & 15) * (uint32_t)cout + (uint32_t)co) * 2u;
 #pragma unroll
     for (int m = 0; m < kRH; ++m) {
-        const uint32_t yrow = (uint32_t)(((d0 + wv) * g.h + h0 + m) * g.w + x0) * (uint32_t)cout * 2u;
-        u2 gt[2];
-        if (SIGN < 0 && ACT == CMNN_ACT_LEAKY) {
-#pragma unroll
-            for (int b = 0; b < 2; ++b) gt[b] = __builtin_amdgcn_raw_buffer_load_b64(gr, ylane, yrow + 32u * b, 0);
-        }
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
             bf16x4 o;
@@ -557,13 +572,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 float f = acc[m][b][i];
                 if (SIGN > 0) {
                     f += bb[b][i];
-                    if (ACT == CMNN_ACT_LEAKY) f = f > 0.f ? f : kLeak * f;
+                    if (ACT == CMNN_ACT_LEAKY) f = leaky(f);
                 } else if (ACT == CMNN_ACT_LEAKY) {
-                    if ((float)__builtin_bit_cast(bf16x4, gt[b])[i] <= 0.f) f *= kLeak;
+                    if ((float)__builtin_bit_cast(bf16x4, gt[m][b])[i] <= 0.f) f *= kLeak;
                 }
                 o[i] = (bf16)f;
             }
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, o), yr, ylane, yrow + 32u * b, 0);
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, o), yr, ylane, yrow(m) + 32u * b, 0);
         }
     }
 }
