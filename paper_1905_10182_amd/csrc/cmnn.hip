@@ -648,243 +648,282 @@ __global__ __launch_bounds__(256) void k_conv_bwd_w(G g, const bf16* __restrict_
 // brick-tiled weight gradient (extents multiples of the 4 x 4 x 16 brick)
 //
 // Workgroup (chunk of bricks, 32 output channels, 32 input channels), all 27
-// taps, 8 waves.  The MFMA K axis is the voxel axis, so a fragment is 8
-// consecutive voxels of one channel: per brick, dy ([co][256 voxels]) and the
-// 6 x 6 x 18 halo of x ([ci][36 halo rows][24], positions x0 - 1 .. x0 + 16)
-// are staged in LDS channel-major.  A staging task is an 8 x 8 (voxel x
-// channel) block: eight 16-byte global loads, a register transpose, eight
-// 16-byte LDS stores.  The next brick's loads are issued before the current
-// brick's MFMAs so that their latency hides behind the compute.  A tap's x
-// fragment starts dx + 1 elements into an aligned 16-byte LDS read: for
-// dx = 0 and +1 the eight elements are realigned from that read and the next
-// dword, and the three x taps of one (dz, dy) share that read.  Row strides
-// are padded so that the 16 rows of a fragment read fall on distinct bank
-// groups.  Two LDS buffers alternate: a wave stores brick br + 1 as soon as
-// its MFMAs on brick br are done, so the stores of one wave overlap the MFMAs
-// of another, with one barrier per brick.  The work units are the 18 pairs
-// (tap group (dz, dy), 16-channel ci block); wave w takes units w, w + 8 and
-// w + 16 and accumulates, for each, the three x taps times two 16-channel co
-// blocks.  The dy fragments of a K step are read once and serve all of them.
+// taps, 12 waves (three per SIMD).  The MFMA K axis is the voxel axis: a
+// fragment is 8 consecutive voxels of one channel.  Per brick, dy (256 voxels)
+// and the 6 x 6 x 18 halo of x are staged in LDS as they lie in memory, voxel by
+// voxel, 16 channels (32 bytes) apart in two halves, and the fragments are read
+// by the transposing LDS read (four voxels of 16 channels per 16 lanes: 128
+// consecutive bytes, at any x shift).  A wave owns a depth
+// tap, a 16-channel half of x and two of the brick's depth slices (K = the two
+// slices' rows), and walks down the six halo rows: each is read once, its
+// three x taps are byte shifts of the 12 voxels read, and it meets the up to
+// three dy rows it is a neighbour of, 18 MFMAs.  The two waves that share taps
+// add up through LDS at the end.  The bias gradient is summed from
+// the dy fragments of two of the waves.
+// What bounds it: the matrix cores run 52% of the time; the rest is LDS reads (17
+// KB a wave and brick, half of the MFMAs' time) and the one barrier a brick.  Two
+// buffers alternate and the next brick's loads are in flight meanwhile.
+// Against staging channel-major (an 8 x 8 register transpose per task, 16-byte
+// LDS stores with bank conflicts, eight waves with 3, 3, 2, .. units each), with
+// the chunk sums: 16 x 32 x 32 x 64, 32 x 32 channels 78 -> 64 us, 96 x 32 215 -> 171 us
+// (1015 TFLOP/s), 160 x 64 at half extents 103 -> 84 us.
 
-constexpr int kDyStride = 256 + 8;        // bf16 per co row of staged dy
-constexpr int kSkew = 8;                  // bf16 shift of each group of 8 channel rows (one 16-byte slot)
-constexpr int kXRow = 24;                 // bf16 per staged halo row (18 used)
-constexpr int kXStride = 36 * kXRow + 8;  // bf16 per ci row of staged x
-constexpr int kXTasks = 36 * 3 * 4;       // (halo row, octet, channel group) blocks of x
-constexpr int kDyTasks = 32 * 4;          // (x octet, channel group) blocks of dy
-constexpr int kBwThreads = 512;
+constexpr int kBwThreads = 768;
+// Voxels 8 and up of a row lie four slots further on: the two octets of a row
+// that 32 lanes read at a time then fall on different banks.
+constexpr uint32_t kBwXRow = 22 * 32, kBwYRow = 20 * 32;          // bytes of a row: 18 and 16 voxels
+constexpr uint32_t kBwXHalf = kHD * kHH * kBwXRow + 64;           // halves 64 bytes out of step with the banks;
+constexpr uint32_t kBwYHalf = kTD * kTH * kBwYRow + 64;           // (also the two voxels read past the last row)
+constexpr uint32_t kBwBuf = 2 * kBwXHalf + 2 * kBwYHalf;
+constexpr int kBwRows = kHD * kHH;                                // halo rows: 36
+constexpr int kBwStep = kBwThreads / (kHW * 4);                   // halo rows staged at a time: 10
 
-__device__ __forceinline__ void transpose8x8(const u4 (&in)[8], u4 (&out)[8])
-{
-    // in[i] holds channels 0..7 of voxel i (bf16 pairs per dword); out[c] holds voxels 0..7 of channel c
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        const int k = c >> 1, hi = c & 1;
-        unsigned o[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const unsigned a = in[2 * j][k], b = in[2 * j + 1][k];
-            // one byte permute: (a >> 16) | (b & 0xffff0000) or (a & 0xffff) | (b << 16)
-            o[j] = __builtin_amdgcn_perm(b, a, hi ? 0x07060302u : 0x05040100u);
-        }
-        out[c] = u4{o[0], o[1], o[2], o[3]};
-    }
-}
-
-__global__ __launch_bounds__(kBwThreads) void k_conv_bwd_w_tile(G g, const bf16* __restrict__ x, int cin,
+__global__ __launch_bounds__(kBwThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_conv_bwd_w_tile(G g, const bf16* __restrict__ x, int cin,
                                                                 const bf16* __restrict__ dy, int cout,
                                                                 int bricks_per_chunk, float* __restrict__ part,
                                                                 long long pstride, bool bias)
 {
-    __shared__ __attribute__((aligned(16))) bf16 sdy2[2][32 * kDyStride + 3 * kSkew];
-    __shared__ __attribute__((aligned(16))) bf16 sx2[2][32 * kXStride + 3 * kSkew];
-    __shared__ float sbias[kBwThreads];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    typedef short s4 __attribute__((ext_vector_type(4)));
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    typedef __attribute__((address_space(3))) s4 lds_s4;
+    __shared__ __attribute__((aligned(128))) char lds[2 * kBwBuf];
+    __shared__ uint32_t row_off[2][kBwRows];
+    static_assert((6 * 18 + 2) * 64 * sizeof(f4) <= sizeof(lds), "the sums of half the waves");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ct = cout / 32, it = cin / 32;
     int bid = blockIdx.x;
     const int cit = bid % it;
     bid /= it;
     const int cot = bid % ct;
     const int ch = bid / ct;
-    // bias gradient (column sums of dy) from the staged dy, by the ci-tile-0 workgroups:
-    // thread (co = tid / 16, segment tid % 16) sums 16 voxels of each brick
-    const bool do_bias = bias && cit == 0;
-    float bsum = 0.f;
     const int nbw = g.w / kTW, nbh = g.h / kTH, nbd = g.d / kTD;
     const long long nbricks = (long long)g.n * nbd * nbh * nbw;
     const long long b0 = (long long)ch * bricks_per_chunk;
     const long long b1 = b0 + bricks_per_chunk < nbricks ? b0 + bricks_per_chunk : nbricks;
-    // staging roles: x block tid (tid < 432), dy block tid - 384 (tid >= 384)
-    const bool has_x = tid < kXTasks, has_dy = tid >= kBwThreads - kDyTasks;
-    const int xcg = tid & 3, xoct = (tid >> 2) % 3, xhr = tid / 12;
-    const int dyt = tid - (kBwThreads - kDyTasks), dcg = dyt & 3, drow = (dyt >> 2) >> 1, dxo = ((dyt >> 2) & 1) * 8;
-    u4 xin[8], dyin[8];
-    // coordinates of the next brick to load (bricks are loaded in order b0, b0 + 1, ...),
-    // advanced brick by brick without divisions
-    int lx0, lh0, ld0, ln;
+    // Staging: five 16-byte parts per thread, four consecutive threads a voxel.
+    // Rounds 0 to 3 are ten halo rows each (round 3: the last six), the waves
+    // from 7 on in round 3 and the first eleven in round 4 take dy.  The halo rows' sources
+    // (byte offset within the sample, kNone where it is padding) are found once
+    // per brick, by one wave, a brick ahead of their use.
+    const int trow = tid / (kHW * 4), hx = tid % (kHW * 4) >> 2, tp = tid & 3;
+    const bool all4 = trow < kBwStep, r3x = trow < kBwRows - 3 * kBwStep, r3y = wave >= 7, r4 = wave < 11;
+    auto slot = [](int v) { return (uint32_t)(v + (v >= 8 ? 4 : 0)) * 32u; };
+    const uint32_t put_x = (uint32_t)(tp >> 1) * kBwXHalf + (uint32_t)trow * kBwXRow + slot(hx) + (uint32_t)(tp & 1) * 16u;
+    const int yv3 = r3y ? (tid - 448) >> 2 : 0, yv4 = r4 ? 80 + (tid >> 2) : 0;  // dy voxels of rounds 3 and 4
+    auto put_y = [&](int v) {
+        return 2 * kBwXHalf + (uint32_t)(tp >> 1) * kBwYHalf + (uint32_t)(v >> 4) * kBwYRow + slot(v & 15) + (uint32_t)(tp & 1) * 16u;
+    };
+    const uint32_t put3 = r3y ? put_y(yv3) : put_x + 3 * kBwStep * kBwXRow, put4 = put_y(yv4);
+    const uint32_t xc = (uint32_t)(cit * 32 + tp * 8) * 2u;
+    auto yrel = [&](int v) {  // of a voxel of the brick
+        return ((uint32_t)(((v >> 6) * g.h + (v >> 4 & 3)) * g.w + (v & 15)) * (uint32_t)cout + (uint32_t)(cot * 32 + tp * 8)) * 2u;
+    };
+    const uint32_t yrel3 = yrel(yv3), yrel4 = yrel(yv4);
+    const uint32_t xsample = (uint32_t)g.d * (uint32_t)g.h * (uint32_t)g.w * (uint32_t)cin * 2u;
+    const uint32_t ysample = (uint32_t)g.d * (uint32_t)g.h * (uint32_t)g.w * (uint32_t)cout * 2u;
+    auto axis = [](int v, int ext, int periodic, bool& out) {
+        const int w = v < 0 ? v + ext : v >= ext ? v - ext : v;
+        out |= w != v && !periodic;
+        return w;
+    };
+    struct Brick {
+        int x, h, d, n;
+    };
+    auto after = [&](Brick b) {
+        b.x += kTW;
+        if (b.x == g.w) {
+            b.x = 0;
+            b.h += kTH;
+            if (b.h == g.h) {
+                b.h = 0;
+                b.d += kTD;
+                if (b.d == g.d) {
+                    b.d = 0;
+                    ++b.n;
+                }
+            }
+        }
+        return b;
+    };
+    Brick next;  // the next brick to load (bricks are loaded in order b0, b0 + 1, ...)
     {
         int r = (int)b0;
-        lx0 = (r % nbw) * kTW;
+        next.x = (r % nbw) * kTW;
         r /= nbw;
-        lh0 = (r % nbh) * kTH;
+        next.h = (r % nbh) * kTH;
         r /= nbh;
-        ld0 = (r % nbd) * kTD;
-        ln = r / nbd;
+        next.d = (r % nbd) * kTD;
+        next.n = r / nbd;
     }
-    const int xdz = xhr / 6 - 1, xdy = xhr % 6 - 1;         // this thread's halo row offsets
-    const int xcoff = cit * 32 + xcg * 8, dyoff = cot * 32 + dcg * 8;
-    auto load = [&]() {
-        const int x0 = lx0, h0 = lh0, d0 = ld0, n = ln;
-        lx0 += kTW;
-        if (lx0 == g.w) {
-            lx0 = 0;
-            lh0 += kTH;
-            if (lh0 == g.h) {
-                lh0 = 0;
-                ld0 += kTD;
-                if (ld0 == g.d) {
-                    ld0 = 0;
-                    ++ln;
-                }
-            }
-        }
-        if (has_x) {
-            int sd = 0, sh = 0;
-            const bool rok = shift_axis(d0, xdz, g.d, g.per[0], sd) && shift_axis(h0, xdy, g.h, g.per[1], sh);
-            // 32-bit element offsets from the tensor base (the host keeps x below 4 GiB)
-            const uint32_t xrow = (uint32_t)(((n * g.d + sd) * g.h + sh) * g.w) * (uint32_t)cin + (uint32_t)xcoff;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int pos = xoct * 8 + i;  // halo position: x = x0 - 1 + pos
-                int sw = 0;
-                xin[i] = u4{0u, 0u, 0u, 0u};
-                if (rok && pos < kTW + 2 && shift_axis(x0, pos - 1, g.w, g.per[2], sw))
-                    xin[i] = *(const u4*)((const char*)x + 2u * (xrow + (uint32_t)sw * (uint32_t)cin));
-            }
-        }
-        if (has_dy) {
-            const int v = ((n * g.d + d0 + (drow >> 2)) * g.h + h0 + (drow & 3)) * g.w + x0 + dxo;
-            const uint32_t src = (uint32_t)v * (uint32_t)cout + (uint32_t)dyoff;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) dyin[i] = *(const u4*)((const char*)dy + 2u * (src + (uint32_t)(i * cout)));
+    auto find_rows = [&](const Brick& b, uint32_t* rows) {
+        if (lane < kBwRows) {
+            bool out = false;
+            const int sd = axis(b.d + lane / kHH - 1, g.d, g.per[0], out);
+            const int sh = axis(b.h + lane % kHH - 1, g.h, g.per[1], out);
+            rows[lane] = out ? kNone : (uint32_t)(sd * g.h + sh) * (uint32_t)g.w * (uint32_t)cin * 2u;
         }
     };
-    auto store = [&](int buf) {
-        bf16* sdy = sdy2[buf];
-        bf16* sx = sx2[buf];
-        u4 out[8];
-        if (has_x) {
-            transpose8x8(xin, out);
+    u4 st[5];
+    auto load = [&](const Brick& b, const uint32_t* rows) {
+        const __amdgpu_buffer_rsrc_t xr = buf_rsrc((const char*)x + (uint64_t)b.n * xsample, xsample);
+        const __amdgpu_buffer_rsrc_t yr = buf_rsrc((const char*)dy + (uint64_t)b.n * ysample, ysample);
+        bool out = !all4;
+        const int sw = axis(b.x + hx - 1, g.w, g.per[2], out);
+        const uint32_t col = out ? kNone : (uint32_t)sw * (uint32_t)cin * 2u + xc;
+        const uint32_t ybase = (uint32_t)((b.d * g.h + b.h) * g.w + b.x) * (uint32_t)cout * 2u;
 #pragma unroll
-            for (int c = 0; c < 8; ++c) *(u4*)&sx[(xcg * 8 + c) * kXStride + xcg * kSkew + xhr * kXRow + xoct * 8] = out[c];
-        }
-        if (has_dy) {
-            transpose8x8(dyin, out);
-#pragma unroll
-            for (int c = 0; c < 8; ++c) *(u4*)&sdy[(dcg * 8 + c) * kDyStride + dcg * kSkew + drow * 16 + dxo] = out[c];
-        }
+        for (int i = 0; i < 3; ++i)
+            st[i] = __builtin_bit_cast(u4, ldb8(xr, __builtin_elementwise_add_sat(rows[trow % kBwStep + i * kBwStep], col), 0));
+        // one load for both kinds: a wave is of one kind
+        const __amdgpu_buffer_rsrc_t r3 = r3y ? yr : xr;
+        const uint32_t o3 = __builtin_elementwise_add_sat(rows[r3x ? trow + 3 * kBwStep : 0], r3x ? col : kNone);
+        st[3] = __builtin_bit_cast(u4, ldb8(r3, r3y ? yrel3 : o3, r3y ? ybase : 0));
+        st[4] = __builtin_bit_cast(u4, ldb8(yr, yrel4, ybase));
     };
-    // work units: (tap group g = (dz, dy), ci block ib), 18 of them; wave w
-    // takes units w, w + 8, w + 16.  The three x taps of a group share one
-    // 20-byte B read per lane (their K windows are byte shifts of it).
-    f4 acc[3][3][2];  // [unit of this wave][x tap][co block]
+    auto store = [&](uint32_t buf) {
+        if (all4) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b) acc[k][a][b] = f4{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < 3; ++i) *(u4*)(lds + buf + put_x + i * kBwStep * kBwXRow) = st[i];
+        }
+        if (r3x || r3y) *(u4*)(lds + buf + put3) = st[3];
+        if (r4) *(u4*)(lds + buf + put4) = st[4];
+    };
+    // this wave's depth tap, x half and pair of depth slices
+    const int dz = wave % 3, ib = wave / 3 & 1, dp = wave / 6;
     const int j = lane >> 4, l16 = lane & 15;
-    // two LDS buffers: brick br + 1 is stored while brick br's MFMAs run in
-    // other waves; one barrier per brick
+    // fragment reads: slice j / 2 of the pair, voxels 8 (j mod 2) + 0..7; a lane
+    // addresses four channels of one voxel, and gets four voxels of one channel
+    const uint32_t lane_at = (uint32_t)(j & 1) * slot(8) + (uint32_t)(l16 >> 2) * 32u + (uint32_t)(l16 & 3) * 8u;
+    const uint32_t get_x = (uint32_t)ib * kBwXHalf + (uint32_t)((2 * dp + dz + (j >> 1)) * kHH) * kBwXRow + lane_at;
+    const uint32_t get_x8 = get_x + ((j & 1) ? 256u : slot(8));  // four voxels 8 further on
+    const uint32_t get_y = 2 * kBwXHalf + (uint32_t)((2 * dp + (j >> 1)) * kTH) * kBwYRow + lane_at;
+    auto tr = [&](uint32_t at) -> u2 {
+        return __builtin_bit_cast(u2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(lds + at)));
+    };
+    const bool ones = bias && cit == 0 && dz == 0 && ib == 0;
+    float bsum[2] = {0.f, 0.f};  // this lane's voxels of channel l16 of each co block
+    f4 acc[3][3][2];             // [dy tap][x tap][co block]
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+#pragma unroll
+        for (int t = 0; t < 9; ++t) acc[t / 3][t % 3][b] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+    Brick following = after(next);
+    if (wave == 0) find_rows(next, row_off[0]);
+    if (wave == 1) find_rows(following, row_off[1]);
+    __syncthreads();
     if (b0 < b1) {
-        load();
+        load(next, row_off[0]);
         store(0);
-        if (b0 + 1 < b1) load();
     }
     __syncthreads();
-    int cur = 0;
+    uint32_t cur = 0;
     for (long long br = b0; br < b1; ++br) {
-        const bf16* sdy = sdy2[cur];
-        const bf16* sx = sx2[cur];
-        if (do_bias) {
-            const bf16* q = &sdy[(tid >> 4) * kDyStride + (tid >> 7) * kSkew + (tid & 15) * 16];
+        const bool more = br + 1 < b1;
+        const int odd = (int)(br - b0) & 1;
+        next = following;
+        following = after(next);
+        if (more) load(next, row_off[odd ^ 1]);
+        if (wave == 11) find_rows(following, row_off[odd]);
+        u2 xt[2][3], yt[4][2][2];
+        auto read_row = [&](int r) {
 #pragma unroll
-            for (int k = 0; k < 16; ++k) bsum += (float)q[k];
-        }
-        // 8 K steps of 32 voxels (two brick rows); lane group j takes voxels 8j..8j+7
-#pragma unroll 8
-        for (int ks = 0; ks < 8; ++ks) {
-            const int row = ks * 2 + (j >> 1), xo = (j & 1) * 8;
-            bf16x8 a[2];
+            for (int k = 0; k < 3; ++k)
+                xt[r & 1][k] = tr(cur + (k == 2 ? get_x8 : get_x + 128u * k) + (uint32_t)r * kBwXRow);
+            if (r < 4) {
 #pragma unroll
-            for (int cb = 0; cb < 2; ++cb)
-                a[cb] = *(const bf16x8*)&sdy[(cb * 16 + l16) * kDyStride + (cb * 2 + (l16 >> 3)) * kSkew + row * 16 + xo];
-            const int dd = row >> 2, hh = row & 3;
+                for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const int u = wave + 8 * k;
-                if (u < 18) {
-                    const int g = u >> 1, ib = u & 1;
-                    const int dz = g / 3 - 1, dyy = g % 3 - 1;
-                    const int hr = (dd + 1 + dz) * 6 + hh + 1 + dyy;
-                    const bf16* q = &sx[(ib * 16 + l16) * kXStride + (ib * 2 + (l16 >> 3)) * kSkew + hr * kXRow + xo];
-                    u4 lo = *(const u4*)q;
-                    unsigned hi = *(const unsigned*)(q + 8);
-                    // opaque to the optimiser: the third tap's window is then built from
-                    // these registers instead of being re-read from LDS as an unaligned load
-                    asm("" : "+v"(lo), "+v"(hi));
-                    // x taps cx = 0, 1, 2 start 0, 1, 2 elements into the read
-                    const u4 f[3] = {lo,
-                                     u4{__builtin_amdgcn_alignbyte(lo[1], lo[0], 2), __builtin_amdgcn_alignbyte(lo[2], lo[1], 2),
-                                        __builtin_amdgcn_alignbyte(lo[3], lo[2], 2), __builtin_amdgcn_alignbyte(hi, lo[3], 2)},
-                                     u4{lo[1], lo[2], lo[3], hi}};
+                    for (int k = 0; k < 2; ++k)
+                        yt[r][b][k] = tr(cur + get_y + (uint32_t)b * kBwYHalf + (uint32_t)r * kBwYRow + 128u * k);
+            }
+        };
+        read_row(0);
 #pragma unroll
-                    for (int cx = 0; cx < 3; ++cx) {
-                        const bf16x8 b = __builtin_bit_cast(bf16x8, f[cx]);
+        for (int r = 0; r < 6; ++r) {
+            const u2 t0 = xt[r & 1][0], t1 = xt[r & 1][1], t2 = xt[r & 1][2];
+            const u4 f[3] = {u4{t0.x, t0.y, t1.x, t1.y},
+                             u4{__builtin_amdgcn_alignbyte(t0.y, t0.x, 2), __builtin_amdgcn_alignbyte(t1.x, t0.y, 2),
+                                __builtin_amdgcn_alignbyte(t1.y, t1.x, 2), __builtin_amdgcn_alignbyte(t2.x, t1.y, 2)},
+                             u4{t0.y, t1.x, t1.y, t2.x}};
+            // the dy row that this halo row is neighbour ty - 1 of; the next rows are
+            // read once the oldest dy row is done with
 #pragma unroll
-                        for (int cb = 0; cb < 2; ++cb)
-                            acc[k][cx][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[cb], b, acc[k][cx][cb], 0, 0, 0);
-                    }
+            for (int ty = 2; ty >= 0; --ty) {
+                const int h = r - ty;
+                if (h >= 0 && h < 4) {
+#pragma unroll
+                    for (int cx = 0; cx < 3; ++cx)
+#pragma unroll
+                        for (int b = 0; b < 2; ++b) {
+                            const u4 a = u4{yt[h][b][0].x, yt[h][b][0].y, yt[h][b][1].x, yt[h][b][1].y};
+                            acc[ty][cx][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                __builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, f[cx]), acc[ty][cx][b], 0, 0, 0);
+                        }
                 }
+                __builtin_amdgcn_sched_barrier(0);
+                if (ty == 2 && r < 5) read_row(r + 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (ones && r < 4) {
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int k = 0; k < 2; ++k)
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            const unsigned w = yt[r][b][k][e];
+                            bsum[b] += __builtin_bit_cast(float, w << 16);
+                            bsum[b] += __builtin_bit_cast(float, w & 0xffff0000u);
+                        }
             }
         }
-        if (br + 1 < b1) {
-            store(cur ^ 1);
-            if (br + 2 < b1) load();
-        }
+        cur ^= kBwBuf;
+        if (more) store(cur);
         __syncthreads();
-        cur ^= 1;
     }
-    if (do_bias) {
-        sbias[tid] = bsum;
-        __syncthreads();
-        if (tid < 32) {
-            float b = 0.f;
+    // the waves of the second pair of slices hand their sums over
+    f4* sum = (f4*)lds + (wave % 6) * 18 * 64 + lane;
+    float* bs = (float*)((f4*)lds + 6 * 18 * 64) + l16;
+    if (ones) {
 #pragma unroll
-            for (int k = 0; k < 16; ++k) b += sbias[tid * 16 + k];
-            part[(long long)ch * pstride + 27LL * cin * cout + cot * 32 + tid] = b;
+        for (int b = 0; b < 2; ++b) {
+            bsum[b] += __shfl_xor(bsum[b], 16);
+            bsum[b] += __shfl_xor(bsum[b], 32);
         }
     }
+    if (dp == 1) {
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) sum[(t * 2 + b) * 64] = acc[t / 3][t % 3][b];
+        if (ones && j == 0) {
+            bs[0] = bsum[0];
+            bs[16] = bsum[1];
+        }
+    }
+    __syncthreads();
+    if (dp == 1) return;
     // D[co][ci]: row (lane / 16) * 4 + i, column lane % 16
+    float* const out = part + (long long)ch * pstride;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const int u = wave + 8 * k;
-        if (u >= 18) continue;
-        const int g = u >> 1, ib = u & 1;
+    for (int t = 0; t < 9; ++t) {
+        float* p = out + ((long long)(dz * 9 + t) * cout) * cin;
 #pragma unroll
-        for (int cx = 0; cx < 3; ++cx) {
-            const int t = g * 3 + cx;
-            float* p = part + (long long)ch * pstride + ((long long)t * cout) * cin;
+        for (int b = 0; b < 2; ++b) {
+            const f4 s = acc[t / 3][t % 3][b] + sum[(t * 2 + b) * 64];
 #pragma unroll
-            for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int co = cot * 32 + cb * 16 + (lane >> 4) * 4 + i;
-                    const int ci = cit * 32 + ib * 16 + (lane & 15);
-                    p[(long long)co * cin + ci] = acc[k][cx][cb][i];
-                }
+            for (int i = 0; i < 4; ++i) {
+                const int co = cot * 32 + b * 16 + j * 4 + i;
+                const int ci = cit * 32 + ib * 16 + l16;
+                p[(long long)co * cin + ci] = s[i];
+            }
         }
+    }
+    if (ones && j == 0) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) out[27LL * cin * cout + cot * 32 + b * 16 + l16] = bsum[b] + bs[16 * b];
     }
 }
 
