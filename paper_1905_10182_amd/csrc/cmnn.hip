@@ -1792,20 +1792,27 @@ bool bwd_w_brick(const G& g, int cin, int cout)
 }
 
 // Voxel chunks of the weight gradient (partials summed in a fixed order).
-// Brick path: about 256 workgroups of 8 waves (one per CU), whole bricks
+// Brick path: at most 256 workgroups (one per CU), whole bricks
 // per chunk.  Generic path: >= 4096 voxels per chunk.
 int bwd_w_chunks(const G& g, int cin, int cout)
 {
     if (bwd_w_brick(g, cin, cout)) {
-        // one workgroup per CU (147 KB of LDS): at most 256 (chunk, tile)
-        // workgroups, so that none waits for a second round
+        // one workgroup per CU (143 KB of LDS): at most 256 (chunk, tile)
+        // workgroups, so that none waits for a second round; then the bricks
+        // per chunk with the least time, at about 1.6 us a brick and 0.028 us to
+        // write and sum a workgroup's partials.  One brick each where 256 CUs
+        // take 256: 24.4 us, two each 21.1; 64 -> 64 on 128 bricks 2 / 3: 23.3 / 20.8;
+        // 1024 bricks 4 / 6: 29.4 / 30.4.
         const long long bricks = g.nvox / (kTD * kTH * kTW);
         const long long tiles = (long long)(cin / 32) * (cout / 32);
         long long c = 256 / tiles;
         if (c < 1) c = 1;
         if (c > bricks) c = bricks;
-        const long long per = (bricks + c - 1) / c;
-        return (int)((bricks + per - 1) / per);
+        long long per = (bricks + c - 1) / c;
+        auto chunks = [&](long long p) { return (bricks + p - 1) / p; };
+        auto cost = [&](long long p) { return 1.6 * (double)p + 0.028 * (double)(chunks(p) * tiles); };
+        while (per < bricks && cost(per + 1) < cost(per)) ++per;
+        return (int)chunks(per);
     }
     long long c = (g.nvox + 4095) / 4096;
     return (int)(c < 64 ? c : 64);
