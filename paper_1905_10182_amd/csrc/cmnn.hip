@@ -15,6 +15,8 @@
 //                   as 16-byte fragments; per-chunk partials, fixed-order sum.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include <cstdint>
 #include <mutex>
 
@@ -564,6 +566,214 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 #pragma unroll
     for (int m = 0; m < kRH; ++m) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            bf16x4 o;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float f = acc[m][b][i];
+                if (SIGN > 0) {
+                    f += bb[b][i];
+                    if (ACT == CMNN_ACT_LEAKY) f = leaky(f);
+                } else if (ACT == CMNN_ACT_LEAKY) {
+                    if ((float)__builtin_bit_cast(bf16x4, gt[m][b])[i] <= 0.f) f *= kLeak;
+                }
+                o[i] = (bf16)f;
+            }
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, o), yr, ylane, yrow(m) + 32u * b, 0);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// forward convolution (and data gradient) for grids that leave CUs idle
+//
+// Workgroup = a 4 x 4 x 16 brick x 32 output channels; wave w owns depth slice w
+// and walks down the halo rows as in the row kernel.  Here the weights go through
+// LDS: read from L1 by every wave, the nine taps' 32 rows of a depth tap (half
+// lines where cin is a multiple of 64) do not fit it, and each wave fetches them
+// from L2.  With one workgroup on a CU nothing else covers a load, so the
+// weights of a depth tap are loaded two taps ahead and the next channels' halo
+// a chunk ahead; two buffers each, one barrier per depth tap.  No load is under
+// a branch: what there is not to load has an offset past its buffer's range.
+// Products are added in the order of the brick kernel: same bits.
+// us, brick kernel / this: 192 -> 96 channels at 16 x 8 x 8 x 16 47 / 28, 64 -> 96 19.5 /
+// 11.9, 96 -> 96 21 / 16; 64 -> 64 at 4 x 16 x 16 x 32 20.5 / 13.0, at 1 x 16 x 16 x 32 12.7 /
+// 11.2; 32 -> 32 at 1 x 32 x 32 x 64 10.5 / 8.7.  The same with the weights read from L1
+// into two register sets, or with twelve waves a brick: 47 and 47.
+constexpr int kFH = kTH + 2, kFRows = kHD * kFH, kFIters = kFRows / 3;
+
+template <int SIGN, int ACT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_conv_few(
+    G g, const bf16* __restrict__ x, int cin, const bf16* __restrict__ wt, const float* __restrict__ bias, int cout,
+    bf16* __restrict__ y, const bf16* __restrict__ gate)
+{
+    typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    __shared__ __attribute__((aligned(128))) char sx[2][kFRows * kRRow];
+    __shared__ __attribute__((aligned(128))) char sw[2][9 * 32 * 64];
+    __shared__ uint32_t row_off[kFRows];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ncb = cout / 32;
+    const int co0 = (int)(blockIdx.x % ncb) * 32;
+    int r0 = (int)(blockIdx.x / ncb);
+    const int nbw = g.w / kTW, nbh = g.h / kTH, nbd = g.d / kTD;
+    const int x0 = (r0 % nbw) * kTW;
+    r0 /= nbw;
+    const int h0 = (r0 % nbh) * kTH;
+    r0 /= nbh;
+    const int d0 = (r0 % nbd) * kTD;
+    const long long n = r0 / nbd;
+    auto source = [](int v, int q, int ext, int periodic, bool& out) -> int {
+        const int t = v + q - 1, w = t < 0 ? t + ext : t >= ext ? t - ext : t;
+        out |= t != w && !periodic;
+        return w;
+    };
+    if (tid < kFRows) {
+        bool out = false;
+        const int sd = source(d0, tid / kFH, g.d, g.per[0], out), sh = source(h0, tid % kFH, g.h, g.per[1], out);
+        row_off[tid] = out ? kNone : (uint32_t)(sd * g.h + sh) * (uint32_t)g.w * (uint32_t)cin * 2u;
+    }
+    const int trow = tid / kRParts, hx = (tid - trow * kRParts) >> 2, part = tid & 3;
+    uint32_t col_off;
+    {
+        bool out = trow >= 3;
+        const int sw = source(x0, hx, g.w, g.per[2], out);
+        col_off = out ? kNone : ((uint32_t)sw * (uint32_t)cin + (uint32_t)part * 8u) * 2u;
+    }
+    const uint32_t put = trow * kRRow + hx * 64 + ((part ^ ((hx >> 1) & 3)) << 4);
+    const uint32_t sample = (uint32_t)g.d * (uint32_t)g.h * (uint32_t)g.w * (uint32_t)cin * 2u;
+    const __amdgpu_buffer_rsrc_t xr = buf_rsrc(x + n * (long long)(sample / 2u), sample);
+    const __amdgpu_buffer_rsrc_t wr = buf_rsrc(wt, 27u * (uint32_t)cout * (uint32_t)cin * 2u);
+    const int co = co0 + (lane >> 4) * 4;  // this lane's output channels co + 16 b + i
+    const uint32_t sample_y = (uint32_t)g.d * (uint32_t)g.h * (uint32_t)g.w * (uint32_t)cout * 2u;
+    const __amdgpu_buffer_rsrc_t yr = buf_rsrc(y + n * (long long)(sample_y / 2u), sample_y);
+    const __amdgpu_buffer_rsrc_t gr = buf_rsrc(gate + n * (long long)(sample_y / 2u), sample_y);
+    const uint32_t ylane = ((uint32_t)(lane & 15) * (uint32_t)cout + (uint32_t)co) * 2u;
+    auto yrow = [&](int m) { return (uint32_t)(((d0 + wv) * g.h + h0 + m) * g.w + x0) * (uint32_t)cout * 2u; };
+    uint32_t lane_a[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const uint32_t vx = (uint32_t)(lane & 15) + (uint32_t)k, grp = (uint32_t)(lane >> 4);
+        lane_a[k] = vx * 64u + ((grp ^ ((vx >> 1) & 3u)) << 4);
+    }
+    u4 stage[kFIters];
+    auto halo = [&](int c) {
+        const uint32_t col = c < cin ? col_off : kNone;
+#pragma unroll
+        for (int it = 0; it < kFIters; ++it)
+            stage[it] = __builtin_bit_cast(u4, ldb8(xr, __builtin_elementwise_add_sat(row_off[(it * 3 + trow) % kFRows], col), (uint32_t)c * 2u));
+    };
+    // weights: rows (tap of the depth tap, output channel) of 32 input channels,
+    // four threads a row, parts swizzled as the halo's are
+    constexpr int kWIters = (9 * 32 * 4 + 255) / 256;
+    u4 ws[kWIters];
+    const int wco = tid >> 2 & 31, wt0 = tid >> 7;  // tap wt0 + 2 it
+    const uint32_t wthr = ((uint32_t)(wt0 * cout + co0 + wco) * (uint32_t)cin + (uint32_t)part * 8u) * 2u;
+    const uint32_t wput = (uint32_t)((tid >> 2) * 64) + ((uint32_t)(part ^ (wco >> 1 & 3)) << 4);
+    auto weights = [&](int c, int tz) {
+#pragma unroll
+        for (int it = 0; it < kWIters; ++it)
+            ws[it] = __builtin_bit_cast(u4, ldb8(wr, c < cin && wt0 + 2 * it < 9 ? wthr : kNone,
+                                                 ((uint32_t)((tz * 9 + 2 * it) * cout) * (uint32_t)cin + (uint32_t)c) * 2u));
+    };
+    auto put_weights = [&](int set) {
+#pragma unroll
+        for (int it = 0; it < kWIters; ++it)
+            if (wt0 + 2 * it < 9) *(u4*)(sw[set] + wput + it * (2 * 32 * 64)) = ws[it];
+    };
+    uint32_t lane_w[2];  // fragment reads: output channel lane % 16 of each block
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const uint32_t c = (uint32_t)(lane & 15) + 16u * b;
+        lane_w[b] = c * 64u + ((((uint32_t)lane >> 4) ^ (c >> 1 & 3u)) << 4);
+    }
+    __syncthreads();
+    halo(0);
+    weights(0, 0);
+    f4 bb[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
+    if (SIGN > 0 && bias) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) bb[b][i] = bias[co + 16 * b + i];
+    }
+    u2 gt[kTH][2];
+    if (SIGN < 0 && ACT == CMNN_ACT_LEAKY) {
+#pragma unroll
+        for (int m = 0; m < kTH; ++m)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) gt[m][b] = __builtin_amdgcn_raw_buffer_load_b64(gr, ylane, yrow(m) + 32u * b, 0);
+    }
+    f4 acc[kTH][2];
+#pragma unroll
+    for (int m = 0; m < kTH; ++m) acc[m][0] = acc[m][1] = f4{0.f, 0.f, 0.f, 0.f};
+    auto store = [&](char* to) {
+        if (trow < 3) {
+#pragma unroll
+            for (int it = 0; it < kFIters; ++it) *(u4*)(to + put + it * 3 * kRRow) = stage[it];
+        }
+    };
+    store(sx[0]);
+    put_weights(0);
+    weights(0, 1);
+    __syncthreads();
+    auto chunk = [&](int c0, auto par) {  // par: the set of its first depth tap, and its LDS buffer
+        constexpr int P = decltype(par)::value;
+#pragma unroll
+        for (int tz = 0; tz < 3; ++tz) {
+            const int dz = SIGN * (tz - 1);
+            put_weights((P + tz + 1) & 1);  // of the next depth tap
+            weights(tz == 0 ? c0 : c0 + 32, tz == 0 ? 2 : tz - 1);
+            if (tz == 0) halo(c0 + 32);
+            bf16x8 bw[9][2];
+            auto frag = [&](int ty) {
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) bw[ty * 3 + j][b] = *(const bf16x8*)(sw[(P + tz) & 1] + (ty * 3 + j) * (32 * 64) + lane_w[b]);
+            };
+            frag(0);
+            bf16x8 af[2][3];
+            auto row_load = [&](int rr) {
+                const int r = SIGN > 0 ? rr : kFH - 1 - rr;
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    af[rr & 1][k] = *(const bf16x8*)(sx[P] + (uint32_t)((wv + 1 + dz) * kFH + r) * kRRow + lane_a[k]);
+            };
+            row_load(0);
+            frag(1);
+            frag(2);
+#pragma unroll
+            for (int rr = 0; rr < kFH; ++rr) {
+                const int r = SIGN > 0 ? rr : kFH - 1 - rr;
+                if (rr + 1 < kFH) row_load(rr + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+#pragma unroll
+                    for (int ty = 0; ty < 3; ++ty) {
+                        const int m = r - 1 - SIGN * (ty - 1);
+                        if (m < 0 || m >= kTH) continue;
+#pragma unroll
+                        for (int b = 0; b < 2; ++b)
+                            acc[m][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                bw[ty * 3 + j][b], af[rr & 1][SIGN > 0 ? j : 2 - j], acc[m][b], 0, 0, 0);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (tz == 2) store(sx[P ^ 1]);
+            __syncthreads();
+        }
+    };
+    for (int c0 = 0; c0 < cin; c0 += 64) {
+        chunk(c0, std::integral_constant<int, 0>{});
+        if (c0 + 32 >= cin) break;
+        chunk(c0 + 32, std::integral_constant<int, 1>{});
+    }
+#pragma unroll
+    for (int m = 0; m < kTH; ++m) {
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
             bf16x4 o;
@@ -1855,6 +2065,16 @@ int conv_dispatch(const G& g, const bf16* x, int cin, const bf16* w, const float
         const bool rows32 = g.nvox / g.n * 2 * (cin > cout ? cin : cout) < (long long)kNone;
         if (g.h % kRH == 0 && row_blocks >= 192 && row_blocks < (1LL << 31) && rows32 && ((uintptr_t)y & 7u) == 0)
             return conv_rows_launch<SIGN, ACT>(g, x, cin, w, bias, cout, y, gate, s);
+        // One workgroup of k_conv_few runs on a CU (120 KB of LDS).  With one chunk
+        // of input channels the brick kernel's several per CU are better in a
+        // second round (288 workgroups, 32 channels: 13.5 us against 15.3); with more,
+        // its weight reads cost more than that (486 workgroups, 96 channels: 36.0
+        // against 34.2; 720, 64 channels: 46 against 36).
+        const long long few_blocks = bricks * (c16 / 2);
+        if ((few_blocks <= 256 || cin > 32) && few_blocks < (1LL << 31) && rows32 && ((uintptr_t)y & 7u) == 0) {
+            k_conv_few<SIGN, ACT><<<dim3((unsigned)few_blocks), 256, 0, s>>>(g, x, cin, w, bias, cout, y, gate);
+            return launched();
+        }
         if (c16 % 6 == 0 && bricks * (c16 / 6) >= 512) return conv_tile_launch<6, SIGN, ACT>(g, x, cin, w, bias, cout, y, gate, s);
         if (c16 % 4 == 0 && bricks * (c16 / 4) >= 512) return conv_tile_launch<4, SIGN, ACT>(g, x, cin, w, bias, cout, y, gate, s);
         // a grid of fewer workgroups than CUs takes 16-channel tiles (twice the workgroups)
