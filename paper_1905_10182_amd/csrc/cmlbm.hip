@@ -2317,6 +2317,14 @@ int tile_steps(const cmlbm_lattice* lat, int n)
     return t2 <= 2 * cus ? 2 : 0;
 }
 
+// Whether s is being captured into a graph (the null stream cannot be).
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (s && hipStreamIsCapturing(s, &status) != hipSuccess) (void)hipGetLastError();
+    return status == hipStreamCaptureStatusActive;
+}
+
 int launch_tile(cmlbm_lattice* lat, int k, hipStream_t s)
 {
     if (lat->p.storage == CMLBM_FP64)
@@ -2720,8 +2728,20 @@ int cmlbm_step(cmlbm_lattice* lat, int32_t nsteps, void* hip_stream)
     if (!lat->initialized) return fail(lat, CMLBM_ESTATE, "step before init");
     hipStream_t s = (hipStream_t)hip_stream;
     const bool march = marches(lat, nsteps);
+    // A graph that holds an even number of steps can be replayed: every replay
+    // starts in the buffer that held the state at capture, so the steps have to
+    // end there.  Each launch changes buffers once, so under capture the
+    // launches of two steps come in pairs (those of three change nothing).
+    const bool pairs = !march && tile_steps(lat, nsteps) && capturing(s);
+    bool second = false;
     for (int32_t k = 0; k < nsteps;) {
-        const int many = march ? 0 : tile_steps(lat, nsteps - k);
+        int many = march ? 0 : tile_steps(lat, nsteps - k);
+        if (pairs && many == 2) {
+            if (second || nsteps - k >= 4)
+                second = !second;
+            else
+                many = 0;
+        }
         int rc = many               ? launch_tile(lat, many, s)
                  : !march           ? launch_step(lat, s)
                  : k == 0           ? launch_to_moments(lat, s)

@@ -1,0 +1,32 @@
+"""The launches of multi-step calls, from the host code alone (no GPU)."""
+import pytest
+
+from hip_recorder import launches
+
+
+def pairs_of_buffers(rows):
+    return [(r[3], r[4]) for r in rows]
+
+
+def test_captured_even_calls_end_where_they_start():
+    """A graph of an even number of steps is replayed from the buffer that held
+    the state at capture, so it has to end there; an odd call changes buffers.
+    Every launch reads what the one before it wrote."""
+    runs = launches("""
+out = []
+for dims in ((8, 8, 8), (9, 11, 13, 2), (32, 32, 16), (32, 32, 32), (8, 60, 60), (8, 9, 8, 30), (64, 64, 64)):
+    for storage in ("fp64", "fp32"):
+        for wall in (0, 1):
+            h = handle3(*dims, storage=storage, wall=wall)
+            for n in range(1, 12):
+                t = time_of(L3.cmlbm_get_time, h)
+                rec(capture=1)
+                assert L3.cmlbm_step(h, n, STREAM) == 0
+                out.append([dims, storage, n, time_of(L3.cmlbm_get_time, h) - t, seen()])
+""")
+    assert any("k_tile<double, 2" in r[0] for *_, rows in runs for r in rows)
+    for dims, storage, n, steps, rows in runs:
+        bufs = pairs_of_buffers(rows)
+        assert steps == n
+        assert all(a[1] == b[0] for a, b in zip(bufs, bufs[1:]))
+        assert (bufs[0][0] == bufs[-1][1]) == (n % 2 == 0), (dims, storage, n)
