@@ -106,7 +106,10 @@ int cmlbm2d_init(cmlbm2d_lattice* lat, const void* dev_rho, const void* dev_u, i
  * with forcing, store.  FP64 and FP32 storage may take several steps in one
  * launch (chosen by size); the populations after n steps are the same bits
  * however n is split into calls.  The buffer that does not hold the state is
- * scratch. */
+ * scratch.  Only kernels are enqueued, so a call can be captured into a HIP
+ * graph; a captured call of an even number of steps ends in the buffer it
+ * starts in, and each replay of the graph advances the state by that many (the
+ * handle's step counter is advanced at capture, not by replays). */
 int cmlbm2d_step(cmlbm2d_lattice* lat, int32_t nsteps, void* hip_stream);
 
 /* rho(x, t) into dev_rho[N] and u = (sum f c + F/2)/rho into dev_u[2][N]

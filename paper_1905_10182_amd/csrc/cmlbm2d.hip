@@ -865,11 +865,13 @@ struct Pass {
 //             0.53 K + 3.7 x; beyond, 3.5 + 7.5 x / 3.5 + 3.9 x.
 // The best rate decides while many steps are left, the best way to end exactly
 // (6 + 4 for ten steps where 8 + 2 has the better start) over the last sixteen.
+// parity 0 or 1: those n steps shall take an even or odd number of passes of an
+// even number of steps (see cmlbm2d_step); -1: any.
 // us per step, k2_step / chosen: FP64 16^2 3.06 / 1.23 (tile), 64^2 3.18 / 1.25
 // (tile), 256^2 4.9 / 2.3 (tile), 500^2 9.3 / 5.8, 1024^2 30.9 / 11.8 (march),
 // 4096^2 495 / 127, 8192^2 1873 / 489; FP32 64^2 3.4 / 1.04, 300^2 4.2 / 1.9, 1024^2
 // 16.8 / 10.1, 4096^2 223 / 78 (march), 8192^2 890 / 270.
-Pass next_pass(const cmlbm2d_lattice* lat, int n)
+Pass next_pass(const cmlbm2d_lattice* lat, int n, int parity)
 {
     constexpr int kMost = 8, kLast = 16;
     const Geom2& g = lat->g;
@@ -903,16 +905,29 @@ Pass next_pass(const cmlbm2d_lattice* lat, int n)
             if (of[K].t * first < of[first].t * K) first = K;
         return of[first];
     }
-    double least[kLast + 1] = {0.0};
-    for (int m = 1; m <= n; ++m) {
-        least[m] = 1e300;
-        for (int K = 1; K <= kMost && K <= m; ++K)
-            if (of[K].t + least[m - K] < least[m]) {
-                least[m] = of[K].t + least[m - K];
-                first = K;
+    // least[m][q]: m steps, q the parity of their even passes (q = 0 where it is free)
+    const int layers = parity < 0 ? 1 : 2;
+    double least[kLast + 1][2] = {{0.0, 1e300}};
+    for (int m = 1; m <= n; ++m)
+        for (int q = 0; q < layers; ++q) {
+            least[m][q] = 1e300;
+            for (int K = 1; K <= kMost && K <= m; ++K) {
+                const double t = of[K].t + least[m - K][layers == 2 && K % 2 == 0 ? 1 - q : q];
+                if (t < least[m][q]) {
+                    least[m][q] = t;
+                    if (m == n && (layers == 1 || q == parity)) first = K;
+                }
             }
-    }
+        }
     return of[first];
+}
+
+// Whether s is being captured into a graph (the null stream cannot be).
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (s && hipStreamIsCapturing(s, &status) != hipSuccess) (void)hipGetLastError();
+    return status == hipStreamCaptureStatusActive;
 }
 
 template <int ST>
@@ -1080,8 +1095,14 @@ int cmlbm2d_step(cmlbm2d_lattice* lat, int32_t nsteps, void* hip_stream)
     if (nsteps < 0) return fail(lat, CMLBM2D_EINVAL, "nsteps must be >= 0");
     if (!lat->initialized) return fail(lat, CMLBM2D_ESTATE, "step before init");
     hipStream_t s = (hipStream_t)hip_stream;
+    // A graph that holds an even number of steps can be replayed: every replay
+    // starts in the buffer that held the state at capture, so the steps have to
+    // end there.  A pass changes buffers once, so under capture the passes of
+    // an even number of steps come in pairs.
+    int parity = nsteps > 1 && capturing(s) ? 0 : -1;
     for (int32_t k = 0; k < nsteps;) {
-        const Pass p = next_pass(lat, nsteps - k);
+        const Pass p = next_pass(lat, nsteps - k, parity);
+        if (parity >= 0 && p.steps % 2 == 0) parity = 1 - parity;
         launch_pass(lat, p, s);
         const int rc = launch_check(lat, "step");
         if (rc) return rc;

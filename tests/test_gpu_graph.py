@@ -52,3 +52,13 @@ def test_replays_advance_the_state(dims, wall, storage, n):
     print("graph", dims, storage, n, flush=True)
     check_replays(lambda: Lattice(nx, ny, nz, tau=0.7, storage=storage, wall=wall, device="cuda:0"),
                   populations(27, (1, nz, ny, nx)), n)
+
+
+@pytest.mark.parametrize("dims", [(64, 64), (300, 211), (1025, 1100)])
+@pytest.mark.parametrize("storage", ["fp64", "fp32"])
+@pytest.mark.parametrize("n", [2, 6, 8, 10])
+def test_replays_advance_the_plane_state(dims, storage, n):
+    from paper_1905_10182_amd.cmlbm2d import Lattice2D
+    nx, ny = dims
+    print("graph", dims, storage, n, flush=True)
+    check_replays(lambda: Lattice2D(nx, ny, tau=0.7, storage=storage, device="cuda:0"), populations(9, (ny, nx)), n)

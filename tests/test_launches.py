@@ -30,3 +30,24 @@ for dims in ((8, 8, 8), (9, 11, 13, 2), (32, 32, 16), (32, 32, 32), (8, 60, 60),
         assert steps == n
         assert all(a[1] == b[0] for a, b in zip(bufs, bufs[1:]))
         assert (bufs[0][0] == bufs[-1][1]) == (n % 2 == 0), (dims, storage, n)
+
+
+def test_captured_even_calls_of_the_plane_solver_end_where_they_start():
+    runs = launches("""
+out = []
+for dims in ((1, 1), (8, 8), (64, 64), (300, 211), (64, 70000), (1025, 1100), (4096, 1100), (3001, 1500), (8192, 8192)):
+    for storage in ("fp64", "fp32", "fp16"):
+        h = handle2(*dims, storage=storage)
+        for n in list(range(1, 26)) + [100, 101]:
+            t = time_of(L2.cmlbm2d_get_time, h)
+            rec(capture=1)
+            assert L2.cmlbm2d_step(h, n, STREAM) == 0
+            out.append([dims, storage, n, time_of(L2.cmlbm2d_get_time, h) - t, seen()])
+""")
+    names = {r[0].split("<")[0] for *_, rows in runs for r in rows}
+    assert names == {"k2_step", "k2_march", "k2_tile"}
+    for dims, storage, n, steps, rows in runs:
+        bufs = pairs_of_buffers(rows)
+        assert steps == n
+        assert all(a[1] == b[0] for a, b in zip(bufs, bufs[1:]))
+        assert (bufs[0][0] == bufs[-1][1]) == (n % 2 == 0), (dims, storage, n)
