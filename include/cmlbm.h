@@ -183,10 +183,12 @@ int cmlbm_init(cmlbm_lattice* lat, const void* dev_rho, const void* dev_u, int i
  * or take two or three steps of a small lattice in one launch (chosen by
  * size); the populations after n steps are the same bits however n
  * is split into calls.  The buffer that does not hold the state is scratch.
- * Only kernels are enqueued, so a call can be captured into a HIP graph; a
- * captured call of an even number of steps ends in the buffer it starts in,
- * and each replay of the graph advances the state by that many (the handle's
- * step counter is advanced at capture, not by replays). */
+ * If a launch fails while the state is the nine numbers, it is undefined until
+ * the next init or restore (ESTATE).  Only kernels are enqueued, so a call can
+ * be captured into a HIP graph; a captured call of an even number of steps ends
+ * in the buffer it starts in, and each replay of the graph advances the state
+ * by that many (the handle's step counter is advanced at capture, not by
+ * replays). */
 int cmlbm_step(cmlbm_lattice* lat, int32_t nsteps, void* hip_stream);
 
 /* One time step (cmlbm_step with nsteps = 1) that also writes the velocity of

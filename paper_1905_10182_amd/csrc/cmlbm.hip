@@ -2747,7 +2747,11 @@ int cmlbm_step(cmlbm_lattice* lat, int32_t nsteps, void* hip_stream)
                  : k == 0           ? launch_to_moments(lat, s)
                  : lat->p.storage == CMLBM_FP64 ? launch_march<double>(lat, s, k == nsteps - 1)
                                                 : launch_march<float>(lat, s, k == nsteps - 1);
-        if (rc) return rc;
+        if (rc) {
+            // the current buffer holds the nine numbers, not populations
+            if (march && k > 0) lat->initialized = lat->snap_valid = false;
+            return rc;
+        }
         lat->cur = 1 - lat->cur;
         lat->t += many ? many : 1;
         k += many ? many : 1;

@@ -51,3 +51,26 @@ for dims in ((1, 1), (8, 8), (64, 64), (300, 211), (64, 70000), (1025, 1100), (4
         assert steps == n
         assert all(a[1] == b[0] for a, b in zip(bufs, bufs[1:]))
         assert (bufs[0][0] == bufs[-1][1]) == (n % 2 == 0), (dims, storage, n)
+
+
+def test_a_launch_that_fails_inside_the_moment_path_ends_the_state():
+    """Between the first and the last step of such a call a buffer holds nine
+    numbers per cell: if a launch fails there, nothing may read it as
+    populations.  A failure of the first launch leaves the state as it was, and
+    so does any failure of a call whose every launch writes populations."""
+    codes = launches("""
+out = []
+for dims, fail in (((64, 64, 64), 0), ((64, 64, 64), 1), ((64, 64, 64), 3), ((48, 40, 40), 2)):
+    h = handle3(*dims)
+    rec(fail=fail)
+    first = L3.cmlbm_step(h, 5, None)
+    launched = len(seen())
+    rec()
+    after = [L3.cmlbm_step(h, 1, None), L3.cmlbm_moments(h, F, None, 0, None), L3.cmlbm_populations(h, F, None),
+             L3.cmlbm_save_state(h, F, 1 << 40, None)]
+    again = L3.cmlbm_init(h, None, None, 0, None)
+    out.append([first, launched, after, again, L3.cmlbm_step(h, 5, None)])
+""")
+    EHIP, ESTATE = -3, -5
+    assert codes == [[EHIP, 0, [0] * 4, 0, 0], [EHIP, 1, [ESTATE] * 4, 0, 0], [EHIP, 3, [ESTATE] * 4, 0, 0],
+                     [EHIP, 2, [0] * 4, 0, 0]]
