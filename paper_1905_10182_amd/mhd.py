@@ -247,7 +247,7 @@ class CoupledMHD:
         self.shape = (int(nz), int(ny), int(nx))
         self.dtype = self.mag.dtype
         self.F = self.torch.zeros((3, 1) + self.shape, dtype=self.dtype, device=self.mag.device)
-        self._u = self._b = None  # step()'s work arrays, from its first call on
+        self._u = self._b = None  # step()'s work arrays, from the first call that needs them on
 
     def init(self, rho, u, b):
         u = np.asarray(u, np.float64).reshape((3,) + self.shape)
@@ -264,8 +264,8 @@ class CoupledMHD:
     def step(self, n=1):
         if self._u is None:
             self._u = self.torch.empty((3, 1) + self.shape, dtype=self.dtype, device=self.mag.device)
-            if self.current == "stencil":
-                self._b = self.torch.empty((3,) + self.shape, dtype=self.dtype, device=self.mag.device)
+        if self._b is None and self.current == "stencil":
+            self._b = self.torch.empty((3,) + self.shape, dtype=self.dtype, device=self.mag.device)
         for _ in range(int(n)):
             u_lag = None if self.current == "stencil" else self.velocity()[1]
             self.mag.lorentz_force(self.F, u_lag, self.current, self._b)
