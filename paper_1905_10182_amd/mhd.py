@@ -198,12 +198,25 @@ class MagneticLattice:
 
     def lorentz_force(self, F_out, u=None, current="populations", b=None):
         """The Lorentz force F = j x b (plus the body force) alone, into F_out (a
-        contiguous device tensor of 3N values).  The stencil current works on b
-        ((3, nz, ny, nx), overwritten) and does not read u; the population
-        current needs u and no b."""
-        assert F_out.is_contiguous() and F_out.dtype == self.dtype and F_out.numel() == 3 * int(np.prod(self.shape))
+        contiguous device tensor of 3N values).  The stencil current needs b, a
+        second such tensor, as its work array (overwritten with the field) and
+        does not read u.  The population current takes the fluid's velocity u
+        (None: at rest) and writes the field to b if it is given."""
+        if b is None and current == "stencil":
+            raise ValueError("the stencil current needs b")
+        for name, t in (("F_out", F_out), ("b", b)):
+            if t is not None:
+                self._check_out(name, t)
+        if b is not None and b.data_ptr() == F_out.data_ptr():
+            raise ValueError("b and F_out are the same tensor")
         self._check(self.lib.cmlbm_mhd_fields(self.handle, _ptr(self._vec(u)), CURRENT[current], _ptr(b), None,
                                               _ptr(F_out), self._stream()), "fields")
+
+    def _check_out(self, name, t):
+        """t is a tensor that the kernels can write 3N values to."""
+        here = t.device.type == self.device.type and self.device.index in (None, t.device.index)
+        if not (here and t.is_contiguous() and t.dtype == self.dtype and t.numel() == 3 * int(np.prod(self.shape))):
+            raise ValueError(f"{name} must be a contiguous {self.dtype} tensor of 3N values on {self.device}")
 
     def populations(self):
         out = self.torch.empty((7, 3) + self.shape, dtype=self.torch.float64, device=self.device)

@@ -31,3 +31,49 @@ def test_stencil_current_chosen_after_the_first_step():
     for current, _, b in seen:
         if current == "stencil":
             assert b.shape == (3,) + SHAPE and b.dtype == S.dtype and b.is_contiguous()
+
+
+def lattice(cls, **attrs):
+    lat = cls.__new__(cls)
+    lat.torch, lat.dtype, lat.shape, lat.device, lat.handle = torch, torch.float64, SHAPE, torch.device("cpu"), None
+    vars(lat).update(attrs)
+    return lat
+
+
+def reached(lat):
+    """Stand-ins for the library: a call that passes the checks ends here."""
+    def call(*args):
+        raise RuntimeError("reached the library")
+    names = ("cmlbm_mhd_fields", "cmlbm_step_velocity")
+    lat.lib, lat._stream = SimpleNamespace(**{n: call for n in names}), lambda: None
+    return lat
+
+
+def vec(*shape, dtype=torch.float64):
+    return torch.zeros(shape or (3,) + SHAPE, dtype=dtype)
+
+
+@pytest.mark.parametrize("kw", [dict(b=None), dict(b=vec(3, 4, 6, 4)), dict(b=vec(dtype=torch.float32)),
+                                dict(b=vec(3, 8, 6, 4).permute(0, 3, 2, 1)), dict(b=vec().to("meta")),
+                                dict(b=vec(), F_out=vec(3, 4, 6, 4)), dict(b=vec(), F_out=vec(dtype=torch.float32)),
+                                dict(b=vec(), F_out=vec().to("meta")), dict(b="F_out"),
+                                dict(current="populations", b=vec(1, 4, 6, 8))],
+                         ids=["none", "small", "fp32", "strided", "device", "small_F", "fp32_F", "device_F", "same",
+                              "populations"])
+def test_lorentz_force_refuses_work_arrays_that_the_kernels_would_overrun(kw):
+    from paper_1905_10182_amd.mhd import MagneticLattice
+    mag = reached(lattice(MagneticLattice))
+    kw = dict(dict(F_out=vec(), current="stencil"), **kw)
+    if isinstance(kw["b"], str):
+        kw["b"] = kw["F_out"]
+    with pytest.raises(ValueError):
+        mag.lorentz_force(**kw)
+
+
+def test_lorentz_force_takes_what_the_library_takes():
+    from paper_1905_10182_amd.mhd import MagneticLattice
+    mag = reached(lattice(MagneticLattice))
+    for kw in (dict(current="stencil", b=vec()), dict(current="stencil", b=vec(3, 1, *SHAPE)), dict(),
+               dict(u=vec()), dict(u=vec(), b=vec())):
+        with pytest.raises(RuntimeError, match="reached the library"):
+            mag.lorentz_force(vec(3, 1, *SHAPE), **kw)
