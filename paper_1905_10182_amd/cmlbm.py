@@ -293,6 +293,8 @@ class Lattice:
         contiguous (3, nbatch, nz, ny, nx) FP64 or FP32 tensor (returned)."""
         assert out.is_contiguous() and tuple(out.shape) == (3,) + self.shape
         assert out.dtype in (self.torch.float64, self.torch.float32)
+        if out.device.type != self.device.type or self.device.index not in (None, out.device.index):
+            raise ValueError(f"out must be on {self.device}")
         io = FP64 if out.dtype == self.torch.float64 else FP32
         self._check(self.lib.cmlbm_step_velocity(self.handle, _ptr(out), io, self._stream()), "step_velocity")
         return out

@@ -77,3 +77,20 @@ def test_lorentz_force_takes_what_the_library_takes():
                dict(u=vec()), dict(u=vec(), b=vec())):
         with pytest.raises(RuntimeError, match="reached the library"):
             mag.lorentz_force(vec(3, 1, *SHAPE), **kw)
+
+
+@pytest.mark.parametrize("out", [vec().to("meta"), vec(3, 4, 6, 8)[..., :7], vec(3, 2, 6, 8), vec(dtype=torch.float16)],
+                         ids=["device", "strided", "small", "fp16"])
+def test_step_velocity_refuses_what_the_kernel_would_overrun(out):
+    from paper_1905_10182_amd import Lattice
+    fluid = reached(lattice(Lattice))
+    with pytest.raises((ValueError, AssertionError)):
+        fluid.step_velocity(out)
+
+
+def test_step_velocity_takes_both_types():
+    from paper_1905_10182_amd import Lattice
+    fluid = reached(lattice(Lattice))
+    for dtype in (torch.float64, torch.float32):
+        with pytest.raises(RuntimeError, match="reached the library"):
+            fluid.step_velocity(vec(dtype=dtype))
