@@ -2060,10 +2060,11 @@ int conv_dispatch(const G& g, const bf16* x, int cin, const bf16* w, const float
         // one pass, so it needs workgroups for three quarters of the CUs to win:
         // 192 -> 25 us against 29 (bricks), 256 -> 24 / 33, 512 -> 20 / 26; at 128
         // it is 11.6 / 10.6 and at 96 22 / 20.  It has 32-bit offsets within a
-        // sample and stores 8 bytes at a time.
-        const long long row_blocks = bricks / 2 * (c16 / 2);
+        // sample and stores 8 bytes at a time; its grid is one-dimensional, and a
+        // launch has fewer than 2^32 work-items.
+        const long long row_blocks = bricks / 2 * (c16 / 2), most_blocks = (1LL << 32) / 256 - 1;
         const bool rows32 = g.nvox / g.n * 2 * (cin > cout ? cin : cout) < (long long)kNone;
-        if (g.h % kRH == 0 && row_blocks >= 192 && row_blocks < (1LL << 31) && rows32 && ((uintptr_t)y & 7u) == 0)
+        if (g.h % kRH == 0 && row_blocks >= 192 && row_blocks <= most_blocks && rows32 && ((uintptr_t)y & 7u) == 0)
             return conv_rows_launch<SIGN, ACT>(g, x, cin, w, bias, cout, y, gate, s);
         // One workgroup of k_conv_few runs on a CU (120 KB of LDS).  With one chunk
         // of input channels the brick kernel's several per CU are better in a
@@ -2071,7 +2072,7 @@ int conv_dispatch(const G& g, const bf16* x, int cin, const bf16* w, const float
         // its weight reads cost more than that (486 workgroups, 96 channels: 36.0
         // against 34.2; 720, 64 channels: 46 against 36).
         const long long few_blocks = bricks * (c16 / 2);
-        if ((few_blocks <= 256 || cin > 32) && few_blocks < (1LL << 31) && rows32 && ((uintptr_t)y & 7u) == 0) {
+        if ((few_blocks <= 256 || cin > 32) && few_blocks <= most_blocks && rows32 && ((uintptr_t)y & 7u) == 0) {
             k_conv_few<SIGN, ACT><<<dim3((unsigned)few_blocks), 256, 0, s>>>(g, x, cin, w, bias, cout, y, gate);
             return launched();
         }

@@ -33,7 +33,8 @@ def seen():
     rows = []
     for i in range(R.rec_count()):
         l = R.rec_get(i)[0]
-        name = demangle(l.name, None, None, None).decode().replace("(anonymous namespace)::", "")
+        name = demangle(l.name.replace(b"DF16b", b"s"), None, None, None)  # (no BF16 in older demanglers)
+        name = name.decode().replace("(anonymous namespace)::", "")
         rows.append([name[name.index("k"):name.index("(")].removeprefix("void "), [l.grid.x, l.grid.y, l.grid.z],
                      l.block.x, l.arg[0], l.arg[1]])
     return rows

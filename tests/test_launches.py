@@ -74,3 +74,23 @@ for dims, fail in (((64, 64, 64), 0), ((64, 64, 64), 1), ((64, 64, 64), 3), ((48
     EHIP, ESTATE = -3, -5
     assert codes == [[EHIP, 0, [0] * 4, 0, 0], [EHIP, 1, [ESTATE] * 4, 0, 0], [EHIP, 3, [ESTATE] * 4, 0, 0],
                      [EHIP, 2, [0] * 4, 0, 0]]
+
+
+def conv_launches(cases):
+    """The kernel, grid and block of forward convolutions ((n, d, h, w), input and output channels)."""
+    return launches(f"""
+out = []
+for dims, cin, cout in {cases!r}:
+    g = NN.geom(*dims)
+    rec()
+    assert LN.cmnn_conv3d_fwd(ctypes.byref(g), A, cin, B, None, cout, 0, S, None) == 0
+    out += [r[:3] for r in seen()]
+""")
+
+
+def test_convolution_launches_have_fewer_than_2_to_the_32_work_items():
+    """A launch's extents count work-items in 32 bits.  The calls here fit a
+    288 GiB device (the last: 17 GB in, 275 GB out)."""
+    cases = [((1024, 32, 32, 128), 32, 1024), ((1024, 32, 28, 128), 64, 1024), ((2048, 16, 4, 1024), 64, 1024)]
+    for (kernel, grid, block), case in zip(conv_launches(cases), cases):
+        assert grid[0] * block < 1 << 32, (kernel, case)
