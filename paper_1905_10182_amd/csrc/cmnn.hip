@@ -2066,13 +2066,20 @@ int conv_dispatch(const G& g, const bf16* x, int cin, const bf16* w, const float
         const bool rows32 = g.nvox / g.n * 2 * (cin > cout ? cin : cout) < (long long)kNone;
         if (g.h % kRH == 0 && row_blocks >= 192 && row_blocks <= most_blocks && rows32 && ((uintptr_t)y & 7u) == 0)
             return conv_rows_launch<SIGN, ACT>(g, x, cin, w, bias, cout, y, gate, s);
-        // One workgroup of k_conv_few runs on a CU (120 KB of LDS).  With one chunk
-        // of input channels the brick kernel's several per CU are better in a
-        // second round (288 workgroups, 32 channels: 13.5 us against 15.3); with more,
-        // its weight reads cost more than that (486 workgroups, 96 channels: 36.0
-        // against 34.2; 720, 64 channels: 46 against 36).
+        // One workgroup of k_conv_few runs on a CU (120 KB of LDS).  While 256 of
+        // them take all there is to do, it wins over the brick kernel (us, bricks /
+        // this: 192 workgroups 32 -> 32 channels 9.2 / 7.5, 96 -> 96 18.5 / 14.2), but
+        // not with one chunk of input channels for at most 128 workgroups, which
+        // leaves it no weights to load ahead and half the workgroups of 16-channel
+        // bricks (128, 32 -> 64: forward 7.5 / 7.6, data gradient 7.3 / 7.7, gated 7.8 /
+        // 8.6).  In more rounds the several brick workgroups of a CU are better,
+        // unless input channels in 64s make their weight rows whole lines, which
+        // do not stay in L1 (64 -> 64: 768 workgroups 44 / 36, 7168 358 / 278; 128 ->
+        // 128: 14336 1406 / 939; 192 -> 96: 1152 192 / 123; against 96 -> 96: 576 37 /
+        // 43, 10752 481 / 595; 160 -> 64: 768 64 / 68; 32 -> 32: 288 13.5 / 15.3).
         const long long few_blocks = bricks * (c16 / 2);
-        if ((few_blocks <= 256 || cin > 32) && few_blocks <= most_blocks && rows32 && ((uintptr_t)y & 7u) == 0) {
+        const bool few = few_blocks <= 256 ? cin > 32 || few_blocks > 128 : cin % 64 == 0;
+        if (few && few_blocks <= most_blocks && rows32 && ((uintptr_t)y & 7u) == 0) {
             k_conv_few<SIGN, ACT><<<dim3((unsigned)few_blocks), 256, 0, s>>>(g, x, cin, w, bias, cout, y, gate);
             return launched();
         }

@@ -94,3 +94,29 @@ def test_convolution_launches_have_fewer_than_2_to_the_32_work_items():
     cases = [((1024, 32, 32, 128), 32, 1024), ((1024, 32, 28, 128), 64, 1024), ((2048, 16, 4, 1024), 64, 1024)]
     for (kernel, grid, block), case in zip(conv_launches(cases), cases):
         assert grid[0] * block < 1 << 32, (kernel, case)
+
+
+# (n, d, h, w), input and output channels, kernel: both sides of every line of the dispatch's rule
+CONV_ROUTES = [
+    ((2, 3, 5, 7), 32, 64, "k_conv_fwd<4"), ((1, 4, 6, 16), 32, 96, "k_conv_fwd<2"),    # no bricks
+    ((192, 4, 8, 16), 32, 32, "k_conv_rows"), ((191, 4, 8, 16), 64, 32, "k_conv_few"),  # 192 row workgroups
+    ((16, 8, 8, 16), 32, 64, "k_conv_tile<1"), ((16, 8, 12, 16), 32, 64, "k_conv_few"),  # one chunk: 128, 192 workgroups
+    ((64, 8, 4, 16), 96, 64, "k_conv_few"), ((65, 8, 4, 16), 96, 64, "k_conv_tile<2"),  # 256, 260 workgroups
+    ((65, 8, 4, 16), 64, 64, "k_conv_few"), ((16, 32, 28, 64), 128, 128, "k_conv_few"),  # whole lines of weights
+    ((16, 32, 28, 64), 32, 32, "k_conv_tile<2"), ((16, 32, 28, 64), 96, 64, "k_conv_tile<4"),
+    ((16, 32, 28, 64), 32, 96, "k_conv_tile<6"), ((16, 32, 28, 64), 96, 192, "k_conv_tile<6"),
+]
+
+
+# the large batches and the small ones of test_gpu_conv_routes.py
+CONV_ROUTES += [
+    ((32, 16, 4, 64), 32, 64, "k_conv_tile<4"), ((1, 16, 4, 64), 32, 64, "k_conv_tile<1"),
+    ((33, 16, 4, 64), 96, 96, "k_conv_tile<6"), ((2, 16, 4, 64), 96, 96, "k_conv_few"),
+    ((1, 4, 4, 16), 64, 32, "k_conv_few"), ((4, 8, 12, 16), 32, 64, "k_conv_tile<1"),
+]
+
+
+def test_convolution_kernels_by_size():
+    got = conv_launches([c[:3] for c in CONV_ROUTES])
+    for (kernel, *_), case in zip(got, CONV_ROUTES):
+        assert kernel.startswith(case[3]), (kernel, case)
