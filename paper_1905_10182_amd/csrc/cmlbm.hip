@@ -787,10 +787,11 @@ __global__ __launch_bounds__(step_block(ST, MASK)) void k_step(const typename st
 // cell update is k_step's, so K steps give the bits of K launches of k_step.
 // Stages are unrolled: with one looped stage and a fixed cell per thread the
 // later stages run half-empty waves and a step takes 3 to 15% longer.
-// us a step, k_step / 3 steps on 4 x 4 x 4 tiles / 2 on 8 x 4 x 2: FP64 with
-// walls 32 x 16 x 16 5.8 / 3.8 / 4.0, FP64 32 x 16 x 16 6.5 / 3.4 / 3.5, 32 x 32 x
-// 16 6.9 / 4.1 / 4.4, 32^3 7.2 / 7.2 / 5.3, 48 x 40 x 40 10.2 / 16 / 11.2; FP32
-// 32 x 16 x 16 5.4 / 2.8 / 3.2, 32^3 4.8 / 4.5 / 4.7, 48 x 40 x 40 6.6 / 10.1 / 9.0.
+// us a step, k_step / 3 steps on 4 x 4 x 4 tiles / 2 on 8 x 4 x 2: FP64 32 x 16 x 16
+// with walls 5.5 / 3.8 / 3.8, 24^3 5.2 / 4.0 / 4.4, 32 x 32 x 16 4.8 / 4.1 / 4.4, 32^3
+// 5.1 / 7.1 / 5.3 and with walls 5.7 / 7.8 / 6.0, 8 x 60 x 60 14.4 / 7.2 / 4.9; FP32
+// 24^3 4.2 / 3.9 / 4.1, 32 x 32 x 16 4.2 / 3.6 / 4.0, 32^3 4.3 / 4.5 / 4.7, 8 x 60 x 60
+// 8.8 / 5.9 / 4.8.
 template <int K, int CX, int CY, int CZ>
 struct TileBox {
     static constexpr int x = CX + 2 * (K - 1), y = CY + 2 * (K - 1), z = CZ + 2 * (K - 1), cells = x * y * z;
@@ -2301,9 +2302,10 @@ void launch_tile_t(cmlbm_lattice* lat, hipStream_t s)
 
 // How many of n steps one launch of k_tile takes (0: none).  The tile's halo
 // makes it do 4.1 (three steps) or 2.4 (two) collisions per cell and step, so
-// it pays only while the workgroups fit the chip at once: one per CU for three
-// FP64 steps (110 KB of LDS each), else two (k_tile's figures: FP64 32^3, 512
-// workgroups, 7.2 us a step by threes, 5.3 by twos, 7.2 by k_step).  A halo
+// it pays only while every workgroup has a CU of its own; two steps at a time
+// also with two workgroups a CU where k_step's waves are mostly idle lanes:
+// rows so short that they make two waves a SIMD all the same (k_tile's figures:
+// 32^3, 512 tiles and 1024 waves, against 8 x 60 x 60, 450 and 3600).  A halo
 // cell wraps around an axis once: no axis shorter than a tile and its halo.
 int tile_steps(const cmlbm_lattice* lat, int n)
 {
@@ -2313,8 +2315,9 @@ int tile_steps(const cmlbm_lattice* lat, int n)
     if (g.nx < 8 || g.ny < 8 || g.nz < 8) return 0;
     const uint64_t cus = lat->cus > 0 ? lat->cus : 256;
     const uint64_t t3 = tile_count<3, 4, 4, 4>(g), t2 = tile_count<2, 8, 4, 2>(g);
-    if (n >= 3 && t3 <= (f64 ? cus : 2 * cus)) return 3;
-    return t2 <= 2 * cus ? 2 : 0;
+    if (n >= 3 && t3 <= cus) return 3;
+    const uint64_t waves = (uint64_t)g.rows * (uint64_t)((g.nx + 63) / 64);
+    return t2 <= cus || (t2 <= 2 * cus && waves >= 8 * cus) ? 2 : 0;
 }
 
 // Whether s is being captured into a graph (the null stream cannot be).

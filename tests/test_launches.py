@@ -120,3 +120,34 @@ def test_convolution_kernels_by_size():
     got = conv_launches([c[:3] for c in CONV_ROUTES])
     for (kernel, *_), case in zip(got, CONV_ROUTES):
         assert kernel.startswith(case[3]), (kernel, case)
+
+
+def box_launches(cases):
+    """Per case ((nx, ny, nz, nbatch), storage, wall, field, steps): the kernels of one call."""
+    return launches(f"""
+out = []
+for dims, storage, wall, field, n in {cases!r}:
+    h = handle3(*dims, storage=storage, wall=wall, field=field)
+    rec()
+    assert L3.cmlbm_step(h, n, None) == 0
+    out.append([r[0] for r in seen()])
+""")
+
+
+# three steps a launch up to a workgroup a CU; two up to that, and up to two workgroups a CU on rows
+# too short for k_step; one beyond
+TILE_ROUTES = [
+    ((32, 32, 16, 1), 5, ["k_tile 3", "k_tile 2"]), ((32, 32, 20, 1), 5, ["k_step"] * 5),
+    ((32, 32, 32, 1), 3, ["k_step"] * 3), ((8, 60, 60, 1), 5, ["k_tile 2", "k_tile 2", "k_step"]),
+    ((8, 9, 8, 30), 3, ["k_tile 2", "k_step"]), ((9, 11, 13, 2), 7, ["k_tile 3", "k_tile 3", "k_step"]),
+    ((7, 8, 8, 1), 3, ["k_step"] * 3), ((8, 8, 8, 1), 1, ["k_step"]),
+]
+
+
+@pytest.mark.parametrize("storage", ["fp64", "fp32"])
+@pytest.mark.parametrize("wall", [0, 1])
+def test_kernels_of_small_lattices_by_size(storage, wall):
+    got = box_launches([(dims, storage, wall, 0, n) for dims, n, _ in TILE_ROUTES])
+    for kernels, (dims, n, want) in zip(got, TILE_ROUTES):
+        short = [k.split("<")[0] + (" " + k.split(", ")[1] if k.startswith("k_tile") else "") for k in kernels]
+        assert short == want, (dims, n)
