@@ -2338,16 +2338,21 @@ int launch_tile(cmlbm_lattice* lat, int k, hipStream_t s)
 }
 
 // Whether a call of n steps goes through the nine numbers: where its first,
-// inner and last steps are estimated to take less than n steps of k_step.
-// k_step moves 54 numbers per cell at about 5.4 TB/s, a lane without a cell
-// costs it as much as one with FP32 numbers, and it takes 6.5 us at the least;
-// an inner step takes the rounds of its workgroups, each zc + 3 planes
-// of 2.6 us (FP32), 3.3 us (FP64) or 3.6 us (FP64 with a link mask); the first
-// and the last step move 36 numbers.  Measured, k_step against an inner step:
-// FP32 32^3 7.4 / 9.7 us, 64^3 13.2 / 11.9, 96^3 37.3 / 23.0, 128^3 81.6 /
-// 46.4, 256^3 649 / 297, 512^3 5250 / 2240; FP64 32^3 7.2 / 11.8, 64^3 22.6 /
-// 15.6, 128^3 162 / 75, 256^3 1320 / 510; FP64 with walls 32 x 16 x 16 5.7 /
-// 12.7, 64^3 21.7 / 17.6, 64 members of 64 x 32 x 32 322 / 140.
+// inner and last steps are estimated to take less than n steps of k_step, by
+// figures fitted to 8 x 82 lattices (FP32 and FP64, with and without walls and a
+// force field) from 16^2 x 8 to 256^3.
+// k_step moves the 128-byte lines of 27 rows each way at 4.9 TB/s; FP64 pays 32
+// ps a lane, with a cell or not; a step takes 6.5 us at the least.  An inner step
+// takes the rounds of its workgroups, each of zc + 3 planes of 2.5 us (FP32, and
+// 0.1 each for walls and a field; tiles narrower than 64 cells as little as
+// 0.62 of that) or, FP64, 3.3 us, 3.85 with a link mask, 5.3 with a mask and a
+// field (its registers do not hold both: scratch), narrow tiles 0.9.  The first
+// step moves 36 numbers and the last costs 1.4 inner ones (FP32), 1.15 (FP64) or
+// 1.8 (FP64 with a mask).
+// k_step against an inner step, us: FP32 64^3 12.1 / 12.7, 80^3 26 / 21, 128^3 81 /
+// 46, 256^3 649 / 297, 8 x 320 x 320 172 / 80; FP64 64^3 22 / 16, 128^3 160 / 74, 256^3
+// 1320 / 510, 8 x 320 x 320 190 / 156; with walls 64^3 21.6 / 17.8, 20 x 100 x 300 69 /
+// 66; with walls and a field 64^3 22 / 23.4, 96^3 68 / 69, 128^3 166 / 100.
 bool marches(cmlbm_lattice* lat, int n)
 {
     const Geom& g = lat->g;
@@ -2359,10 +2364,16 @@ bool marches(cmlbm_lattice* lat, int n)
     const int TY = march_rows(f64, g.ny), zc = march_zc(lat, TY);
     const uint64_t wgs = march_cols(g, TY) * (uint64_t)((g.nz + zc - 1) / zc), cap = lat->cus > 0 ? lat->cus : 256;
     if (wgs * (uint64_t)(TY + 3) * 64 > 0xffffffffULL) return false;  // work-items of a launch
+    const double lines = (double)g.rows * (double)((g.nx * elem + 127) / 128 * 128) * 54;
     const double lanes = (double)g.rows * ((g.nx + 63) / 64 * 64);
-    const double step = std::max({6.5, 54.0 * elem * (double)g.ncell / 5.4e6, 54.0 * 4 * lanes / 5.4e6});
-    const double inner = (double)((wgs + cap - 1) / cap) * (zc + 3) * (!f64 ? 2.6 : lat->needs_mask ? 3.6 : 3.3);
-    return n * step > 0.75 * step + (n - 2) * inner + std::max(1.25 * inner, 0.75 * step);
+    const double step = std::max({6.5, lines / 4.9e6, f64 ? 32e-6 * lanes : 0.0});
+    const bool field = lat->force_mode == CMLBM_FORCE_FIELD, mask = lat->needs_mask;
+    const double width = std::min(g.nx, kMomTX) / (double)kMomTX;
+    const double plane = f64 ? (!mask ? 3.3 : field ? 5.3 : 3.85) * (0.9 + 0.1 * width)
+                             : (2.5 + 0.1 * field + 0.1 * mask) * (0.62 + 0.38 * width);
+    const double inner = (double)((wgs + cap - 1) / cap) * (zc + 3) * plane;
+    const double last = inner * (!f64 ? 1.4 : mask ? 1.8 : 1.15);
+    return n * step > 0.75 * step + (n - 2) * inner + last;
 }
 
 int launch_step(cmlbm_lattice* lat, hipStream_t s)

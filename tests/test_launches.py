@@ -151,3 +151,28 @@ def test_kernels_of_small_lattices_by_size(storage, wall):
     for kernels, (dims, n, want) in zip(got, TILE_ROUTES):
         short = [k.split("<")[0] + (" " + k.split(", ")[1] if k.startswith("k_tile") else "") for k in kernels]
         assert short == want, (dims, n)
+
+
+# (nx, ny, nz, nbatch), storage, wall, field, steps; whether the call goes through the nine numbers
+MARCH_ROUTES = [
+    ((64, 64, 64, 1), "fp64", 1, 0, 2, False), ((64, 64, 64, 1), "fp64", 1, 0, 10, True),
+    ((64, 64, 64, 1), "fp64", 1, 1, 10, False), ((128, 128, 128, 1), "fp64", 1, 1, 3, True),
+    ((80, 80, 80, 1), "fp64", 1, 1, 10, False), ((80, 80, 80, 1), "fp64", 0, 1, 2, True),
+    ((8, 320, 320, 1), "fp64", 1, 1, 10, False), ((8, 320, 320, 1), "fp64", 0, 0, 2, True),
+    ((16, 256, 256, 1), "fp64", 1, 0, 2, False), ((16, 256, 256, 1), "fp32", 1, 1, 2, True),
+    ((64, 64, 64, 1), "fp32", 0, 0, 10, False), ((80, 80, 80, 1), "fp32", 1, 1, 2, True),
+    ((5, 11, 40, 512), "fp64", 0, 0, 10, False), ((5, 11, 40, 64), "fp32", 0, 1, 2, False),
+    ((256, 256, 256, 1), "fp32", 1, 1, 2, True), ((256, 256, 256, 1), "fp64", 1, 1, 2, True),
+]
+
+
+def test_moment_path_by_size():
+    got = box_launches([c[:5] for c in MARCH_ROUTES])
+    for kernels, (*case, march) in zip(got, MARCH_ROUTES):
+        n = case[-1]
+        if march:
+            assert kernels[0].startswith("k_step<") and kernels[0].endswith(", 1>"), case  # nine numbers out
+            assert all(k.startswith("k_march<") for k in kernels[1:]), case
+            assert [k.endswith("true>") for k in kernels[1:]] == [False] * (n - 2) + [True], case  # populations last
+        else:
+            assert len(kernels) == n and all(k.startswith("k_step<") for k in kernels), case
