@@ -1767,7 +1767,8 @@ struct cmlbm_lattice {
     int cu_per_xcd;  // compute units per XCD of the lattice's device (the moment kernel's generation size)
     int cus;         // compute units of the lattice's device (0 if unknown)
     int psi_zc;      // z chunk of the pseudo-potential tiles (0 until the first launch)
-    int march_zc;    // z chunk of k_march (0 until the first call that could use it)
+    int march_zc;    // z chunk of k_march (0 until the first call that could use it),
+    int march_ty;    // and the interior rows of its tiles
     std::string err;
 };
 
@@ -2125,29 +2126,30 @@ int launch_step_red(cmlbm_lattice* lat, hipStream_t s)
     }
 }
 
-// Interior rows of k_march's tiles: FP32 12 (15 waves), or 6 on lattices of
-// fewer than 24 rows; FP64 8, the most whose 11 waves (three on a SIMD) leave
-// a lane the 168 registers it takes.
-int march_rows(bool f64, int ny) { return f64 ? 8 : ny >= 24 ? 12 : 6; }
-
-// Planes per workgroup of k_march: the fewest rounds of workgroups over the
-// CUs, each costing its planes, two halo planes and a start.
+// Columns of k_march's workgroups, and what a launch with chunks of zc planes
+// costs: the rounds of workgroups over the CUs, each of its planes, two halo
+// planes and a start.
 uint64_t march_cols(const Geom& g, int TY)
 {
     return (uint64_t)((g.nx + kMomTX - 1) / kMomTX) * (uint64_t)((g.ny + TY - 1) / TY) * g.nb;
 }
 
+uint64_t march_cost(const Geom& g, int TY, int zc, int cus)
+{
+    const uint64_t cap = cus > 0 ? (uint64_t)cus : 256;
+    return ((march_cols(g, TY) * (uint64_t)((g.nz + zc - 1) / zc) + cap - 1) / cap) * (uint64_t)(zc + 3);
+}
+
+// Planes per workgroup of k_march: the least cost.
 int march_chunk(const Geom& g, int TY, int cus)
 {
-    const uint64_t cols = march_cols(g, TY);
-    const uint64_t cap = cus > 0 ? (uint64_t)cus : 256;
     int best = g.nz;
     uint64_t best_cost = ~0ULL;
     for (int n = 1; n <= g.nz; ++n) {
         const int zc = (g.nz + n - 1) / n;
         if ((g.nz + zc - 1) / zc != n) continue;
-        if (cols * n * (uint64_t)(TY + 3) * 64 > 0xffffffffULL) break;  // work-items of a launch
-        const uint64_t cost = ((cols * n + cap - 1) / cap) * (uint64_t)(zc + 3);
+        if (march_cols(g, TY) * n * (uint64_t)(TY + 3) * 64 > 0xffffffffULL) break;  // work-items of a launch
+        const uint64_t cost = march_cost(g, TY, zc, cus);
         if (cost < best_cost) {
             best_cost = cost;
             best = zc;
@@ -2156,17 +2158,35 @@ int march_chunk(const Geom& g, int TY, int cus)
     return best;
 }
 
-int march_zc(cmlbm_lattice* lat, int TY)
+// Interior rows of k_march's tiles, and the chunk that goes with them: FP64 8
+// rows, the most whose 11 waves (three on a SIMD) leave a lane the 168 registers
+// it takes; FP32 12 (15 waves), or 6 on lattices of fewer than 24 rows and where
+// that costs less, at three quarters of the time a plane: lattices too small
+// to give every CU a tile of 12 (us a step, 12 / 6: 256 x 256 x 1 9.6 / 9.1, 64 x 64 x
+// 16 10.4 / 8.5, 64^3 12.5 / 11.7; not 512 x 512 x 1 18.3 / 20.0, 200 x 200 x 8 16.5 /
+// 17.9, 96^3 23.4 / 24.9).
+void march_plan(cmlbm_lattice* lat)
 {
-    if (!lat->march_zc) lat->march_zc = march_chunk(lat->g, TY, lat->cus);
-    return lat->march_zc;
+    if (lat->march_zc) return;
+    const Geom& g = lat->g;
+    const bool f64 = lat->p.storage == CMLBM_FP64;
+    int TY = f64 ? 8 : g.ny < 24 ? 6 : 12, zc = march_chunk(g, TY, lat->cus);
+    if (TY == 12) {
+        const int zc6 = march_chunk(g, 6, lat->cus);
+        if (3 * march_cost(g, 6, zc6, lat->cus) < 4 * march_cost(g, 12, zc, lat->cus)) {
+            TY = 6;
+            zc = zc6;
+        }
+    }
+    lat->march_ty = TY;
+    lat->march_zc = zc;
 }
 
 template <typename T, int TY, bool FIELD, bool MASK>
 void launch_march_t(cmlbm_lattice* lat, hipStream_t s, bool pout)
 {
     const Geom& g = lat->g;
-    const int zc = march_zc(lat, TY);
+    const int zc = lat->march_zc;
     const int nzc = (g.nz + zc - 1) / zc;
     const int ntx = (g.nx + kMomTX - 1) / kMomTX, nty = (g.ny + TY - 1) / TY;
     dim3 grid((unsigned)(ntx * nty * g.nb * nzc));
@@ -2226,9 +2246,10 @@ void launch_march_ty(cmlbm_lattice* lat, hipStream_t s, bool pout)
 template <typename T>
 int launch_march(cmlbm_lattice* lat, hipStream_t s, bool pout)
 {
+    march_plan(lat);
     if constexpr (sizeof(T) == 8)
         launch_march_ty<T, 8>(lat, s, pout);
-    else if (march_rows(false, lat->g.ny) == 12)
+    else if (lat->march_ty == 12)
         launch_march_ty<T, 12>(lat, s, pout);
     else
         launch_march_ty<T, 6>(lat, s, pout);
@@ -2339,16 +2360,15 @@ int launch_tile(cmlbm_lattice* lat, int k, hipStream_t s)
 
 // Whether a call of n steps goes through the nine numbers: where its first,
 // inner and last steps are estimated to take less than n steps of k_step, by
-// figures fitted to 8 x 82 lattices (FP32 and FP64, with and without walls and a
-// force field) from 16^2 x 8 to 256^3.
+// figures fitted to 97 sizes from 16 x 8 x 8 to 256^3 (FP32 and FP64, with and
+// without walls and a force field).
 // k_step moves the 128-byte lines of 27 rows each way at 4.9 TB/s; FP64 pays 32
 // ps a lane, with a cell or not; a step takes 6.5 us at the least.  An inner step
-// takes the rounds of its workgroups, each of zc + 3 planes of 2.5 us (FP32, and
-// 0.1 each for walls and a field; tiles narrower than 64 cells as little as
-// 0.62 of that) or, FP64, 3.3 us, 3.85 with a link mask, 5.3 with a mask and a
-// field (its registers do not hold both: scratch), narrow tiles 0.9.  The first
-// step moves 36 numbers and the last costs 1.4 inner ones (FP32), 1.15 (FP64) or
-// 1.8 (FP64 with a mask).
+// takes march_cost planes of 2.5 us (FP32; 0.1 more each for walls and a field,
+// 0.8 of that with tiles of 6 rows, down to 0.8 on narrow lattices) or, FP64, 3.3
+// us, 3.85 with a link mask, 5.8 with a mask and a field (its registers do not
+// hold both: scratch), down to 0.9.  The first step moves 36 numbers and the last
+// costs 1.4 inner ones (FP32), 1.15 (FP64) or 1.8 (FP64 with a mask).
 // k_step against an inner step, us: FP32 64^3 12.1 / 12.7, 80^3 26 / 21, 128^3 81 /
 // 46, 256^3 649 / 297, 8 x 320 x 320 172 / 80; FP64 64^3 22 / 16, 128^3 160 / 74, 256^3
 // 1320 / 510, 8 x 320 x 320 190 / 156; with walls 64^3 21.6 / 17.8, 20 x 100 x 300 69 /
@@ -2361,17 +2381,18 @@ bool marches(cmlbm_lattice* lat, int n)
     const uint64_t elem = f64 ? 8 : 4;
     // k_march's offsets within a plane are 32-bit, below its offset of no cell
     if ((uint64_t)g.ny * g.rstride * elem >= 0xffffff00ULL) return false;
-    const int TY = march_rows(f64, g.ny), zc = march_zc(lat, TY);
-    const uint64_t wgs = march_cols(g, TY) * (uint64_t)((g.nz + zc - 1) / zc), cap = lat->cus > 0 ? lat->cus : 256;
+    march_plan(lat);
+    const int TY = lat->march_ty, zc = lat->march_zc;
+    const uint64_t wgs = march_cols(g, TY) * (uint64_t)((g.nz + zc - 1) / zc);
     if (wgs * (uint64_t)(TY + 3) * 64 > 0xffffffffULL) return false;  // work-items of a launch
     const double lines = (double)g.rows * (double)((g.nx * elem + 127) / 128 * 128) * 54;
     const double lanes = (double)g.rows * ((g.nx + 63) / 64 * 64);
     const double step = std::max({6.5, lines / 4.9e6, f64 ? 32e-6 * lanes : 0.0});
     const bool field = lat->force_mode == CMLBM_FORCE_FIELD, mask = lat->needs_mask;
     const double width = std::min(g.nx, kMomTX) / (double)kMomTX;
-    const double plane = f64 ? (!mask ? 3.3 : field ? 5.3 : 3.85) * (0.9 + 0.1 * width)
-                             : (2.5 + 0.1 * field + 0.1 * mask) * (0.62 + 0.38 * width);
-    const double inner = (double)((wgs + cap - 1) / cap) * (zc + 3) * plane;
+    const double plane = f64 ? (!mask ? 3.3 : field ? 5.8 : 3.85) * (0.9 + 0.1 * width)
+                             : (2.5 + 0.1 * field + 0.1 * mask) * (0.8 + 0.2 * width) * (TY == 6 ? 0.8 : 1.0);
+    const double inner = (double)march_cost(g, TY, zc, lat->cus) * plane;
     const double last = inner * (!f64 ? 1.4 : mask ? 1.8 : 1.15);
     return n * step > 0.75 * step + (n - 2) * inner + last;
 }

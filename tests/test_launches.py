@@ -176,3 +176,16 @@ def test_moment_path_by_size():
             assert [k.endswith("true>") for k in kernels[1:]] == [False] * (n - 2) + [True], case  # populations last
         else:
             assert len(kernels) == n and all(k.startswith("k_step<") for k in kernels), case
+
+
+def test_tile_rows_of_the_moment_kernel():
+    """FP64 tiles of 8 rows; FP32 12, or 6 for few rows and for lattices that do
+    not give every CU a tile of 12."""
+    cases = [((256, 256, 1, 1), "mom32", 6), ((64, 64, 64, 1), "mom32", 6), ((64, 64, 16, 1), "mom32", 6),
+             ((512, 512, 1, 1), "mom32", 12), ((200, 200, 8, 1), "mom32", 12), ((96, 96, 96, 1), "mom32", 12),
+             ((256, 256, 256, 1), "mom32", 12), ((96, 20, 96, 8), "mom32", 6), ((64, 32, 32, 16), "fp32", 12),
+             ((64, 32, 32, 16), "fp64", 8)]
+    got = box_launches([(dims, storage, 0, 0, 2) for dims, storage, _ in cases])
+    for kernels, (dims, storage, rows) in zip(got, cases):
+        kind = "double" if storage == "fp64" else "float"
+        assert kernels[1].startswith(f"k_march<{kind}, {rows}, "), (dims, kernels)
