@@ -2160,18 +2160,19 @@ int march_chunk(const Geom& g, int TY, int cus)
 
 // Interior rows of k_march's tiles, and the chunk that goes with them: FP64 8
 // rows, the most whose 11 waves (three on a SIMD) leave a lane the 168 registers
-// it takes; FP32 12 (15 waves), or 6 on lattices of fewer than 24 rows and where
-// that costs less, at three quarters of the time a plane: lattices too small
-// to give every CU a tile of 12 (us a step, 12 / 6: 256 x 256 x 1 9.6 / 9.1, 64 x 64 x
-// 16 10.4 / 8.5, 64^3 12.5 / 11.7; not 512 x 512 x 1 18.3 / 20.0, 200 x 200 x 8 16.5 /
-// 17.9, 96^3 23.4 / 24.9).
+// it takes; FP32 12 (15 waves), or 6 on lattices of fewer than 24 rows, and, in
+// moment storage, where that costs less, at three quarters of the time a plane:
+// lattices too small to give every CU a tile of 12 (us a step, 12 / 6: 256 x 256 x
+// 1 9.6 / 9.1, 64 x 64 x 16 10.4 / 8.5, 64^3 12.5 / 11.7; not 512 x 512 x 1 18.3 / 20.0,
+// 200 x 200 x 8 16.5 / 17.9, 96^3 23.4 / 24.9).  Population storage takes single
+// steps on such lattices, and its last step, 27 numbers out, gains nothing.
 void march_plan(cmlbm_lattice* lat)
 {
     if (lat->march_zc) return;
     const Geom& g = lat->g;
     const bool f64 = lat->p.storage == CMLBM_FP64;
     int TY = f64 ? 8 : g.ny < 24 ? 6 : 12, zc = march_chunk(g, TY, lat->cus);
-    if (TY == 12) {
+    if (TY == 12 && lat->p.storage == CMLBM_MOM32) {
         const int zc6 = march_chunk(g, 6, lat->cus);
         if (3 * march_cost(g, 6, zc6, lat->cus) < 4 * march_cost(g, 12, zc, lat->cus)) {
             TY = 6;
@@ -2360,15 +2361,15 @@ int launch_tile(cmlbm_lattice* lat, int k, hipStream_t s)
 
 // Whether a call of n steps goes through the nine numbers: where its first,
 // inner and last steps are estimated to take less than n steps of k_step, by
-// figures fitted to 97 sizes from 16 x 8 x 8 to 256^3 (FP32 and FP64, with and
+// figures fitted to 85 sizes from 16 x 8 x 8 to 256^3 (FP32 and FP64, with and
 // without walls and a force field).
 // k_step moves the 128-byte lines of 27 rows each way at 4.9 TB/s; FP64 pays 32
 // ps a lane, with a cell or not; a step takes 6.5 us at the least.  An inner step
 // takes march_cost planes of 2.5 us (FP32; 0.1 more each for walls and a field,
-// 0.8 of that with tiles of 6 rows, down to 0.8 on narrow lattices) or, FP64, 3.3
-// us, 3.85 with a link mask, 5.8 with a mask and a field (its registers do not
-// hold both: scratch), down to 0.9.  The first step moves 36 numbers and the last
-// costs 1.4 inner ones (FP32), 1.15 (FP64) or 1.8 (FP64 with a mask).
+// down to 0.62 of that on narrow lattices) or, FP64, 3.3 us, 3.85 with a link
+// mask, 5.8 with a mask and a field (its registers do not hold both: scratch),
+// down to 0.9.  The first step moves 36 numbers and the last costs 1.4 inner ones
+// (FP32), 1.15 (FP64) or 1.8 (FP64 with a mask).
 // k_step against an inner step, us: FP32 64^3 12.1 / 12.7, 80^3 26 / 21, 128^3 81 /
 // 46, 256^3 649 / 297, 8 x 320 x 320 172 / 80; FP64 64^3 22 / 16, 128^3 160 / 74, 256^3
 // 1320 / 510, 8 x 320 x 320 190 / 156; with walls 64^3 21.6 / 17.8, 20 x 100 x 300 69 /
@@ -2391,7 +2392,7 @@ bool marches(cmlbm_lattice* lat, int n)
     const bool field = lat->force_mode == CMLBM_FORCE_FIELD, mask = lat->needs_mask;
     const double width = std::min(g.nx, kMomTX) / (double)kMomTX;
     const double plane = f64 ? (!mask ? 3.3 : field ? 5.8 : 3.85) * (0.9 + 0.1 * width)
-                             : (2.5 + 0.1 * field + 0.1 * mask) * (0.8 + 0.2 * width) * (TY == 6 ? 0.8 : 1.0);
+                             : (2.5 + 0.1 * field + 0.1 * mask) * (0.62 + 0.38 * width);
     const double inner = (double)march_cost(g, TY, zc, lat->cus) * plane;
     const double last = inner * (!f64 ? 1.4 : mask ? 1.8 : 1.15);
     return n * step > 0.75 * step + (n - 2) * inner + last;

@@ -189,3 +189,10 @@ def test_tile_rows_of_the_moment_kernel():
     for kernels, (dims, storage, rows) in zip(got, cases):
         kind = "double" if storage == "fp64" else "float"
         assert kernels[1].startswith(f"k_march<{kind}, {rows}, "), (dims, kernels)
+
+
+def test_population_storage_keeps_its_tile_rows():
+    """The choice of 6 rows on small lattices is moment storage's: 65^3 in FP32
+    takes tiles of 12 (183 us for ten steps; with tiles of 6 not chosen, 195)."""
+    (kernels,) = box_launches([((65, 65, 65, 1), "fp32", 0, 0, 10)])
+    assert kernels[1].startswith("k_march<float, 12, ")
