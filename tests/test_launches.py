@@ -138,8 +138,8 @@ for dims, storage, wall, field, n in {cases!r}:
 # too short for k_step; one beyond
 TILE_ROUTES = [
     ((32, 32, 16, 1), 5, ["k_tile 3", "k_tile 2"]), ((32, 32, 20, 1), 5, ["k_step"] * 5),
-    ((32, 32, 32, 1), 3, ["k_step"] * 3), ((8, 60, 60, 1), 5, ["k_tile 2", "k_tile 2", "k_step"]),
-    ((8, 9, 8, 30), 3, ["k_tile 2", "k_step"]), ((9, 11, 13, 2), 7, ["k_tile 3", "k_tile 3", "k_step"]),
+    ((32, 32, 32, 1), 3, ["k_step"] * 3), ((8, 60, 60, 1), 5, ["k_tile 2", "k_tile 3"]),
+    ((8, 9, 8, 30), 3, ["k_tile 3"]), ((8, 9, 8, 30), 6, ["k_tile 2", "k_tile 2", "k_tile 2"]), ((9, 11, 13, 2), 7, ["k_tile 3", "k_tile 3", "k_step"]),
     ((7, 8, 8, 1), 3, ["k_step"] * 3), ((8, 8, 8, 1), 1, ["k_step"]),
 ]
 
