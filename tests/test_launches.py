@@ -196,3 +196,49 @@ def test_population_storage_keeps_its_tile_rows():
     takes tiles of 12 (183 us for ten steps; with tiles of 6 not chosen, 195)."""
     (kernels,) = box_launches([((65, 65, 65, 1), "fp32", 0, 0, 10)])
     assert kernels[1].startswith("k_march<float, 12, ")
+
+
+def test_lattices_of_the_schedule_tests_take_the_moment_path():
+    """Of test_gpu_march_schedule.py: every kind of lattice, and the blocked order,
+    whose grid is rounded up beyond the tiles, on the first two."""
+    blocked = {"fp64": (120, 122, 6, 66), "fp32": (120, 190, 6, 66)}
+    tiles = {"fp64": 2 * 16 * 66, "fp32": 2 * 16 * 66}
+    runs = launches(f"""
+out = []
+for storage, dims in list({blocked!r}.items()) + [(s, (40, 60, 40, 8)) for s in ("fp64", "fp32")]:
+    for wall in (0, 1):
+        for field in (0, 1):
+            for n in (6, 7):
+                h = handle3(*dims, storage=storage, wall=wall, field=field)
+                rec()
+                assert L3.cmlbm_step(h, n, None) == 0
+                out.append([storage, list(dims), n, seen()])
+""")
+    for storage, dims, n, rows in runs:
+        assert [r[0].split("<")[0] for r in rows] == ["k_step"] + ["k_march"] * (n - 1), (storage, dims)
+        if tuple(dims) == blocked[storage]:
+            assert rows[1][1][0] > tiles[storage] and rows[1][1][0] % 256 == 0
+
+
+def plane_launches(cases):
+    """Per case ((nx, ny), storage, steps): the kernels of one call of the plane solver."""
+    return launches(f"""
+out = []
+for dims, storage, n in {cases!r}:
+    h = handle2(*dims, storage=storage)
+    rec()
+    assert L2.cmlbm2d_step(h, n, None) == 0
+    out.append([r[0] for r in seen()])
+""")
+
+
+def test_planes_of_the_long_pass_tests_take_them():
+    """Of test_gpu_march2d_eight.py and test_gpu_nonfinite.py."""
+    cases = [(d, "fp32", n) for d in ((8192, 1750), (5000, 3750), (128, 70000)) for n in (8, 21)]
+    for kernels in plane_launches(cases):
+        assert any(k.startswith("k2_march<1, 2, 8,") for k in kernels)
+    cases = [((300, 211), 7, "k2_tile"), ((1025, 1100), 4, "k2_march<{}, 1, 4,"), ((4096, 1100), 6, "k2_march<{}, {}, 6,"),
+             ((8192, 1750), 8, "k2_march<{}, {}, 8,")]
+    for storage, st, v in (("fp64", 0, 1), ("fp32", 1, 2)):
+        for kernels, (dims, n, want) in zip(plane_launches([(d, storage, n) for d, n, _ in cases]), cases):
+            assert any(k.startswith(want.format(st, v)) for k in kernels), (dims, storage, kernels)
