@@ -818,14 +818,20 @@ void launch_march_k(cmlbm2d_lattice* lat, hipStream_t s)
                                                                 (T)lat->fu[1], nullptr);
 }
 
-template <int ST, int V>
-void launch_march_v(cmlbm2d_lattice* lat, int K, hipStream_t s)
+// Most steps of a k2_march pass: eight, and six with one FP32 cell a lane, which
+// eight do not make faster (next_pass).
+constexpr int march_most(bool f64, int V) { return f64 || V == 2 ? 8 : 6; }
+
+// One pass of that many steps; false if there is none.
+template <int ST, int V, int K = 2>
+bool launch_march_v(cmlbm2d_lattice* lat, int steps, hipStream_t s)
 {
-    if constexpr (ST == CMLBM2D_FP64 || V == 2) {
-        if (K == 8) return launch_march_k<ST, V, 8>(lat, s);
+    if constexpr (K <= march_most(ST == CMLBM2D_FP64, V)) {
+        if (steps != K) return launch_march_v<ST, V, K + 2>(lat, steps, s);
+        launch_march_k<ST, V, K>(lat, s);
+        return true;
     }
-    if (K == 6) return launch_march_k<ST, V, 6>(lat, s);
-    K == 4 ? launch_march_k<ST, V, 4>(lat, s) : launch_march_k<ST, V, 2>(lat, s);
+    return false;
 }
 
 template <int ST>
@@ -884,7 +890,7 @@ Pass next_pass(const cmlbm2d_lattice* lat, int n, int parity)
         if (t < of[K].t) of[K] = Pass{kind, K, V, t};
     };
     const int V = f64 || g.nx % 2 ? 1 : 2;
-    for (int K = 2; K <= (f64 || V == 2 ? 8 : 6); K += 2) {
+    for (int K = 2; K <= march_most(f64, V); K += 2) {
         int w = 1;
         const int rows = march_rows2(g, march_strips(g, V, march_halo(K)), K, &w);
         const double per_row = f64      ? (K == 2 ? 1.45 : K == 4 ? 1.75 : K == 6 ? 2.15 : 2.6)
@@ -931,23 +937,20 @@ bool capturing(hipStream_t s)
 }
 
 template <int ST>
-void launch_pass_st(cmlbm2d_lattice* lat, const Pass& p, hipStream_t s)
+bool launch_pass_st(cmlbm2d_lattice* lat, const Pass& p, hipStream_t s)
 {
-    if (p.kind == Pass::TILE) return launch_tile<ST>(lat, p.steps, s);
+    if (p.kind == Pass::TILE) return launch_tile<ST>(lat, p.steps, s), true;
     if constexpr (ST == CMLBM2D_FP32) {
         if (p.V == 2) return launch_march_v<ST, 2>(lat, p.steps, s);
     }
-    launch_march_v<ST, 1>(lat, p.steps, s);
+    return launch_march_v<ST, 1>(lat, p.steps, s);
 }
 
-void launch_pass(cmlbm2d_lattice* lat, const Pass& p, hipStream_t s)
+bool launch_pass(cmlbm2d_lattice* lat, const Pass& p, hipStream_t s)
 {
-    if (p.kind == Pass::STEP)
-        launch_step(lat, s);
-    else if (lat->p.storage == CMLBM2D_FP64)
-        launch_pass_st<CMLBM2D_FP64>(lat, p, s);
-    else
-        launch_pass_st<CMLBM2D_FP32>(lat, p, s);
+    if (p.kind == Pass::STEP) return launch_step(lat, s), true;
+    if (lat->p.storage == CMLBM2D_FP64) return launch_pass_st<CMLBM2D_FP64>(lat, p, s);
+    return launch_pass_st<CMLBM2D_FP32>(lat, p, s);
 }
 
 template <int ST>
@@ -1103,7 +1106,7 @@ int cmlbm2d_step(cmlbm2d_lattice* lat, int32_t nsteps, void* hip_stream)
     for (int32_t k = 0; k < nsteps;) {
         const Pass p = next_pass(lat, nsteps - k, parity);
         if (parity >= 0 && p.steps % 2 == 0) parity = 1 - parity;
-        launch_pass(lat, p, s);
+        if (!launch_pass(lat, p, s)) return fail(lat, CMLBM2D_EINVAL, "no kernel for a pass of these steps");
         const int rc = launch_check(lat, "step");
         if (rc) return rc;
         lat->cur = 1 - lat->cur;

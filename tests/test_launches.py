@@ -242,3 +242,26 @@ def test_planes_of_the_long_pass_tests_take_them():
     for storage, st, v in (("fp64", 0, 1), ("fp32", 1, 2)):
         for kernels, (dims, n, want) in zip(plane_launches([(d, storage, n) for d, n, _ in cases]), cases):
             assert any(k.startswith(want.format(st, v)) for k in kernels), (dims, storage, kernels)
+
+
+def test_passes_take_the_steps_that_they_count():
+    """Every k2_march launch is the kernel of as many steps as the call advances by,
+    on odd rows (one FP32 cell a lane, six at most) too."""
+    dims = [(3001, 1500), (5001, 3750), (8191, 2048), (4096, 1100), (1025, 1100), (129, 70000)]
+    runs = launches(f"""
+out = []
+for dims in {dims!r}:
+    for storage in ("fp64", "fp32"):
+        h = handle2(*dims, storage=storage)
+        for n in (2, 4, 6, 8, 16, 40):
+            rec()
+            assert L2.cmlbm2d_step(h, n, None) == 0
+            out.append([dims, storage, n, [r[0] for r in seen()]])
+""")
+    for dims, storage, n, kernels in runs:
+        if any(k.startswith("k2_tile") for k in kernels):
+            continue
+        steps = [int(k.split(", ")[2]) if k.startswith("k2_march") else 1 for k in kernels]
+        assert sum(steps) == n, (dims, storage, kernels)
+        if storage == "fp32" and dims[0] % 2:
+            assert max(steps) <= 6
