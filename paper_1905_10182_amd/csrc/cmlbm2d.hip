@@ -652,6 +652,7 @@ struct cmlbm2d_lattice {
     Geom2 g;
     void* pop[2];
     int cur;  // buffer holding the state
+    int cus;  // compute units of the lattice's device
     int force_mode;
     double fu[2];  // UNIFORM force
     const void* field;
@@ -741,12 +742,13 @@ constexpr int march_waves(int K) { return K >= 6 ? 2 : K == 4 ? 3 : 4; }
 // Rows per wave of k2_march, and the waves that a SIMD then runs: the least of
 // that number (a SIMD is bound by their instructions) times the rows of each
 // and the 2 K it starts and ends with.
-int march_rows2(const Geom2& g, int strips, int K, int* waves_per_simd)
+int march_rows2(const Geom2& g, int strips, int K, int cus, int* waves_per_simd)
 {
-    int best = g.ny, best_w = (strips + 1023) / 1024;
+    const int simds = 4 * cus;
+    int best = g.ny, best_w = (strips + simds - 1) / simds;
     uint64_t best_cost = (uint64_t)best_w * (uint64_t)(g.ny + 2 * K);
     for (int w = 1; w <= march_waves(K); ++w) {
-        const int n = std::min(g.ny, 1024 * w / strips);
+        const int n = std::min(g.ny, simds * w / strips);
         if (n < 1) continue;
         const int rows = (g.ny + n - 1) / n;
         const uint64_t cost = (uint64_t)w * (uint64_t)(rows + 2 * K);
@@ -804,7 +806,7 @@ void launch_march_k(cmlbm2d_lattice* lat, hipStream_t s)
 {
     using T = typename storage2<ST>::T;
     const Geom2& g = lat->g;
-    const int strips = march_strips(g, V, march_halo(K)), rows = march_rows2(g, strips, K, nullptr);
+    const int strips = march_strips(g, V, march_halo(K)), rows = march_rows2(g, strips, K, lat->cus, nullptr);
     const uint64_t waves = (uint64_t)strips * (uint64_t)((g.ny + rows - 1) / rows);
     const dim3 grid((unsigned)((waves + kBlock / 64 - 1) / (kBlock / 64)));
     const T* src = (const T*)lat->pop[lat->cur];
@@ -862,12 +864,12 @@ struct Pass {
 // The first of the launches that take n steps in the least time, by estimates
 // of each kernel's launch in us (measured, FP64 / FP32; the four-rolls mill on
 // n x n cells):
-//   k2_step   3.0 + 160 (80) bytes per cell at 5.6 TB/s;
+//   k2_step   3.0 + 160 (80) bytes per cell at 5.6 TB/s (by 256 CUs);
 //   k2_march  2.5 + waves per SIMD x (rows + 2 K) x the time of a row: K = 2
 //             1.45 / 1.65 (HBM-bound), 4 1.75 / 2.15, 6 2.15 / 2.95, 8 2.6 / 3.8
 //             (3.4 with two waves); FP32 with one cell a lane 0.97, 1.26, 1.69
 //             and, no better than 6, 2.19;
-//   k2_tile   with x = workgroups / 256: up to 1, 4.6 + 0.59 K + 3.7 x / 3.6 +
+//   k2_tile   with x = workgroups per CU: up to 1, 4.6 + 0.59 K + 3.7 x / 3.6 +
 //             0.53 K + 3.7 x; beyond, 3.5 + 7.5 x / 3.5 + 3.9 x.
 // The best rate decides while many steps are left, the best way to end exactly
 // (6 + 4 for ten steps where 8 + 2 has the better start) over the last sixteen.
@@ -883,7 +885,7 @@ Pass next_pass(const cmlbm2d_lattice* lat, int n, int parity)
     const Geom2& g = lat->g;
     const bool f64 = lat->p.storage == CMLBM2D_FP64;
     Pass of[kMost + 1];  // the fastest launch of k steps
-    of[1] = Pass{Pass::STEP, 1, g.V, 3.0 + (double)g.ncell * (f64 ? 160.0 : 80.0) / 5.6e6};
+    of[1] = Pass{Pass::STEP, 1, g.V, 3.0 + (double)g.ncell * (f64 ? 160.0 : 80.0) / (5.6e6 / 256.0 * lat->cus)};
     if ((!f64 && lat->p.storage != CMLBM2D_FP32) || n < 2) return of[1];
     for (int K = 2; K <= kMost; ++K) of[K] = Pass{Pass::STEP, 0, 1, 1e300};
     auto consider = [&](Pass::Kind kind, int K, int V, double t) {
@@ -892,7 +894,7 @@ Pass next_pass(const cmlbm2d_lattice* lat, int n, int parity)
     const int V = f64 || g.nx % 2 ? 1 : 2;
     for (int K = 2; K <= march_most(f64, V); K += 2) {
         int w = 1;
-        const int rows = march_rows2(g, march_strips(g, V, march_halo(K)), K, &w);
+        const int rows = march_rows2(g, march_strips(g, V, march_halo(K)), K, lat->cus, &w);
         const double per_row = f64      ? (K == 2 ? 1.45 : K == 4 ? 1.75 : K == 6 ? 2.15 : 2.6)
                                : V == 1 ? (K == 2 ? 0.97 : K == 4 ? 1.26 : 1.69)
                                         : (K == 2 ? 1.65 : K == 4 ? 2.15 : K == 6 ? 2.95 : w > 1 ? 3.4 : 3.8);
@@ -900,7 +902,7 @@ Pass next_pass(const cmlbm2d_lattice* lat, int n, int parity)
     }
     for (int K = 2; K <= 7; ++K) {
         const int R = kTileRows - 2 * K;
-        const double x = (double)march_strips(g, 1, K) * ((g.ny + R - 1) / R) / 256.0;
+        const double x = (double)march_strips(g, 1, K) * ((g.ny + R - 1) / R) / lat->cus;
         if (x > 8192) break;  // far beyond its range, and near a launch's work-items
         const double t = x > 1.0 ? 3.5 + (f64 ? 7.5 : 3.9) * x : (f64 ? 4.6 + 0.59 * K : 3.6 + 0.53 * K) + 3.7 * x;
         consider(Pass::TILE, K, 1, t);
@@ -1034,6 +1036,10 @@ int cmlbm2d_create(const cmlbm2d_params* params, void* pop_a, size_t pop_a_bytes
     lat->pop[0] = pop_a;
     lat->pop[1] = pop_b;
     lat->cur = 0;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&lat->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        lat->cus < 1)
+        lat->cus = 256;
     lat->force_mode = CMLBM2D_FORCE_NONE;
     lat->fu[0] = lat->fu[1] = 0.0;
     lat->field = nullptr;

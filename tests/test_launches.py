@@ -265,3 +265,22 @@ for dims in {dims!r}:
         assert sum(steps) == n, (dims, storage, kernels)
         if storage == "fp32" and dims[0] % 2:
             assert max(steps) <= 6
+
+
+@pytest.mark.parametrize("cus", [64, 256])
+def test_plane_passes_are_sized_for_the_compute_units(cus):
+    """k2_march's waves fill the SIMDs of the lattice's device, as many each as its
+    registers leave room for."""
+    runs = launches(f"""
+out = []
+rec(cus={cus})
+for dims in ((4096, 4096), (8192, 8192)):
+    h = handle2(*dims, storage="fp64")
+    rec(cus={cus})
+    assert L2.cmlbm2d_step(h, 8, None) == 0
+    out.append(seen())
+""")
+    for rows in runs:
+        kernel, grid, block = rows[0][:3]
+        assert kernel.startswith("k2_march<0, 1, ")
+        assert grid[0] * block // 64 <= {"2": 4, "4": 3, "6": 2, "8": 2}[kernel.split(", ")[2]] * 4 * cus
