@@ -127,6 +127,7 @@ def alu_roofline(n, glups):
     if v is None:
         return None
     a = v * glups * 1e9
+    # "bound" names the peak of this row; k_march is near the HBM rate of a copy as well
     return {"bound": "alu", "kernel": "k_march", "achieved": round(a / 1e12, 2), "peak": round(VALU_PEAK_LANE_OPS / 1e12, 2),
             "unit": "T lane-op/s", "frac": round(a / VALU_PEAK_LANE_OPS, 4), "valu_lane_ops_per_cell": v}
 
@@ -242,18 +243,19 @@ def precision_legs(n, names, steps, warmup, repeats, error_steps, fields):
 # D2Q9 (App. B model): nine populations read + nine written, plus the force
 # field (two components) read, per cell
 BYTES_PER_CELL_2D = {"fp64": 144 + 16, "fp32": 72 + 8, "fp16": 36 + 8, "bf16": 36 + 8}
-STEP_KERNEL_2D = {"fp64": "k2_march<0, 1, 8, true>", "fp32": "k2_march<1, 2, 8, true>", "fp16": "k2_step<2, 4, true>",
+STEP_KERNEL_2D = {"fp64": "k2_march<0, 1, 6, true>", "fp32": "k2_march<1, 2, 8, true>", "fp16": "k2_step<2, 4, true>",
                   "bf16": "k2_step<3, 4, true>"}
 
 
 def bytes_per_cell_2d(storage, steps):
     """HBM bytes per cell and step of one call of `steps` steps on a large
-    plane: FP64 and FP32 storage take up to eight steps in one pass (ten as
-    six and four), and an odd one by itself."""
+    plane: FP32 storage takes eight steps in most passes and FP64 six, the last
+    few passes of a call as many as end it, and an odd step goes by itself."""
     full = BYTES_PER_CELL_2D[storage]
     if storage not in ("fp64", "fp32"):
         return full
-    return full * ((steps // 2 * 2 + 7) // 8 + steps % 2) / steps
+    most = 8 if storage == "fp32" else 6
+    return full * ((steps // 2 * 2 + most - 1) // most + steps % 2) / steps
 
 
 def run_gpu_2d(n, storage, steps, warmup, repeats):

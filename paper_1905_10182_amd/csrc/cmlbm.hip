@@ -957,7 +957,7 @@ __global__ __launch_bounds__(kBlock) void k_init(typename storage<ST>::S* __rest
 //   of t + 1.
 // CMLBM_MOM32 keeps its state this way.  FP64 and FP32 population storage
 // takes it between the first and the last step of a call (marches()): step 1
-// pulls populations and stores m (k_step with MOUT), the steps between go
+// pulls populations and stores m (k_step with OUT = kOutMoments), the steps between go
 // from m to m, the last one from m to populations (POUT).  The nine numbers
 // are the values that k_step itself holds in registers when it reconstructs,
 // in the storage type, so the populations that come out are the same bits.
@@ -990,14 +990,20 @@ constexpr int march_bufs(int TY)
 //   write 24 populations to LDS, each at the cell it streams to; barrier;
 //   the TY interior waves read what arrived at their cells, reduce each c_z
 //   class to its six in-plane sums, and finish plane p - 1.
-// What bounds it: FP32 the issue of vector instructions, about 440 per cell
-// (a reconstruction for each of the 15 waves of a 12-row tile, a collision for
-// 12); FP64 those and HBM.  Per step against k_step: FP32 256^3 649 -> 297 us
-// (56 G cells/s, 4.1 TB/s), 512^3 5250 -> 2240 us; FP64 256^3 1320 -> 510 us
-// (4.7 TB/s), 64 channels of 64 x 32 x 32 with walls 322 -> 140 us.  Moment
-// storage, whose earlier kernel kept the c_z classes in four LDS slots behind
-// two barriers and waited for its stores before each plane: 256^3 314 -> 304
-// us, 512^3 2380 -> 2200 us.
+// What bounds it: FP32 vector instructions and HBM together.  480 lane-operations
+// per cell at 256^3, 462 at 512^3 (a reconstruction for each of the 15 waves of a
+// 12-row tile, a collision for 12) are issued at 66 and 69% of the rate at 2.4
+// GHz, and 4.2 and 4.9 TB/s are 77 and 90% of a copy's; a tenth fewer
+// instructions gained 3 to 4%.  FP64 HBM (4.7 TB/s).  Per step against k_step:
+// FP32 256^3 649 -> 297 us, 512^3 5250 -> 2240 us; FP64 256^3 1320 -> 510 us, 64
+// channels of 64 x 32 x 32 with walls 322 -> 140 us.  Moment storage, whose earlier
+// kernel kept the c_z classes in four LDS slots behind two barriers and waited
+// for its stores before each plane: 256^3 314 -> 304 us, 512^3 2380 -> 2200 us,
+// 100^3 84 -> 33 us (more workgroups); but one to four planes over more
+// columns than CUs are slower than there, whose two halo planes were not
+// collided (512 x 512 x 1 16.6 -> 18.4 us, 512 x 512 x 4 30.8 -> 34.4, 1024 x 1024 x 1 47
+// -> 56).  Two loops, the first without the finish, gain 1 to 5% of those
+// and lose 2% at 512^3.
 // The z exchange stays in registers: of source plane p, class c_z = -1 goes
 // to target p - 1, 0 to p, +1 to p + 1, so a lane carries the sums of two
 // classes across iterations and every plane is reconstructed once per chunk
@@ -2193,10 +2199,9 @@ void launch_march_t(cmlbm_lattice* lat, hipStream_t s, bool pout)
     dim3 grid((unsigned)(ntx * nty * g.nb * nzc));
     // the blocked schedule when an XCD's generation covers whole tile rows,
     // it takes no more rounds of one workgroup per CU than the plain order,
-    // and each XCD runs at least 8 generations: it starts an XCD's workgroups
-    // together instead of staggered, which measured 2% slower with 3
-    // generations (256^3) and 1.2% faster with 22 (512^3, reads 1.17 -> 1.06x
-    // the algorithmic bytes)
+    // and each XCD runs at least 8 generations.  Moment storage at 512^3, 11
+    // generations: 2143 us against 2174 in the plain order, reads 1.32 against
+    // 1.33 x the algorithmic bytes; FP32 storage there 2435 / 2444 us a step
     const int cpx = lat->cu_per_xcd;
     int gens = 0;
     if (cpx > 0 && cpx % ntx == 0) {

@@ -273,8 +273,8 @@ __global__ __launch_bounds__(kBlock) void k2_step(const typename storage2<ST>::S
 // cells (none where a strip is exactly a periodic row), and a chunk of rows
 // starts and ends K rows outside.
 // What bounds it: K = 2 HBM, 72 bytes per cell (FP32) and 8 with a field, at 5.1
-// TB/s; K = 8 the issue of vector instructions, about 133 per cell and step, 95%
-// of the time.  Per step at 8192^2 with a force field: FP32 k2_step 890, K = 2 524,
+// TB/s; K = 8 the issue of vector instructions, 148 lane-operations per cell and
+// step (the overlap included) at 85% of the rate at 2.4 GHz.  Per step at 8192^2 with a force field: FP32 k2_step 890, K = 2 524,
 // 4 320, 6 299, 8 270 us; FP64 1870, 1100, 592, 518, 489.
 // H: for K = 2, 8 cells make strips of whole 64-byte pieces, where 2 leave each
 // end in pieces that two waves write (FP32 8192^2 1260 -> 1050 us a pass);
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(kBlock, K >= 6 ? 2 : 1) void k2_march(const typenam
     const int ys = chunk * rows, ye = ys + rows < g.ny ? ys + rows : g.ny;
     if (ys >= g.ny) return;  // whole wave
     // cells of this lane: position i0 in the strip, x (periodic); stored are the
-    // positions [K, 64 V - K) of an overlapping strip that lie in the row
+    // positions [H, 64 V - H) of an overlapping strip that lie in the row
     const bool ring = g.nx == 64 * V;
     const int stride = ring ? 64 * V : 64 * V - 2 * H, i0 = lane * V;
     const int xr = strip * stride + i0 - (ring ? 0 : H);
