@@ -68,8 +68,8 @@ COUNTERS_FILE = os.path.join(ROOT, "profiles", "k_step_counters.md")
 MOM_COUNTERS_FILE = os.path.join(ROOT, "profiles", "k_step_mom_tgv_counters.md")
 # non-packed FP32 VALU: 256 CUs x 4 SIMDs x 16 lanes per clock x 2.4 GHz
 VALU_PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_1905_10182_amd", "csrc", f) 
-                  for f in ("cmlbm.hip", "d3q27.hpp", "lockstep.hpp")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_1905_10182_amd", "csrc", f)
+                  for f in ("cmlbm.hip", "d3q27.hpp", "d3q27_collide.inl")]
 ALL_LEGS = ("fp32", "precision", "fp64", "mom", "d2q9", "mhd", "shanchen", "fused", "copy", "conv", "warmstart", "cpu")
 
 

@@ -35,7 +35,6 @@
 
 #include "cmlbm.h"
 #include "d3q27.hpp"
-#include "lockstep.hpp"
 
 using namespace cmlbm;
 
@@ -361,7 +360,7 @@ __device__ __forceinline__ S lane_shift(S v, bool from_prev)
 // the hot path: one fused time step
 //
 // Every cell pulls its 27 populations from x - c_i (eq. "streaming" read
-// backwards), collides in central-moment space (collide() in d3q27.hpp) and
+// backwards), collides in central-moment space (collide() in d3q27_collide.inl) and
 // stores its 27 post-collision populations at its own index with
 // non-temporal stores (they are not read again in this step).
 //
@@ -633,13 +632,13 @@ __global__ __launch_bounds__(step_block(ST, MASK)) void k_step(const typename st
             T drho, k5[5], s5[5];
             const T om1 = T(1) - omega;
             if constexpr (sizeof(S) == 2)
-                pre_collision(h[c], Fx[c], Fy[c], Fz[c], rho0s, drho, ux, uy, uz, k5);
+                joined::pre_collision(h[c], Fx[c], Fy[c], Fz[c], rho0s, drho, ux, uy, uz, k5);
             else
                 lockstep::pre_collision(h[c], Fx[c], Fy[c], Fz[c], rho0s, drho, ux, uy, uz, k5);
 #pragma unroll
             for (int j = 0; j < 5; ++j) s5[j] = om1 * k5[j];
             if constexpr (sizeof(S) == 2)
-                reconstruct(drho, ux, uy, uz, Fx[c], Fy[c], Fz[c], s5, rho0s, h[c]);
+                joined::reconstruct(drho, ux, uy, uz, Fx[c], Fy[c], Fz[c], s5, rho0s, h[c]);
             else
                 lockstep::reconstruct(drho, ux, uy, uz, Fx[c], Fy[c], Fz[c], s5, rho0s, h[c]);
             mq[c][0] = drho;
@@ -657,7 +656,7 @@ __global__ __launch_bounds__(step_block(ST, MASK)) void k_step(const typename st
                            (uint32_t)x0 * (uint32_t)sizeof(S), v[j]);
             return;
         } else if constexpr (MODEL == 0 && sizeof(S) == 2) {
-            collide<T>(h[c], Fx[c], Fy[c], Fz[c], omega, rho0s, rho, ux, uy, uz);
+            joined::collide<T>(h[c], Fx[c], Fy[c], Fz[c], omega, rho0s);
         } else if constexpr (MODEL == 0) {
             lockstep::collide<T>(h[c], Fx[c], Fy[c], Fz[c], omega, rho0s);
         } else {

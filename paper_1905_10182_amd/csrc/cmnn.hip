@@ -405,9 +405,10 @@ __global__ __launch_bounds__(256) void k_conv_tile(G g, const bf16* __restrict__
 // What waits on memory at the start of a workgroup is issued together: the gates
 // and the first row's weights with the halo (forward 65 -> 60 us; all nine
 // weights early, or the gates kept with them, run out of registers: 87 us).
-// 16 x 32 x 32 x 64, 32 -> 32: 91 -> 60 us forward, 81 -> 56 us data gradient
-// (1037 TFLOP/s); 96 -> 32: 220 -> 168 and (32 -> 96) 182 -> 153; 160 -> 64 at
-// half extents: 92 -> 75 and 134 -> 84.
+// us, brick kernel / this, repeated on the same tensors, 16 x 32 x 32 x 64: 32 -> 32
+// forward 77 / 52, data gradient 76 / 50, gated 81 / 57; 96 -> 32 201 / 153; 32 -> 96
+// 187 / 147; 160 -> 64 at half extents 79 / 64 and its data gradient 131 / 78.  In a
+// training step 32 -> 32 takes 59 forward and 61 gated (950 TFLOP/s).
 constexpr int kRH = 8, kRHH = kRH + 2, kRRows = kHD * kRHH;  // 60 halo rows of 18 voxels
 constexpr uint32_t kRRow = kHW * 64;                          // bytes of a halo row
 constexpr int kRParts = kHW * 4;                              // 16-byte parts of a halo row: 72

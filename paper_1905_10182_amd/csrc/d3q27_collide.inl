@@ -1,20 +1,5 @@
-// The per-cell collision of FP64 and FP32 population storage and of moment
-// storage (16-bit population storage keeps the form in d3q27.hpp: its stored
-// values follow every rounding of the arithmetic).
-//
-// The steps of one call pass through kernels of their own (k_step, k_march in
-// cmlbm.hip), and any split of a run into calls gives the same bits.  So the
-// contraction of a multiplication and an addition into one rounding stays
-// within one source expression here (contract(on)): what is fused does not
-// depend on what a function is inlined into.
-#pragma once
-
-#include "d3q27.hpp"
-
-#pragma clang fp contract(on)
-
-namespace cmlbm {
-namespace lockstep {
+// The per-cell collision: included by d3q27.hpp, once per contraction mode and
+// each time in a namespace of its own.
 
 // inv1d with its first- and second-order inputs given at half scale
 // (m1h = m1 / 2, m2h = m2 / 2) and hu = u / 2: with o = (g+ - g-) / 2 and
@@ -184,8 +169,3 @@ __device__ __forceinline__ void collide(T h[27], T Fx, T Fy, T Fz, T omega, T rh
     for (int j = 0; j < 5; ++j) s[j] = om1 * k[j];
     reconstruct(drho, ux, uy, uz, Fx, Fy, Fz, s, rho0, h);
 }
-
-}  // namespace lockstep
-}  // namespace cmlbm
-
-#pragma clang fp contract(fast)
