@@ -185,10 +185,12 @@ int cmlbm_init(cmlbm_lattice* lat, const void* dev_rho, const void* dev_u, int i
  * is split into calls.  The buffer that does not hold the state is scratch.
  * If a launch fails while the state is the nine numbers, it is undefined until
  * the next init or restore (ESTATE).  Only kernels are enqueued, so a call can
- * be captured into a HIP graph; a captured call of an even number of steps ends
- * in the buffer it starts in, and each replay of the graph advances the state
- * by that many (the handle's step counter is advanced at capture, not by
- * replays). */
+ * be captured into a HIP graph, whose replays work on the buffers of the
+ * capture.  From the first call on the handle that is captured on, every
+ * cmlbm_step of an even number of steps ends in the buffer it starts in: each
+ * replay of such a captured call advances the state by that many steps, and so
+ * do calls between replays (the handle's step counter is advanced at capture,
+ * not by replays). */
 int cmlbm_step(cmlbm_lattice* lat, int32_t nsteps, void* hip_stream);
 
 /* One time step (cmlbm_step with nsteps = 1) that also writes the velocity of

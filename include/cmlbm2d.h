@@ -107,8 +107,10 @@ int cmlbm2d_init(cmlbm2d_lattice* lat, const void* dev_rho, const void* dev_u, i
  * launch (chosen by size); the populations after n steps are the same bits
  * however n is split into calls.  The buffer that does not hold the state is
  * scratch.  Only kernels are enqueued, so a call can be captured into a HIP
- * graph; a captured call of an even number of steps ends in the buffer it
- * starts in, and each replay of the graph advances the state by that many (the
+ * graph, whose replays work on the buffers of the capture.  From the first call
+ * on the handle that is captured on, every cmlbm2d_step of an even number of
+ * steps ends in the buffer it starts in: each replay of such a captured call
+ * advances the state by that many steps, and so do calls between replays (the
  * handle's step counter is advanced at capture, not by replays). */
 int cmlbm2d_step(cmlbm2d_lattice* lat, int32_t nsteps, void* hip_stream);
 

@@ -1765,6 +1765,7 @@ struct cmlbm_lattice {
     size_t off_ftab64, off_ftab32, off_mask, off_part, off_final, off_snap, off_wpart;
     int gpb;
     bool needs_mask, mask_ready, initialized, snap_valid;
+    bool graph;  // a call has been captured: even calls end in the buffer they start in
     int force_mode;
     const void* field;
     int field_dtype;
@@ -2350,12 +2351,16 @@ int tile_steps(const cmlbm_lattice* lat, int n)
     return n == 3 && t3 <= 2 * cus ? 3 : 2;
 }
 
-// Whether s is being captured into a graph (the null stream cannot be).
-bool capturing(hipStream_t s)
+// Whether calls on this lattice are in a HIP graph: noted by every entry that
+// reads or writes the state on s (the null stream cannot be captured).
+bool in_graph(cmlbm_lattice* lat, hipStream_t s)
 {
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (s && hipStreamIsCapturing(s, &status) != hipSuccess) (void)hipGetLastError();
-    return status == hipStreamCaptureStatusActive;
+    if (!lat->graph && s) {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &status) != hipSuccess) (void)hipGetLastError();
+        lat->graph = status == hipStreamCaptureStatusActive;
+    }
+    return lat->graph;
 }
 
 int launch_tile(cmlbm_lattice* lat, int k, hipStream_t s)
@@ -2640,6 +2645,7 @@ int cmlbm_create(const cmlbm_params* params, void* pop_a, size_t pop_a_bytes, vo
     lat->mask_ready = false;
     lat->initialized = false;
     lat->snap_valid = false;
+    lat->graph = false;
     lat->force_mode = -1;  // table not yet written
     {
         int dev = 0, cus = 0;
@@ -2737,6 +2743,7 @@ int cmlbm_init(cmlbm_lattice* lat, const void* dev_rho, const void* dev_u, int i
     if (!lat) return CMLBM_EINVAL;
     if (io_dtype != CMLBM_FP64 && io_dtype != CMLBM_FP32) return fail(lat, CMLBM_EINVAL, "io_dtype must be FP64/FP32");
     hipStream_t s = (hipStream_t)hip_stream;
+    in_graph(lat, s);
     int rc = ensure_mask(lat, s);
     if (rc) return rc;
     rc = ensure_force(lat, s);
@@ -2755,6 +2762,7 @@ int cmlbm_load_populations(cmlbm_lattice* lat, const double* dev_in, void* hip_s
     if (lat->p.storage == CMLBM_MOM32)
         return fail(lat, CMLBM_EINVAL, "moment storage keeps nine numbers per cell: populations cannot be loaded");
     hipStream_t s = (hipStream_t)hip_stream;
+    in_graph(lat, s);
     int rc = ensure_mask(lat, s);
     if (rc) return rc;
     rc = ensure_force(lat, s);
@@ -2772,11 +2780,11 @@ int cmlbm_step(cmlbm_lattice* lat, int32_t nsteps, void* hip_stream)
     if (!lat->initialized) return fail(lat, CMLBM_ESTATE, "step before init");
     hipStream_t s = (hipStream_t)hip_stream;
     const bool march = marches(lat, nsteps);
-    // A graph that holds an even number of steps can be replayed: every replay
-    // starts in the buffer that held the state at capture, so the steps have to
-    // end there.  Each launch changes buffers once, so under capture the
-    // launches of two steps come in pairs (those of three change nothing).
-    const bool pairs = !march && tile_steps(lat, nsteps) && capturing(s);
+    // A graph keeps the buffers of its capture, so once a call is in one, the state
+    // has to be where the number of steps alone puts it: an even number of steps
+    // ends in the buffer it starts in.  Each launch changes buffers once, so the
+    // launches of two steps then come in pairs (those of three change nothing).
+    const bool pairs = in_graph(lat, s) && !march && tile_steps(lat, nsteps);
     bool second = false;
     for (int32_t k = 0; k < nsteps;) {
         int many = march ? 0 : tile_steps(lat, nsteps - k);
@@ -2808,6 +2816,7 @@ int cmlbm_step_velocity(cmlbm_lattice* lat, void* dev_u, int io_dtype, void* hip
     if (!lat->initialized) return fail(lat, CMLBM_ESTATE, "step before init");
     if (!dev_u) return fail(lat, CMLBM_EINVAL, "step_velocity needs dev_u[3][N]");
     hipStream_t s = (hipStream_t)hip_stream;
+    in_graph(lat, s);
     int rc;
     if (velocity_fused(lat, io_dtype)) {
         rc = launch_step_velocity(lat, dev_u, s);
@@ -2828,6 +2837,7 @@ int cmlbm_moments(cmlbm_lattice* lat, void* dev_rho, void* dev_u, int io_dtype, 
     if (io_dtype != CMLBM_FP64 && io_dtype != CMLBM_FP32) return fail(lat, CMLBM_EINVAL, "io_dtype must be FP64/FP32");
     if (!lat->initialized) return fail(lat, CMLBM_ESTATE, "moments before init");
     if (!dev_rho && !dev_u) return CMLBM_OK;
+    in_graph(lat, (hipStream_t)hip_stream);
     return launch_gather(lat, dev_rho, dev_u, io_dtype == CMLBM_FP64, nullptr, (hipStream_t)hip_stream);
 }
 
@@ -2837,6 +2847,7 @@ int cmlbm_populations(cmlbm_lattice* lat, double* dev_out, void* hip_stream)
     if (lat->p.storage == CMLBM_MOM32)
         return fail(lat, CMLBM_ESTATE, "moment storage keeps the post-collision state: no pre-collision populations");
     if (!lat->initialized) return fail(lat, CMLBM_ESTATE, "populations before init");
+    in_graph(lat, (hipStream_t)hip_stream);
     return launch_gather(lat, nullptr, nullptr, 1, dev_out, (hipStream_t)hip_stream);
 }
 
@@ -2918,6 +2929,7 @@ int cmlbm_save_state(cmlbm_lattice* lat, void* dev_blob, size_t blob_bytes, void
     Layout L;
     make_layout(&lat->p, &L);
     if (blob_bytes < L.pop_bytes) return fail(lat, CMLBM_ENOMEM, "state blob too small");
+    in_graph(lat, (hipStream_t)hip_stream);
     return hip_check(lat,
                      hipMemcpyAsync(dev_blob, lat->pop[lat->cur], L.pop_bytes, hipMemcpyDeviceToDevice,
                                     (hipStream_t)hip_stream),
@@ -2931,6 +2943,7 @@ int cmlbm_restore_state(cmlbm_lattice* lat, const void* dev_blob, size_t blob_by
     make_layout(&lat->p, &L);
     if (blob_bytes < L.pop_bytes) return fail(lat, CMLBM_ENOMEM, "state blob too small");
     hipStream_t s = (hipStream_t)hip_stream;
+    in_graph(lat, s);
     int rc = ensure_mask(lat, s);
     if (rc) return rc;
     rc = ensure_force(lat, s);

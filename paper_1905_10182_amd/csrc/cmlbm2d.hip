@@ -657,6 +657,7 @@ struct cmlbm2d_lattice {
     double fu[2];  // UNIFORM force
     const void* field;
     bool initialized;
+    bool graph;  // a call has been captured: even calls end in the buffer they start in
     int64_t t;
     std::string err;
 };
@@ -930,12 +931,16 @@ Pass next_pass(const cmlbm2d_lattice* lat, int n, int parity)
     return of[first];
 }
 
-// Whether s is being captured into a graph (the null stream cannot be).
-bool capturing(hipStream_t s)
+// Whether calls on this lattice are in a HIP graph: noted by every entry that
+// reads or writes the state on s (the null stream cannot be captured).
+bool in_graph(cmlbm2d_lattice* lat, hipStream_t s)
 {
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (s && hipStreamIsCapturing(s, &status) != hipSuccess) (void)hipGetLastError();
-    return status == hipStreamCaptureStatusActive;
+    if (!lat->graph && s) {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &status) != hipSuccess) (void)hipGetLastError();
+        lat->graph = status == hipStreamCaptureStatusActive;
+    }
+    return lat->graph;
 }
 
 template <int ST>
@@ -1044,6 +1049,7 @@ int cmlbm2d_create(const cmlbm2d_params* params, void* pop_a, size_t pop_a_bytes
     lat->fu[0] = lat->fu[1] = 0.0;
     lat->field = nullptr;
     lat->initialized = false;
+    lat->graph = false;
     lat->t = 0;
     *out = lat;
     return CMLBM2D_OK;
@@ -1089,6 +1095,7 @@ int cmlbm2d_init(cmlbm2d_lattice* lat, const void* dev_rho, const void* dev_u, i
     if (!lat) return CMLBM2D_EINVAL;
     if (io_dtype != CMLBM2D_FP64 && io_dtype != CMLBM2D_FP32)
         return fail(lat, CMLBM2D_EINVAL, "io_dtype must be FP64 or FP32");
+    in_graph(lat, (hipStream_t)hip_stream);
     launch_init(lat, io_dtype == CMLBM2D_FP64 ? INIT_EQ_F64 : INIT_EQ_F32, dev_rho, dev_u, nullptr,
                 (hipStream_t)hip_stream);
     const int rc = launch_check(lat, "init");
@@ -1104,11 +1111,11 @@ int cmlbm2d_step(cmlbm2d_lattice* lat, int32_t nsteps, void* hip_stream)
     if (nsteps < 0) return fail(lat, CMLBM2D_EINVAL, "nsteps must be >= 0");
     if (!lat->initialized) return fail(lat, CMLBM2D_ESTATE, "step before init");
     hipStream_t s = (hipStream_t)hip_stream;
-    // A graph that holds an even number of steps can be replayed: every replay
-    // starts in the buffer that held the state at capture, so the steps have to
-    // end there.  A pass changes buffers once, so under capture the passes of
-    // an even number of steps come in pairs.
-    int parity = nsteps > 1 && capturing(s) ? 0 : -1;
+    // A graph keeps the buffers of its capture, so once a call is in one, the state
+    // has to be where the number of steps alone puts it: an even number of steps
+    // ends in the buffer it starts in.  A pass changes buffers once, so the passes
+    // of an even number of steps then come in pairs.
+    int parity = in_graph(lat, s) ? 0 : -1;
     for (int32_t k = 0; k < nsteps;) {
         const Pass p = next_pass(lat, nsteps - k, parity);
         if (parity >= 0 && p.steps % 2 == 0) parity = 1 - parity;
@@ -1129,6 +1136,7 @@ int cmlbm2d_moments(cmlbm2d_lattice* lat, void* dev_rho, void* dev_u, int io_dty
         return fail(lat, CMLBM2D_EINVAL, "io_dtype must be FP64 or FP32");
     if (!lat->initialized) return fail(lat, CMLBM2D_ESTATE, "moments before init");
     if (!dev_rho && !dev_u) return CMLBM2D_OK;
+    in_graph(lat, (hipStream_t)hip_stream);
     launch_gather(lat, dev_rho, dev_u, io_dtype == CMLBM2D_FP64, nullptr, (hipStream_t)hip_stream);
     return launch_check(lat, "moments");
 }
@@ -1137,6 +1145,7 @@ int cmlbm2d_populations(cmlbm2d_lattice* lat, double* dev_out, void* hip_stream)
 {
     if (!lat || !dev_out) return CMLBM2D_EINVAL;
     if (!lat->initialized) return fail(lat, CMLBM2D_ESTATE, "populations before init");
+    in_graph(lat, (hipStream_t)hip_stream);
     launch_gather(lat, nullptr, nullptr, 1, dev_out, (hipStream_t)hip_stream);
     return launch_check(lat, "populations");
 }
@@ -1144,6 +1153,7 @@ int cmlbm2d_populations(cmlbm2d_lattice* lat, double* dev_out, void* hip_stream)
 int cmlbm2d_load_populations(cmlbm2d_lattice* lat, const double* dev_in, void* hip_stream)
 {
     if (!lat || !dev_in) return CMLBM2D_EINVAL;
+    in_graph(lat, (hipStream_t)hip_stream);
     launch_init(lat, INIT_POPS_F64, nullptr, nullptr, dev_in, (hipStream_t)hip_stream);
     const int rc = launch_check(lat, "load populations");
     if (rc) return rc;

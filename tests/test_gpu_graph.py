@@ -34,6 +34,16 @@ def check_replays(make, f, n):
     A.step(n)  # and ordinary calls go on from there
     B.step(n)
     assert torch.equal(A.populations(), B.populations())
+    # the same lattice by turns: a new state, ordinary calls, the new state again, the graph
+    f2 = f.flip(-1).contiguous()
+    A.load_populations(f2)
+    A.step(n)
+    A.step(2)
+    want = A.populations()
+    A.load_populations(f2)
+    graph.replay()
+    A.step(2)
+    assert torch.equal(A.populations(), want)
 
 
 def populations(q, shape):

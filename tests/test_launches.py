@@ -76,6 +76,43 @@ for dims, fail in (((64, 64, 64), 0), ((64, 64, 64), 1), ((64, 64, 64), 3), ((48
                      [EHIP, 2, [0] * 4, 0, 0]]
 
 
+def test_calls_between_replays_keep_the_buffers():
+    """Once any call on a lattice has been captured, ordinary calls of an even
+    number of steps end in the buffer they start in as well: a graph goes on from
+    the buffers of its capture.  Until then they take the fewest launches."""
+    runs = launches("""
+out = []
+firsts3 = [lambda h: L3.cmlbm_step(h, 2, STREAM), lambda h: L3.cmlbm_moments(h, F, None, 0, STREAM),
+           lambda h: L3.cmlbm_populations(h, F, STREAM), lambda h: L3.cmlbm_step_velocity(h, F, 0, STREAM),
+           lambda h: L3.cmlbm_save_state(h, F, 1 << 40, STREAM), lambda h: L3.cmlbm_restore_state(h, F, 1 << 40, STREAM),
+           lambda h: L3.cmlbm_load_populations(h, F, STREAM)]
+firsts2 = [lambda h: L2.cmlbm2d_step(h, 1, STREAM), lambda h: L2.cmlbm2d_moments(h, F, None, 0, STREAM),
+           lambda h: L2.cmlbm2d_populations(h, F, STREAM), lambda h: L2.cmlbm2d_load_populations(h, F, STREAM)]
+for make, step, firsts in ((lambda: handle3(8, 9, 8, 30), L3.cmlbm_step, firsts3),
+                           (lambda: handle2(2048, 2048), L2.cmlbm2d_step, firsts2)):
+    for first in firsts:
+        h = make()
+        assert step(h, 2, STREAM) == 0
+        rec()
+        assert step(h, 2, STREAM) == 0
+        before = len(seen())
+        rec(capture=1)
+        assert first(h) == 0
+        rec(capture=0)
+        rows = []
+        for n in (2, 4, 6, 8):
+            rec()
+            assert step(h, n, None) == 0
+            rows.append(seen())
+        out.append([before, rows])
+""")
+    assert len(runs) == 11
+    for before, calls in runs:
+        assert before == 1
+        for rows in calls:
+            assert len(rows) % 2 == 0 and rows[0][3] == rows[-1][4]
+
+
 def conv_launches(cases):
     """The kernel, grid and block of forward convolutions ((n, d, h, w), input and output channels)."""
     return launches(f"""
