@@ -2329,12 +2329,15 @@ void launch_tile_t(cmlbm_lattice* lat, hipStream_t s)
 
 // How many of n steps one launch of k_tile takes (0: none).  The tile's halo
 // makes it do 4.1 (three steps) or 2.4 (two) collisions per cell and step, so
-// it pays only while every workgroup has a CU of its own; two steps at a time
-// also with two workgroups a CU where k_step's waves are mostly idle lanes:
-// rows so short that they make two waves a SIMD all the same (k_tile's figures:
-// 32^3, 512 tiles and 1024 waves, against 8 x 60 x 60, 450 and 3600), and there
-// three at a time for the last three steps, which beats two and one (8 x 9 x 8 by
-// 30, FP32: 15.6 / 17.3 us).  A halo cell wraps around an axis once: no axis
+// it pays while every workgroup has a CU of its own.  Up to two workgroups a CU,
+// two steps at a time also pay where k_step starts more than a wave a SIMD for
+// the same cells, on rows that leave most lanes idle (FP32, us a step, k_tile /
+// k_step: 22 x 36 x 31, 1116 waves: 4.6 / 5.2; 8 x 60 x 60, 3600: 4.7 / 8.8; but
+// 32^3, 1024: 4.7 / 4.2), and in FP32 with a wall or solid cells at any number of
+// waves (32^3: 4.9 / 5.1).  FP32 alone has registers for two workgroups of
+// three steps a CU: there they take the last three of a call (8 x 9 x 8 by 30: 15.6 us,
+// two steps and one 17.3) and the short rows that have too many tiles of two
+// (11 x 42 x 51 with walls: 5.6 / 7.6).  A halo cell wraps around an axis once: no axis
 // shorter than a tile and its halo.
 int tile_steps(const cmlbm_lattice* lat, int n)
 {
@@ -2345,10 +2348,12 @@ int tile_steps(const cmlbm_lattice* lat, int n)
     const uint64_t cus = lat->cus > 0 ? lat->cus : 256;
     const uint64_t t3 = tile_count<3, 4, 4, 4>(g), t2 = tile_count<2, 8, 4, 2>(g);
     if (n >= 3 && t3 <= cus) return 3;
-    const uint64_t waves = (uint64_t)g.rows * (uint64_t)((g.nx + 63) / 64);
     if (t2 <= cus) return 2;
-    if (t2 > 2 * cus || waves < 8 * cus) return 0;
-    return n == 3 && t3 <= 2 * cus ? 3 : 2;
+    const bool many_waves = (uint64_t)g.rows * (uint64_t)((g.nx + 63) / 64) > 4 * cus;
+    const bool three = !f64 && n >= 3 && t3 <= 2 * cus;
+    if (t2 > 2 * cus) return many_waves && three ? 3 : 0;
+    if (!many_waves && (f64 || !lat->needs_mask)) return 0;
+    return three && n == 3 ? 3 : 2;
 }
 
 // Whether calls on this lattice are in a HIP graph: noted by every entry that
